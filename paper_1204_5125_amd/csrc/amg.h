@@ -42,7 +42,10 @@ struct Level {
     Csr P, R;
     DevBuf<int> rsrc;           // R entry q = conj(P entry rsrc[q])
     DevBuf<double> rho;         // estimate of rho(D^-1 A) (device scalar)
-    DevBuf<int> rap_tp, rap_trip;  // products (p, q, s) of each entry of A_{l+1}, upper triangle
+    Csr AP;                     // A P (FP64), the first half of the Galerkin product
+    DevBuf<int> rap_tp;         // pairs (R entry, A P entry) of each entry of A_{l+1}, upper triangle
+    DevBuf<int2> rap_pair;
+    DevBuf<int> rap_mir;        // the mirror entry of each upper entry
     // Copies used by the V-cycle: levels >= 1 renumbered so that every colour
     // is one contiguous row range (new index r' = position in cperm).
     DevBuf<int> perm, iperm;        // new -> old, old -> new (l >= 1)

@@ -66,30 +66,53 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile(const int *__restrict__ in
     if (threadIdx.x == kBlock - 1) bsum[blockIdx.x] = sm[kBlock - 1];
 }
 
-__global__ void k_scan_add(int *out, const int *boff, int n)
+// out[i] += the offset of i's tile, and out[n] = the total
+__global__ void k_scan_add(int *out, const int *boff, const int *bsum, int n, int nb)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) out[i] += boff[i / kScanTile];
+    if (i < n) {
+        if (nb > 1) out[i] += boff[i / kScanTile];
+    } else if (i == n) {
+        out[n] = (nb > 1 ? boff[nb - 1] : 0) + bsum[nb - 1];
+    }
 }
 
-// exclusive scan of in[0..n) into out; returns the total (synchronises s)
-static int64_t scan_excl(const int *in, int *out, int n, hipStream_t s)
+// Scratch of one symbolic phase, grown as needed and kept until it ends (an
+// allocation per use cost more than most of the kernels it served).
+struct SymTmp {
+    DevBuf<int> scan;             // tile sums and offsets
+    DevBuf<int> a, b, c, d, e, f; // per-row work arrays
+    DevBuf<int> flags;            // "undecided nodes are left" of a batch of rounds
+    DevBuf<int> err;
+};
+
+static int *need(DevBuf<int> &b, size_t n)
+{
+    if (b.count < n) b.alloc(n);
+    return b.get();
+}
+
+static void scan_tiles(const int *in, int *out, int n, int *tmp, hipStream_t s)
+{
+    const int nb = (n + kScanTile - 1) / kScanTile;
+    int *bsum = tmp, *boff = tmp + nb + 1;
+    k_scan_tile<<<nb, kBlock, 0, s>>>(in, out, bsum, n);
+    GLK_CHECK_LAUNCH();
+    if (nb > 1) scan_tiles(bsum, boff, nb, tmp + 2 * (nb + 1), s);
+    k_scan_add<<<blocks_for((int64_t)n + 1), kBlock, 0, s>>>(out, boff, bsum, n, nb);
+    GLK_CHECK_LAUNCH();
+}
+
+// exclusive scan of in[0..n) into out[0..n], out[n] the total, which is also
+// returned (synchronises s); in and out must not overlap
+static int64_t scan_excl(const int *in, int *out, int n, SymTmp &T, hipStream_t s)
 {
     if (n <= 0) return 0;
-    const int nb = (n + kScanTile - 1) / kScanTile;
-    DevBuf<int> bsum(nb), boff(nb);
-    k_scan_tile<<<nb, kBlock, 0, s>>>(in, out, bsum.get(), n);
-    GLK_CHECK_LAUNCH();
-    if (nb > 1) {
-        scan_excl(bsum.get(), boff.get(), nb, s);
-        k_scan_add<<<blocks_for(n), kBlock, 0, s>>>(out, boff.get(), n);
-        GLK_CHECK_LAUNCH();
-    }
-    int last_out = 0, last_in = 0;
-    GLK_HIP(hipMemcpyAsync(&last_out, out + n - 1, sizeof(int), hipMemcpyDeviceToHost, s));
-    GLK_HIP(hipMemcpyAsync(&last_in, in + n - 1, sizeof(int), hipMemcpyDeviceToHost, s));
+    scan_tiles(in, out, n, need(T.scan, 4 * ((size_t)n / kScanTile + 4) + 64), s);
+    int total = 0;
+    GLK_HIP(hipMemcpyAsync(&total, out + n, sizeof(int), hipMemcpyDeviceToHost, s));
     GLK_HIP(hipStreamSynchronize(s));
-    return (int64_t)last_out + last_in;
+    return (int64_t)total;
 }
 
 // ---------------------------------------------------------- keys ------
@@ -249,46 +272,67 @@ __global__ void k_fill_int(int *a, int n, int val)
     if (i < n) a[i] = val;
 }
 
-__global__ void k_mis_m1(int n, const int *rp, const int *ci, const int *state, unsigned long long *m1)
+// A word that other threads of the same kernel may be writing: an old value
+// only delays a decision.
+__device__ __forceinline__ int load_relaxed(const int *p)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    unsigned long long best = 0;
-    for (int p = rp[i]; p < rp[i + 1]; ++p) {
-        const int j = ci[p];
-        if (state[j] == 0) best = max(best, keyof(j) + 1ull);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void store_relaxed(int *p, int v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// One round of the distance-2 independent set (state 0 undecided, 1 root, 2
+// not a root).  A node is not a root once a root lies within distance 2, and is
+// one once every smaller index within distance 2 is decided and no root is
+// there: the outcome is the serial greedy one whatever order the threads
+// decide in, so states are read and written in place, one kernel a round
+// (four, with the nodes left counted by one atomic each, cost 7.4 ms of a
+// 257^2 setup).  A node whose smallest neighbour is undecided is far from the
+// front and waits; the others are listed in LDS and get kMisLanes lanes each,
+// which take the neighbours in turn with a batch of loads in flight (a thread
+// walking the 25 words of its neighbourhood one by one took 23 us a round).
+// flag (nullable): set when a node was undecided before this round.
+constexpr int kMisLanes = 8;
+
+__global__ __launch_bounds__(kBlock) void k_mis_round(int n, const int *__restrict__ rp, const int *__restrict__ ci,
+                                                      int *state, int *flag)
+{
+    __shared__ int list[kBlock];
+    __shared__ int count;
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    {
+        const int i = blockIdx.x * kBlock + threadIdx.x;
+        const bool open = i < n && load_relaxed(state + i) == 0;
+        if (open) {
+            const int first = ci[rp[i]];
+            if (first >= i || load_relaxed(state + first) != 0) list[atomicAdd(&count, 1)] = i;
+        }
+        if (flag && __syncthreads_or(open) && threadIdx.x == 0) *flag = 1;
     }
-    m1[i] = best;
-}
-
-__global__ void k_mis_select(int n, const int *rp, const int *ci, const unsigned long long *m1,
-                             int *state)
-{
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n || state[i] != 0) return;
-    unsigned long long best = 0;
-    for (int p = rp[i]; p < rp[i + 1]; ++p) best = max(best, m1[ci[p]]);
-    if (best == keyof(i) + 1ull) state[i] = 1;
-}
-
-__global__ void k_mis_near(int n, const int *rp, const int *ci, const int *state, int *near1)
-{
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    int r = 0;
-    for (int p = rp[i]; p < rp[i + 1]; ++p) r |= (state[ci[p]] == 1);
-    near1[i] = r;
-}
-
-__global__ void k_mis_remove(int n, const int *rp, const int *ci, const int *near1, int *state,
-                             int *remaining)
-{
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n || state[i] != 0) return;
-    int r = 0;
-    for (int p = rp[i]; p < rp[i + 1]; ++p) r |= near1[ci[p]];
-    if (r) state[i] = 2;
-    else atomicAdd(remaining, 1);
+    __syncthreads();
+    const int lane = threadIdx.x % kMisLanes, total = count;
+    for (int c = threadIdx.x / kMisLanes; c < total; c += kBlock / kMisLanes) {
+        const int i = list[c];
+        int seen = 0;  // bit 0: a root nearby, bit 1: a smaller undecided node
+        for (int p = rp[i] + lane; p < rp[i + 1]; p += kMisLanes) {
+            const int j = ci[p], e = rp[j + 1];
+            for (int q = rp[j]; q < e; q += 8) {  // j itself among its columns
+                int k[8], sk[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) k[u] = q + u < e ? ci[q + u] : i;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) sk[u] = load_relaxed(state + k[u]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) seen |= (sk[u] == 1 ? 1 : 0) | (sk[u] == 0 && k[u] < i ? 2 : 0);
+            }
+        }
+#pragma unroll
+        for (int o = kMisLanes / 2; o > 0; o >>= 1) seen |= __shfl_xor(seen, o, 64);
+        if (lane == 0 && seen != 2) store_relaxed(state + i, seen & 1 ? 2 : 1);
+    }
 }
 
 __global__ void k_agg_phase_a(int n, const int *rp, const int *ci, const int *state, int *rootA)
@@ -376,46 +420,208 @@ __global__ void k_transpose_fill(int n, const int *prp, const int *pci, const in
     }
 }
 
-__global__ void k_sort_rows(int nr, const int *rrp, int *rci, int *rsrc)
+constexpr int kRowWaves = kBlock / 64;  // rows per work-group of the wave-per-row kernels
+
+__device__ __forceinline__ void wave_sync()
 {
-    const int r = blockIdx.x * kBlock + threadIdx.x;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// rows of the transpose in ascending column order, a wave per row: an entry's
+// place is the number of smaller columns (an insertion sort by one thread per
+// row took 48 ms for the 129^3 grid)
+__global__ __launch_bounds__(kBlock) void k_sort_rows(int nr, const int *__restrict__ rrp,
+                                                      const int *__restrict__ ci_in, const int *__restrict__ src_in,
+                                                      int *__restrict__ rci, int *__restrict__ rsrc)
+{
+    const int r = blockIdx.x * kRowWaves + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (r >= nr) return;
     const int b = rrp[r], e = rrp[r + 1];
-    for (int p = b + 1; p < e; ++p) {
-        const int kc = rci[p], ks = rsrc[p];
-        int q = p - 1;
-        while (q >= b && rci[q] > kc) {
-            rci[q + 1] = rci[q];
-            rsrc[q + 1] = rsrc[q];
-            --q;
+    for (int p0 = b; p0 < e; p0 += 64) {
+        const int p = p0 + lane;
+        const int c = p < e ? ci_in[p] : 0;
+        int rank = 0;
+        for (int q = b; q < e; ++q) rank += ci_in[q] < c;
+        if (p < e) {
+            rci[b + rank] = c;
+            rsrc[b + rank] = src_in[p];
         }
-        rci[q + 1] = kc;
-        rsrc[q + 1] = ks;
     }
 }
 
-// pattern of R A P, row by row
-__global__ void k_rap_pattern(int nc, const int *rrp, const int *rci, const int *arp, const int *aci,
-                              const int *prp, const int *pci, const int *crp, int *cnt, int *cci,
-                              int *err)
+// pattern of A P, a thread per row
+__global__ void k_ap_pattern(int n, const int *rp, const int *ci, const int *prp, const int *pci, const int *aprp,
+                             int *cnt, int *apci, int *err)
 {
-    const int I = blockIdx.x * kBlock + threadIdx.x;
-    if (I >= nc) return;
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n) return;
     int buf[kMaxRow];
     int u = 0;
-    for (int p = rrp[I]; p < rrp[I + 1]; ++p) {
-        const int i = rci[p];
-        for (int q = arp[i]; q < arp[i + 1]; ++q) {
-            const int j = aci[q];
-            for (int s = prp[j]; s < prp[j + 1]; ++s)
-                if (!sorted_insert(buf, u, pci[s])) { atomicOr(err, 4); return; }
+    for (int q = rp[i]; q < rp[i + 1]; ++q) {
+        const int j = ci[q];
+        for (int s = prp[j]; s < prp[j + 1]; ++s)
+            if (!sorted_insert(buf, u, pci[s])) { atomicOr(err, 4); return; }
+    }
+    if (apci) {
+        const int o = aprp[i];
+        for (int t = 0; t < u; ++t) apci[o + t] = buf[t];
+    } else {
+        cnt[i] = u;
+    }
+}
+
+// The pairs (R entry p, A P entry k of row rci[p]) of coarse row I, which make
+// up row I of R (A P), dealt to the lanes of a wave 64 at a time in row order:
+// f(valid, p, k).  pre: 64 words of LDS.
+template <class F>
+__device__ __forceinline__ void wave_pairs(int b, int e, const int *__restrict__ rci, const int *__restrict__ aprp,
+                                           int *pre, int lane, F &&f)
+{
+    for (int base = b; base < e; base += 64) {
+        const int p = base + lane, i = p < e ? rci[p] : 0;
+        const int o = p < e ? aprp[i] : 0, len = p < e ? aprp[i + 1] - o : 0;
+        int sum = len;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(sum, d, 64);
+            if (lane >= d) sum += v;
+        }
+        const int total = __shfl(sum, 63, 64);
+        wave_sync();
+        pre[lane] = sum - len;
+        wave_sync();
+        for (int f0 = 0; f0 < total; f0 += 64) {
+            const int idx = f0 + lane;
+            int l = 0;  // the last lane whose pairs start at or before idx
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1)
+                if (pre[l + d] <= idx) l += d;
+            const int k = __shfl(o, l, 64) + idx - pre[l];
+            f(idx < total, base + l, k);
         }
     }
-    if (cci) {
-        const int o = crp[I];
-        for (int t = 0; t < u; ++t) cci[o + t] = buf[t];
-    } else {
-        cnt[I] = u;
+}
+
+// Pattern of R (A P), a wave per coarse row: the row's columns gathered in an
+// LDS hash set, compacted, and placed by the number of smaller ones.  A row of
+// more than kMaxRow columns is refused (err 4).  (A thread per row inserting
+// the columns of R A P one by one into a sorted list took 217 ms for the first
+// level of the 129^3 grid, twice; see k_rap_pairs.)
+constexpr int kHash = 2 * kMaxRow;
+
+__global__ __launch_bounds__(kBlock) void k_rap_pattern(int nc, const int *__restrict__ rrp,
+                                                        const int *__restrict__ rci, const int *__restrict__ aprp,
+                                                        const int *__restrict__ apci, const int *__restrict__ crp,
+                                                        int *cnt, int *cci, int *err)
+{
+    __shared__ int s_tab[kRowWaves][kHash], s_list[kRowWaves][kMaxRow], s_pre[kRowWaves][64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, I = blockIdx.x * kRowWaves + w;
+    if (I >= nc) return;
+    int *tab = s_tab[w], *list = s_list[w];
+    for (int t = lane; t < kHash; t += 64) tab[t] = -1;
+    wave_sync();
+    int fresh = 0;
+    bool full = false;
+    wave_pairs(rrp[I], rrp[I + 1], rci, aprp, s_pre[w], lane, [&](bool valid, int, int k) {
+        if (!valid) return;
+        const int c = apci[k];
+        unsigned h = ((unsigned)c * 2654435761u) % kHash;
+        int tries = 0;
+        for (; tries < kHash; ++tries, h = (h + 1) % kHash) {
+            const int old = atomicCAS(&tab[h], -1, c);
+            if (old == -1) ++fresh;
+            if (old == -1 || old == c) break;
+        }
+        full |= tries == kHash;
+    });
+    for (int d = 32; d > 0; d >>= 1) fresh += __shfl_xor(fresh, d, 64);
+    if (__any(full) || fresh > kMaxRow) {
+        if (lane == 0) atomicOr(err, 4);
+        return;
+    }
+    if (!cci) {
+        if (lane == 0) cnt[I] = fresh;
+        return;
+    }
+    wave_sync();
+    int at = 0;
+    for (int t0 = 0; t0 < kHash; t0 += 64) {
+        const int c = tab[t0 + lane];
+        const unsigned long long m = __ballot(c >= 0);
+        if (c >= 0) list[at + __popcll(m & ((1ull << lane) - 1))] = c;
+        at += __popcll(m);
+    }
+    wave_sync();
+    const int o = crp[I];
+    for (int t = lane; t < at; t += 64) {
+        const int c = list[t];
+        int rank = 0;
+        for (int k = 0; k < at; ++k) rank += list[k] < c;
+        cci[o + rank] = c;
+    }
+}
+
+// The pairs of every entry of the upper triangle (J >= I) of R (A P), a wave
+// per coarse row: counted (pair == NULL: cnt[t]), or listed in row order
+// (pair[tp[t] ..]).  A chunk of 64 pairs is ordered among itself by comparing
+// every lane's entry with the earlier lanes', so the lists are the same in
+// every run.
+__global__ __launch_bounds__(kBlock) void k_rap_pairs(int nc, const int *__restrict__ rrp,
+                                                      const int *__restrict__ rci, const int *__restrict__ aprp,
+                                                      const int *__restrict__ apci, const int *__restrict__ crp,
+                                                      const int *__restrict__ cci, int *__restrict__ cnt,
+                                                      const int *__restrict__ tp, int2 *__restrict__ pair)
+{
+    __shared__ int s_col[kRowWaves][kMaxRow], s_cur[kRowWaves][kMaxRow], s_pre[kRowWaves][64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, I = blockIdx.x * kRowWaves + w;
+    if (I >= nc) return;
+    int *col = s_col[w], *cur = s_cur[w];
+    const int cb = crp[I], u = crp[I + 1] - cb;
+    for (int t = lane; t < u; t += 64) {
+        col[t] = cci[cb + t];
+        cur[t] = pair ? tp[cb + t] : 0;
+    }
+    wave_sync();
+    wave_pairs(rrp[I], rrp[I + 1], rci, aprp, s_pre[w], lane, [&](bool valid, int p, int k) {
+        const int J = valid ? apci[k] : -1;
+        int t = -1;
+        if (J >= I) t = find_col(col, 0, u, J);
+        if (!pair) {
+            if (t >= 0) atomicAdd(&cur[t], 1);
+            return;
+        }
+        int before = 0, all = 0;
+        for (int l = 0; l < 64; ++l) {
+            const bool same = __builtin_amdgcn_readlane(t, l) == t;
+            before += same && l < lane;
+            all += same;
+        }
+        if (t >= 0) {
+            const int at = cur[t];
+            pair[at + before] = make_int2(p, k);
+            if (before == all - 1) cur[t] = at + all;
+        }
+        wave_sync();
+    });
+    if (pair) return;
+    wave_sync();
+    for (int t = lane; t < u; t += 64) cnt[cb + t] = cur[t];
+}
+
+// mir[t] for an upper entry t = (I, J), J > I: the entry (J, I) (the pattern of
+// R A P is symmetric); the diagonal's own index
+__global__ void k_rap_mirror(int nc, const int *__restrict__ crp, const int *__restrict__ cci, int *__restrict__ mir,
+                             int *err)
+{
+    const int g = blockIdx.x * kBlock + threadIdx.x, I = g / 8, lane = g % 8;
+    if (I >= nc) return;
+    for (int t = crp[I] + lane; t < crp[I + 1]; t += 8) {
+        const int J = cci[t];
+        if (J < I) continue;
+        const int u = find_col(cci, crp[J], crp[J + 1], I);
+        if (u >= crp[J + 1] || cci[u] != I) atomicOr(err, 16);
+        mir[t] = u;
     }
 }
 
@@ -432,48 +638,35 @@ __global__ void k_parity_colour(Geom g, int *col)
 
 constexpr int kRecolourPasses = 2;  // iterated-greedy passes after the colouring rounds
 
-// colour priority: the smaller index first (the rounds then reproduce the
-// serial greedy colouring in index order)
-__device__ __forceinline__ unsigned long long colour_key(int i)
-{
-    return (unsigned long long)(0xFFFFFFFFu - (uint32_t)i);
-}
-
-__global__ void k_jp_ready(int n, const int *rp, const int *ci, const int *col, int *ready)
+// One round of the greedy colouring in index order: a node takes the smallest
+// colour free among its smaller neighbours once all of them are coloured (the
+// serial result whatever order the threads decide in; see k_mis_round).
+__global__ __launch_bounds__(kBlock) void k_jp_round(int n, const int *__restrict__ rp, const int *__restrict__ ci,
+                                                     int *col, int *flag, int *err)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    int r = 0;
-    if (col[i] < 0) {
-        r = 1;
-        const unsigned long long k = colour_key(i);
-        for (int p = rp[i]; p < rp[i + 1]; ++p) {
-            const int j = ci[p];
-            if (j != i && col[j] < 0 && colour_key(j) > k) { r = 0; break; }
-        }
-    }
-    ready[i] = r;
-}
-
-__global__ void k_jp_colour(int n, const int *rp, const int *ci, const int *ready, int *col,
-                            int *remaining, int *err)
-{
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    if (!ready[i]) {
-        if (col[i] < 0) atomicAdd(remaining, 1);
-        return;
-    }
+    const bool open = i < n && load_relaxed(col + i) < 0;
+    if (flag && __syncthreads_or(open) && threadIdx.x == 0) *flag = 1;
+    if (!open) return;
+    const int b = rp[i], e = rp[i + 1];
     unsigned long long used[4] = {0, 0, 0, 0};
-    for (int p = rp[i]; p < rp[i + 1]; ++p) {
-        const int j = ci[p];
-        const int c = (j != i) ? col[j] : -1;
-        if (c >= 0 && c < 256) used[c >> 6] |= 1ull << (c & 63);
+    for (int p = b; p < e; p += 4) {  // columns ascend
+        int j[4], c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) j[u] = p + u < e ? ci[p + u] : i;
+        if (j[0] >= i) break;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = j[u] < i ? load_relaxed(col + j[u]) : 256;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (c[u] < 0) return;
+            if (c[u] < 256) used[c[u] >> 6] |= 1ull << (c[u] & 63);
+        }
     }
     int c = 0;
     while (c < 256 && (used[c >> 6] >> (c & 63) & 1ull)) ++c;
     if (c == 256) atomicOr(err, 8);
-    col[i] = c;
+    store_relaxed(col + i, c);
 }
 
 // Iterated greedy (Culberson): the rows of one colour class (an independent
@@ -495,22 +688,61 @@ __global__ void k_ig_class(int n, const int *rp, const int *ci, const int *old, 
     nw[i] = c;
 }
 
-__global__ void k_colour_hist(int n, const int *col, int *hist)
+// Rows grouped by colour, ascending inside a colour: rows of each colour per
+// block (cnt[c nblk + block]; a colour the block lacks counts 0), and, after an
+// exclusive scan of those counts, the places.
+__global__ __launch_bounds__(kBlock) void k_colour_count(int n, const int *__restrict__ col, int nblk, int ncol,
+                                                         int *__restrict__ cnt)
 {
+    __shared__ int h[257];
+    for (int c = threadIdx.x; c < 257; c += kBlock) h[c] = 0;
+    __syncthreads();
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) atomicAdd(&hist[col[i]], 1);
+    if (i < n) atomicAdd(&h[col[i]], 1);
+    __syncthreads();
+    for (int c = threadIdx.x; c < ncol; c += kBlock) cnt[(size_t)c * nblk + blockIdx.x] = h[c];
 }
 
-__global__ void k_flag_eq(int n, const int *col, int c, int *flag)
+__global__ __launch_bounds__(kBlock) void k_colour_place(int n, const int *__restrict__ col, int nblk,
+                                                         const int *__restrict__ off, int *__restrict__ dst)
 {
+    __shared__ int sc[kBlock];
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) flag[i] = (col[i] == c);
+    const int c = i < n ? col[i] : -1;
+    sc[threadIdx.x] = c;
+    __syncthreads();
+    if (i >= n) return;
+    int before = 0;
+    for (int t = 0; t < (int)threadIdx.x; ++t) before += sc[t] == c;
+    dst[off[(size_t)c * nblk + blockIdx.x] + before] = i;
 }
 
-__global__ void k_scatter_colour(int n, const int *col, int c, const int *pos, int *dst)
+// rows of each colour: 257 counters per block in LDS, added to the totals
+__global__ __launch_bounds__(kBlock) void k_colour_hist(int n, const int *__restrict__ col, int *hist)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < n && col[i] == c) dst[pos[i]] = i;
+    __shared__ int h[257];
+    for (int c = threadIdx.x; c < 257; c += kBlock) h[c] = 0;
+    __syncthreads();
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) atomicAdd(&h[col[i]], 1);
+    __syncthreads();
+    for (int c = threadIdx.x; c < 257; c += kBlock)
+        if (h[c]) atomicAdd(&hist[c], h[c]);
+}
+
+// longest row of rows row0[c] .. row0[c + 1] - 1 (block c)
+__global__ __launch_bounds__(kBlock) void k_row_widths(const int *__restrict__ rp, const int *__restrict__ row0,
+                                                       int *__restrict__ width)
+{
+    __shared__ int sm[kBlock / 64];
+    int m = 1;
+    for (int r = row0[blockIdx.x] + threadIdx.x; r < row0[blockIdx.x + 1]; r += kBlock) m = max(m, rp[r + 1] - rp[r]);
+    for (int d = 32; d > 0; d >>= 1) m = max(m, __shfl_xor(m, d, 64));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kBlock / 64; ++k) m = max(m, sm[k]);
+        width[blockIdx.x] = m;
+    }
 }
 
 // --------------------------------------------------------- numeric ----
@@ -706,97 +938,77 @@ struct RValues {
     }
 };
 
-// Upper triangle (J >= I) of R A P.  The products of each stored entry are
-// listed once per hierarchy (symbolic), in the order of the row traversal
-// p (R row), q (A row), s (P row), and the numeric setup sums them in that
-// order, one thread per entry.
-template <class F>
-__device__ __forceinline__ void rap_traverse(int I, const int *rrp, const int *rci, const int *arp,
-                                             const int *aci, const int *prp, const int *pci, const int *cci,
-                                             int cb, int ce, F &&f)
-{
-    for (int p = rrp[I]; p < rrp[I + 1]; ++p) {
-        const int i = rci[p];
-        for (int q = arp[i]; q < arp[i + 1]; ++q) {
-            const int j = aci[q];
-            for (int s = prp[j]; s < prp[j + 1]; ++s) {
-                const int J = pci[s];
-                if (J < I) continue;
-                const int t = find_col(cci, cb, ce, J);
-                if (t < ce && cci[t] == J) f(t, p, q, s);
+// A_{l+1} = R (A P) in two products: A P is formed once (a fine row's entry is
+// used by every coarse row of its R column), so the second product has about a
+// third of the terms that R A P has term by term, and lists two indices per
+// term instead of three.
+// (A P)_ik = sum of A_ij P_jk over the row's j, LPR lanes per row, a lane per
+// entry; the lanes of a row read the same A and P entries.
+template <int LPR>
+struct ApValues {
+    int n;
+    const int *__restrict__ rp, *__restrict__ ci;
+    const double2 *__restrict__ av;
+    const int *__restrict__ prp, *__restrict__ pci;
+    const double2 *__restrict__ pv;
+    const int *__restrict__ aprp, *__restrict__ apci;
+    double2 *__restrict__ apv;
+    __device__ void operator()(int, int) const
+    {
+        const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+        const int i = (int)(g / LPR), lane = (int)(g % LPR);
+        if (i >= n) return;
+        const int b = rp[i], e = rp[i + 1], ke = aprp[i + 1];
+        for (int k = aprp[i] + lane; k < ke; k += LPR) {
+            const int c = apci[k];
+            double2 acc = make_double2(0.0, 0.0);
+            for (int q = b; q < e; ++q) {
+                const int j = ci[q], s1 = prp[j + 1];
+                int s = prp[j];
+                while (s < s1 && pci[s] < c) ++s;
+                if (s < s1 && pci[s] == c) acc = cadd(acc, cmul(av[q], pv[s]));
             }
+            apv[k] = acc;
         }
     }
-}
+};
 
-__global__ void k_rap_count(int nc, const int *rrp, const int *rci, const int *arp, const int *aci,
-                            const int *prp, const int *pci, const int *crp, const int *cci, int *cnt)
-{
-    const int I = blockIdx.x * kBlock + threadIdx.x;
-    if (I >= nc) return;
-    rap_traverse(I, rrp, rci, arp, aci, prp, pci, cci, crp[I], crp[I + 1],
-                 [&](int t, int, int, int) { cnt[t] += 1; });
-}
-
-__global__ void k_rap_fill(int nc, const int *rrp, const int *rci, const int *arp, const int *aci,
-                           const int *prp, const int *pci, const int *crp, const int *cci, const int *tp,
-                           int *fill, int *trip)
-{
-    const int I = blockIdx.x * kBlock + threadIdx.x;
-    if (I >= nc) return;
-    rap_traverse(I, rrp, rci, arp, aci, prp, pci, cci, crp[I], crp[I + 1], [&](int t, int p, int q, int s) {
-        const int k = tp[t] + fill[t]++;
-        trip[3 * k] = p;
-        trip[3 * k + 1] = q;
-        trip[3 * k + 2] = s;
-    });
-}
-
-// cv[t] = sum of (R_p A_q) P_s over the products of entry t (0 for J < I).
-// kRapLanes lanes share an entry: lane j sums products j, j + kRapLanes, ...
-// of its list in order, then the lanes are added by a fixed butterfly, so a
-// setup is bit-reproducible; neighbouring lanes read neighbouring triples.
+// Upper triangle (J >= I) of R (A P), mirrored: entry t = the sum of R_p (A P)_k
+// over its pairs, which are listed once per hierarchy (symbolic) in the order
+// of the row.  kRapLanes lanes share an entry: lane j sums pairs j, j +
+// kRapLanes, ... in order, then the lanes are added by a fixed butterfly, so a
+// setup is bit-reproducible; neighbouring lanes read neighbouring pairs.
 constexpr int kRapLanes = 8;
 
 struct RapValues {
     int nnz;
-    const int *__restrict__ tp, *__restrict__ trip;
-    const double2 *__restrict__ rv, *__restrict__ av, *__restrict__ pv;
+    const int *__restrict__ tp;
+    const int2 *__restrict__ pair;
+    const int *__restrict__ mir;
+    const double2 *__restrict__ rv, *__restrict__ apv;
     double2 *__restrict__ cv;
     __device__ void operator()(int, int) const
     {
         const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
         const int t = (int)(g / kRapLanes), lane = (int)(g % kRapLanes);
-        const bool act = t < nnz;
+        const int b = t < nnz ? tp[t] : 0, e = t < nnz ? tp[t + 1] : 0;
         double2 acc = make_double2(0.0, 0.0);
-        if (act)
-            for (int k = tp[t] + lane; k < tp[t + 1]; k += kRapLanes) {
-                const double2 ra = cmul(rv[trip[3 * k]], av[trip[3 * k + 1]]);
-                acc = cadd(acc, cmul(ra, pv[trip[3 * k + 2]]));
-            }
+        for (int k = b + lane; k < e; k += kRapLanes) {
+            const int2 q = pair[k];
+            acc = cadd(acc, cmul(rv[q.x], apv[q.y]));
+        }
     #pragma unroll
         for (int o = kRapLanes / 2; o > 0; o >>= 1) {
             acc.x += __shfl_xor(acc.x, o, 64);
             acc.y += __shfl_xor(acc.y, o, 64);
         }
-        if (act && lane == 0) cv[t] = acc;
-    }
-};
-
-struct RapMirror {
-    int nc;
-    const int *crp, *cci;
-    double2 *cv;
-    __device__ void operator()(int, int) const
-    {
-        const int I = blockIdx.x * kBlock + threadIdx.x;
-        if (I >= nc) return;
-        for (int t = crp[I]; t < crp[I + 1]; ++t) {
-            const int J = cci[t];
-            if (J > I) break;
-            if (J == I) { cv[t].y = 0.0; break; }
-            const int u = find_col(cci, crp[J], crp[J + 1], I);
-            cv[t] = (u < crp[J + 1] && cci[u] == I) ? cconj(cv[u]) : make_double2(0.0, 0.0);
+        if (lane != 0 || b == e) return;  // a lower entry has no pairs
+        const int u = mir[t];
+        if (u == t) {
+            cv[t] = make_double2(acc.x, 0.0);
+        } else {
+            cv[t] = acc;
+            cv[u] = cconj(acc);
         }
     }
 };
@@ -1201,22 +1413,43 @@ static void check_err(const DevBuf<int> &err, hipStream_t s, const char *what)
     const int e = read_int(err.get(), s);
     if (e & 2 || e & 4) fail(GL_ERR_UNSUPPORTED, std::string(what) + ": a coarse row exceeds the setup row limit");
     if (e & 8) fail(GL_ERR_UNSUPPORTED, std::string(what) + ": more than 256 colours");
+    if (e & 16) fail(GL_ERR_HIP, std::string(what) + ": a coarse pattern is not symmetric");
     if (e) fail(GL_ERR_HIP, std::string(what) + ": aggregation left a node unassigned");
 }
 
 // CSR pattern (rp from counts, then columns) helper
-static void alloc_rowptr(Csr &M, const int *cnt, hipStream_t s)
+static void alloc_rowptr(Csr &M, const int *cnt, SymTmp &T, hipStream_t s)
 {
     M.rp.alloc((size_t)M.n + 1);
-    const int64_t nnz = scan_excl(cnt, M.rp.get(), M.n, s);
+    const int64_t nnz = scan_excl(cnt, M.rp.get(), M.n, T, s);
     if (nnz > INT32_MAX - 1) fail(GL_ERR_UNSUPPORTED, "sparse matrix too large");
     M.nnz = (int)nnz;
-    GLK_HIP(hipMemcpyAsync(M.rp.get() + M.n, &M.nnz, sizeof(int), hipMemcpyHostToDevice, s));
-    GLK_HIP(hipStreamSynchronize(s));
     M.ci.alloc((size_t)std::max(1, M.nnz));
 }
 
-static void colour_level(gl_precond *pre, int l, hipStream_t s)
+// Launches rounds of a wave-like decision until none of its nodes is
+// undecided: round(flag) enqueues one round, which sets *flag when nodes are
+// left.  The host looks after a batch of rounds only (rounds after the last
+// decision change nothing), and a batch grows with the rounds already run.
+template <class Round>
+static void run_rounds(int n, SymTmp &T, hipStream_t s, const char *what, Round &&round)
+{
+    constexpr int slots = 256;
+    int *flags = need(T.flags, slots), slot = 0;
+    int64_t done = 0;
+    for (;;) {
+        if (done > (int64_t)n + 8) fail(GL_ERR_HIP, std::string(what) + " did not terminate");
+        if (slot == 0) k_fill_int<<<1, slots, 0, s>>>(flags, slots, 0);
+        const int batch = 8 + (int)std::min<int64_t>(done / 4, 64);
+        for (int r = 0; r < batch; ++r) round(r + 1 == batch ? flags + slot : nullptr);
+        GLK_CHECK_LAUNCH();
+        done += batch;
+        if (read_int(flags + slot, s) == 0) return;
+        slot = (slot + 1) % slots;
+    }
+}
+
+static void colour_level(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
 {
     Level &L = pre->L[l];
     const int n = L.n, nb = blocks_for(n);
@@ -1228,30 +1461,22 @@ static void colour_level(gl_precond *pre, int l, hipStream_t s)
         GLK_CHECK_LAUNCH();
         L.ncolors = n > 1 ? 2 : 1;
     } else {
-        DevBuf<int> ready(n), cnt(1), err(1);
-        GLK_HIP(hipMemsetAsync(err.get(), 0, sizeof(int), s));
+        int *err = need(T.err, 1);
+        k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
         k_fill_int<<<nb, kBlock, 0, s>>>(L.color.get(), n, -1);
-        // index priorities colour in waves (many rounds): the host reads the
-        // uncoloured count every few rounds (later rounds change nothing)
-        for (int round = 0;; ++round) {
-            if (round > n + 8) fail(GL_ERR_HIP, "colouring did not terminate");
-            GLK_HIP(hipMemsetAsync(cnt.get(), 0, sizeof(int), s));
-            k_jp_ready<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.color.get(), ready.get());
-            k_jp_colour<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), ready.get(), L.color.get(),
-                                              cnt.get(), err.get());
-            GLK_CHECK_LAUNCH();
-            if ((round & 3) == 3 && read_int(cnt.get(), s) == 0) break;
-        }
-        check_err(err, s, "colouring");
+        run_rounds(n, T, s, "colouring", [&](int *flag) {
+            k_jp_round<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.color.get(), flag, err);
+        });
+        check_err(T.err, s, "colouring");
         // class sizes and the number of colours
-        DevBuf<int> hist(257);
+        int *hist = need(T.a, 257);
         std::vector<int> h;
         int nc = 0;
         auto count = [&] {
-            GLK_HIP(hipMemsetAsync(hist.get(), 0, 257 * sizeof(int), s));
-            k_colour_hist<<<nb, kBlock, 0, s>>>(n, L.color.get(), hist.get());
+            k_fill_int<<<2, kBlock, 0, s>>>(hist, 257, 0);
+            k_colour_hist<<<std::min(nb, 256), kBlock, 0, s>>>(n, L.color.get(), hist);
             GLK_CHECK_LAUNCH();
-            h = to_host(hist.get(), 257, s);
+            h = to_host(hist, 257, s);
             nc = 0;
             for (int c = 0; c < 257; ++c)
                 if (h[c]) nc = c + 1;
@@ -1259,134 +1484,125 @@ static void colour_level(gl_precond *pre, int l, hipStream_t s)
         count();
         // iterated greedy: never more colours, often fewer (each colour costs
         // two dependent passes per symmetric sweep)
-        DevBuf<int> nw(n);
+        int *nw = need(T.b, n);
         for (int pass = 0; pass < kRecolourPasses; ++pass) {
-            k_fill_int<<<nb, kBlock, 0, s>>>(nw.get(), n, -1);
+            k_fill_int<<<nb, kBlock, 0, s>>>(nw, n, -1);
             for (int c = nc - 1; c >= 0; --c)
-                k_ig_class<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.color.get(), c, nw.get(), err.get());
+                k_ig_class<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.color.get(), c, nw, err);
             GLK_CHECK_LAUNCH();
-            GLK_HIP(hipMemcpyAsync(L.color.get(), nw.get(), sizeof(int) * (size_t)n, hipMemcpyDeviceToDevice, s));
+            GLK_HIP(hipMemcpyAsync(L.color.get(), nw, sizeof(int) * (size_t)n, hipMemcpyDeviceToDevice, s));
             count();
         }
-        check_err(err, s, "recolouring");
+        check_err(T.err, s, "recolouring");
         L.ncolors = nc;
         // rows grouped by colour
         L.cperm.alloc(n);
         L.coff.assign(nc + 1, 0);
-        DevBuf<int> flag(n), pos(n);
-        for (int c = 0; c < nc; ++c) {
-            L.coff[c + 1] = L.coff[c] + h[c];
-            k_flag_eq<<<nb, kBlock, 0, s>>>(n, L.color.get(), c, flag.get());
-            scan_excl(flag.get(), pos.get(), n, s);
-            k_scatter_colour<<<nb, kBlock, 0, s>>>(n, L.color.get(), c, pos.get(), L.cperm.get() + L.coff[c]);
-            GLK_CHECK_LAUNCH();
-        }
+        for (int c = 0; c < nc; ++c) L.coff[c + 1] = L.coff[c] + h[c];
+        int *bc = need(T.b, (size_t)nc * nb), *off = need(T.c, (size_t)nc * nb + 1);
+        k_colour_count<<<nb, kBlock, 0, s>>>(n, L.color.get(), nb, nc, bc);
+        scan_excl(bc, off, nc * nb, T, s);
+        k_colour_place<<<nb, kBlock, 0, s>>>(n, L.color.get(), nb, off, L.cperm.get());
+        GLK_CHECK_LAUNCH();
     }
 }
 
 // aggregation of level l; returns the number of aggregates
-static int aggregate_level(gl_precond *pre, int l, hipStream_t s)
+static int aggregate_level(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
 {
     Level &L = pre->L[l];
     const int n = L.n, nb = blocks_for(n);
     const int *rp = L.A.rp.get(), *ci = L.A.ci.get();
-    DevBuf<int> state(n), near1(n), cnt(1), err(1), rootA(n), rootB(n), flag(n), id(n);
-    DevBuf<unsigned long long> m1(n);
-    k_fill_int<<<nb, kBlock, 0, s>>>(state.get(), n, 0);
-    GLK_HIP(hipMemsetAsync(err.get(), 0, sizeof(int), s));
-    // index priorities decide roots in waves across the grid (many rounds):
-    // the host reads the undecided count every few rounds (rounds after the
-    // last decision change nothing)
-    for (int round = 0;; ++round) {
-        if (round > n + 8) fail(GL_ERR_HIP, "aggregation did not terminate");
-        GLK_HIP(hipMemsetAsync(cnt.get(), 0, sizeof(int), s));
-        k_mis_m1<<<nb, kBlock, 0, s>>>(n, rp, ci, state.get(), m1.get());
-        k_mis_select<<<nb, kBlock, 0, s>>>(n, rp, ci, m1.get(), state.get());
-        k_mis_near<<<nb, kBlock, 0, s>>>(n, rp, ci, state.get(), near1.get());
-        k_mis_remove<<<nb, kBlock, 0, s>>>(n, rp, ci, near1.get(), state.get(), cnt.get());
-        GLK_CHECK_LAUNCH();
-        if ((round & 3) == 3 && read_int(cnt.get(), s) == 0) break;
-    }
-    k_agg_phase_a<<<nb, kBlock, 0, s>>>(n, rp, ci, state.get(), rootA.get());
-    k_agg_phase_b<<<nb, kBlock, 0, s>>>(n, rp, ci, rootA.get(), rootB.get(), err.get());
-    k_root_flags<<<nb, kBlock, 0, s>>>(n, state.get(), flag.get());
+    int *state = need(T.a, n), *rootA = need(T.b, n), *rootB = need(T.c, n), *flag = need(T.d, n);
+    int *id = need(T.e, (size_t)n + 1), *err = need(T.err, 1);
+    k_fill_int<<<nb, kBlock, 0, s>>>(state, n, 0);
+    k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
+    run_rounds(n, T, s, "aggregation",
+               [&](int *left) { k_mis_round<<<nb, kBlock, 0, s>>>(n, rp, ci, state, left); });
+    k_agg_phase_a<<<nb, kBlock, 0, s>>>(n, rp, ci, state, rootA);
+    k_agg_phase_b<<<nb, kBlock, 0, s>>>(n, rp, ci, rootA, rootB, err);
+    k_root_flags<<<nb, kBlock, 0, s>>>(n, state, flag);
     GLK_CHECK_LAUNCH();
-    check_err(err, s, "aggregation");
-    const int nc = (int)scan_excl(flag.get(), id.get(), n, s);
+    check_err(T.err, s, "aggregation");
+    const int nc = (int)scan_excl(flag, id, n, T, s);
     L.nc = nc;
     L.agg.alloc(n);
     L.root.alloc(std::max(1, nc));
     L.aggsize.alloc(std::max(1, nc));
-    GLK_HIP(hipMemsetAsync(L.aggsize.get(), 0, sizeof(int) * std::max(1, nc), s));
-    k_agg_number<<<nb, kBlock, 0, s>>>(n, rootB.get(), id.get(), state.get(), L.agg.get(), L.root.get(),
-                                       L.aggsize.get());
+    k_fill_int<<<blocks_for(std::max(1, nc)), kBlock, 0, s>>>(L.aggsize.get(), std::max(1, nc), 0);
+    k_agg_number<<<nb, kBlock, 0, s>>>(n, rootB, id, state, L.agg.get(), L.root.get(), L.aggsize.get());
     GLK_CHECK_LAUNCH();
     return nc;
 }
 
-static void transfer_patterns(gl_precond *pre, int l, hipStream_t s)
+static void transfer_patterns(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
 {
     Level &L = pre->L[l];
     Level &Nx = pre->L[l + 1];
-    const int n = L.n, nc = L.nc, nb = blocks_for(n), nbc = blocks_for(nc);
-    DevBuf<int> cnt(std::max(n, nc)), err(1);
-    GLK_HIP(hipMemsetAsync(err.get(), 0, sizeof(int), s));
+    const int n = L.n, nc = L.nc, nb = blocks_for(n);
+    const int nbw = (nc + kRowWaves - 1) / kRowWaves;  // a wave per coarse row
+    int *cnt = need(T.a, std::max(n, nc)), *err = need(T.err, 1);
+    k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
     // P: n x nc
     L.P.n = n;
     L.P.m = nc;
-    k_p_pattern<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.agg.get(), nullptr, cnt.get(),
-                                      nullptr, err.get());
+    k_p_pattern<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.agg.get(), nullptr, cnt, nullptr, err);
     GLK_CHECK_LAUNCH();
-    check_err(err, s, "prolongator pattern");
-    alloc_rowptr(L.P, cnt.get(), s);
-    k_p_pattern<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.agg.get(), L.P.rp.get(), nullptr,
-                                      L.P.ci.get(), err.get());
+    check_err(T.err, s, "prolongator pattern");
+    alloc_rowptr(L.P, cnt, T, s);
+    k_p_pattern<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.agg.get(), L.P.rp.get(), nullptr, L.P.ci.get(),
+                                      err);
     // R = P^H: nc x n
     L.R.n = nc;
     L.R.m = n;
-    GLK_HIP(hipMemsetAsync(cnt.get(), 0, sizeof(int) * nc, s));
-    k_col_count<<<blocks_for(L.P.nnz), kBlock, 0, s>>>(L.P.nnz, L.P.ci.get(), cnt.get());
+    k_fill_int<<<blocks_for(nc), kBlock, 0, s>>>(cnt, nc, 0);
+    k_col_count<<<blocks_for(L.P.nnz), kBlock, 0, s>>>(L.P.nnz, L.P.ci.get(), cnt);
     GLK_CHECK_LAUNCH();
-    alloc_rowptr(L.R, cnt.get(), s);
+    alloc_rowptr(L.R, cnt, T, s);
     L.rsrc.alloc(std::max(1, L.R.nnz));
-    DevBuf<int> fill(nc);
-    GLK_HIP(hipMemsetAsync(fill.get(), 0, sizeof(int) * nc, s));
-    k_transpose_fill<<<nb, kBlock, 0, s>>>(n, L.P.rp.get(), L.P.ci.get(), L.R.rp.get(), fill.get(),
-                                           L.R.ci.get(), L.rsrc.get());
-    k_sort_rows<<<nbc, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.rsrc.get());
+    int *fill = need(T.b, nc), *tci = need(T.c, std::max(1, L.R.nnz)), *tsrc = need(T.d, std::max(1, L.R.nnz));
+    k_fill_int<<<blocks_for(nc), kBlock, 0, s>>>(fill, nc, 0);
+    k_transpose_fill<<<nb, kBlock, 0, s>>>(n, L.P.rp.get(), L.P.ci.get(), L.R.rp.get(), fill, tci, tsrc);
+    k_sort_rows<<<nbw, kBlock, 0, s>>>(nc, L.R.rp.get(), tci, tsrc, L.R.ci.get(), L.rsrc.get());
     GLK_CHECK_LAUNCH();
+    // A P pattern
+    L.AP.n = n;
+    L.AP.m = nc;
+    k_ap_pattern<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.P.rp.get(), L.P.ci.get(), nullptr, cnt, nullptr,
+                                       err);
+    GLK_CHECK_LAUNCH();
+    check_err(T.err, s, "Galerkin pattern");
+    alloc_rowptr(L.AP, cnt, T, s);
+    k_ap_pattern<<<nb, kBlock, 0, s>>>(n, L.A.rp.get(), L.A.ci.get(), L.P.rp.get(), L.P.ci.get(), L.AP.rp.get(), nullptr,
+                                       L.AP.ci.get(), err);
     // A_{l+1} = R A P pattern
     Nx.n = nc;
     Nx.A.n = nc;
     Nx.A.m = nc;
-    k_rap_pattern<<<nbc, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.A.rp.get(), L.A.ci.get(),
-                                         L.P.rp.get(), L.P.ci.get(), nullptr, cnt.get(), nullptr, err.get());
+    k_rap_pattern<<<nbw, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.AP.rp.get(), L.AP.ci.get(), nullptr, cnt,
+                                         nullptr, err);
     GLK_CHECK_LAUNCH();
-    check_err(err, s, "Galerkin pattern");
-    alloc_rowptr(Nx.A, cnt.get(), s);
-    k_rap_pattern<<<nbc, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.A.rp.get(), L.A.ci.get(),
-                                         L.P.rp.get(), L.P.ci.get(), Nx.A.rp.get(), nullptr, Nx.A.ci.get(),
-                                         err.get());
+    check_err(T.err, s, "Galerkin pattern");
+    alloc_rowptr(Nx.A, cnt, T, s);
+    k_rap_pattern<<<nbw, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.AP.rp.get(), L.AP.ci.get(), Nx.A.rp.get(),
+                                         nullptr, Nx.A.ci.get(), err);
     GLK_CHECK_LAUNCH();
-    // product lists of the upper triangle for the numeric Galerkin product
+    // the pairs of the upper triangle for the numeric Galerkin product
     const int nnzc = Nx.A.nnz;
-    DevBuf<int> pc(std::max(1, nnzc));
-    GLK_HIP(hipMemsetAsync(pc.get(), 0, sizeof(int) * std::max(1, nnzc), s));
-    k_rap_count<<<nbc, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.A.rp.get(), L.A.ci.get(), L.P.rp.get(),
-                                       L.P.ci.get(), Nx.A.rp.get(), Nx.A.ci.get(), pc.get());
+    int *pc = need(T.b, std::max(1, nnzc));
+    k_rap_pairs<<<nbw, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.AP.rp.get(), L.AP.ci.get(), Nx.A.rp.get(),
+                                       Nx.A.ci.get(), pc, nullptr, nullptr);
     GLK_CHECK_LAUNCH();
     L.rap_tp.alloc((size_t)nnzc + 1);
-    const int64_t ntrip = scan_excl(pc.get(), L.rap_tp.get(), nnzc, s);
-    if (ntrip > (int64_t)1 << 30) fail(GL_ERR_UNSUPPORTED, "Galerkin product: too many products");
-    const int total = (int)ntrip;
-    GLK_HIP(hipMemcpyAsync(L.rap_tp.get() + nnzc, &total, sizeof(int), hipMemcpyHostToDevice, s));
-    L.rap_trip.alloc((size_t)3 * std::max<int64_t>(1, ntrip));
-    GLK_HIP(hipMemsetAsync(pc.get(), 0, sizeof(int) * std::max(1, nnzc), s));
-    k_rap_fill<<<nbc, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.A.rp.get(), L.A.ci.get(), L.P.rp.get(),
-                                      L.P.ci.get(), Nx.A.rp.get(), Nx.A.ci.get(), L.rap_tp.get(), pc.get(),
-                                      L.rap_trip.get());
+    const int64_t npair = scan_excl(pc, L.rap_tp.get(), nnzc, T, s);
+    if (npair < 0 || npair > (int64_t)1 << 30) fail(GL_ERR_UNSUPPORTED, "Galerkin product: too many products");
+    L.rap_pair.alloc((size_t)std::max<int64_t>(1, npair));
+    L.rap_mir.alloc(std::max(1, nnzc));
+    k_rap_pairs<<<nbw, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.AP.rp.get(), L.AP.ci.get(), Nx.A.rp.get(),
+                                       Nx.A.ci.get(), nullptr, L.rap_tp.get(), L.rap_pair.get());
+    k_rap_mirror<<<blocks_for((int64_t)nc * 8), kBlock, 0, s>>>(nc, Nx.A.rp.get(), Nx.A.ci.get(), L.rap_mir.get(), err);
     GLK_CHECK_LAUNCH();
-    GLK_HIP(hipStreamSynchronize(s));
+    check_err(T.err, s, "Galerkin product");
 }
 
 static void alloc_values(gl_precond *pre)
@@ -1413,6 +1629,7 @@ static void alloc_values(gl_precond *pre)
         if (l < pre->nlev - 1) {
             L.P.v64.alloc(std::max(1, L.P.nnz));
             L.P.v32.alloc(std::max(1, L.P.nnz));
+            L.AP.v64.alloc(std::max(1, L.AP.nnz));
             L.R.v64.alloc(std::max(1, L.R.nnz));
             L.R.v32.alloc(std::max(1, L.R.nnz));
             L.rho.alloc(1);
@@ -1432,14 +1649,14 @@ static void alloc_values(gl_precond *pre)
 
 // copy of M with rows taken in the order rowperm and columns relabelled by colmap
 static void permuted_copy(const Csr &M, const int *rowperm, const int *colmap, Csr &out, DevBuf<int> &map,
-                          hipStream_t s)
+                          SymTmp &T, hipStream_t s)
 {
     out.n = M.n;
     out.m = M.m;
-    DevBuf<int> cnt(std::max(1, M.n));
-    k_perm_count<<<blocks_for(M.n), kBlock, 0, s>>>(M.n, rowperm, M.rp.get(), cnt.get());
+    int *cnt = need(T.a, std::max(1, M.n));
+    k_perm_count<<<blocks_for(M.n), kBlock, 0, s>>>(M.n, rowperm, M.rp.get(), cnt);
     GLK_CHECK_LAUNCH();
-    alloc_rowptr(out, cnt.get(), s);
+    alloc_rowptr(out, cnt, T, s);
     map.alloc(std::max(1, out.nnz));
     k_perm_fill<<<blocks_for(M.n), kBlock, 0, s>>>(M.n, rowperm, M.rp.get(), M.ci.get(), colmap, out.rp.get(),
                                                    out.ci.get(), map.get());
@@ -1449,7 +1666,7 @@ static void permuted_copy(const Csr &M, const int *rowperm, const int *colmap, C
 }
 
 // the colour-ordered copies the V-cycle works on
-static void build_apply_copies(gl_precond *pre, hipStream_t s)
+static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
 {
     // level 0 of a simplicial mesh is a CSR level like the coarse ones (when
     // it is not the coarsest, which is applied as a dense inverse in node order)
@@ -1470,20 +1687,20 @@ static void build_apply_copies(gl_precond *pre, hipStream_t s)
         const bool generic = l >= lfirst;
         const int *rowp = generic ? L.perm.get() : nullptr;
         const int *colp = generic ? L.iperm.get() : nullptr;
-        if (generic) permuted_copy(L.A, rowp, colp, L.Aa, L.amap, s);
+        if (generic) permuted_copy(L.A, rowp, colp, L.Aa, L.amap, T, s);
         if (l + 1 < pre->nlev) {
             Level &Nx = pre->L[l + 1];
-            permuted_copy(L.P, rowp, Nx.iperm.get(), L.Pa, L.pmap, s);
-            permuted_copy(L.R, Nx.perm.get(), colp, L.Ra, L.rmap, s);
+            permuted_copy(L.P, rowp, Nx.iperm.get(), L.Pa, L.pmap, T, s);
+            permuted_copy(L.R, Nx.perm.get(), colp, L.Ra, L.rmap, T, s);
             if (l == 0 && !generic) {
                 const GeomT<double> g = geom_t<double>(pre->mesh->g);
                 Csr &B = L.Rb;
                 B.n = L.Ra.n;
                 B.m = 2 * g.npair;
-                DevBuf<int> cnt(std::max(1, B.n));
-                k_black_count<<<blocks_for(B.n), kBlock, 0, s>>>(B.n, g, L.Ra.rp.get(), L.Ra.ci.get(), cnt.get());
+                int *cnt = need(T.a, std::max(1, B.n));
+                k_black_count<<<blocks_for(B.n), kBlock, 0, s>>>(B.n, g, L.Ra.rp.get(), L.Ra.ci.get(), cnt);
                 GLK_CHECK_LAUNCH();
-                alloc_rowptr(B, cnt.get(), s);
+                alloc_rowptr(B, cnt, T, s);
                 L.bmap.alloc(std::max(1, B.nnz));
                 k_black_fill<<<blocks_for(B.n), kBlock, 0, s>>>(B.n, g, L.Ra.rp.get(), L.Ra.ci.get(), L.rmap.get(),
                                                                 B.rp.get(), B.ci.get(), L.bmap.get());
@@ -1493,10 +1710,10 @@ static void build_apply_copies(gl_precond *pre, hipStream_t s)
                 Csr &Q = L.Pb;
                 Q.n = g.npair;
                 Q.m = L.Pa.m;
-                DevBuf<int> qcnt(std::max(1, Q.n));
-                k_pblack_count<<<blocks_for(Q.n), kBlock, 0, s>>>(g, L.Pa.rp.get(), qcnt.get());
+                int *qcnt = need(T.a, std::max(1, Q.n));
+                k_pblack_count<<<blocks_for(Q.n), kBlock, 0, s>>>(g, L.Pa.rp.get(), qcnt);
                 GLK_CHECK_LAUNCH();
-                alloc_rowptr(Q, qcnt.get(), s);
+                alloc_rowptr(Q, qcnt, T, s);
                 L.pbmap.alloc(std::max(1, Q.nnz));
                 k_pblack_fill<<<blocks_for(Q.n), kBlock, 0, s>>>(g, L.Pa.rp.get(), L.Pa.ci.get(), L.pmap.get(),
                                                                  Q.rp.get(), Q.ci.get(), L.pbmap.get());
@@ -1507,15 +1724,13 @@ static void build_apply_copies(gl_precond *pre, hipStream_t s)
         }
         if (generic) {
             // padded colour blocks for the Gauss-Seidel sweeps
-            std::vector<int> rp = to_host(L.Aa.rp.get(), (size_t)L.n + 1, s);
-            L.ewidth.assign(L.ncolors, 0);
+            int *row0 = need(T.a, (size_t)L.ncolors + 1), *wid = need(T.b, L.ncolors);
+            to_device(row0, L.coff, s);
+            k_row_widths<<<L.ncolors, kBlock, 0, s>>>(L.Aa.rp.get(), row0, wid);
+            GLK_CHECK_LAUNCH();
+            L.ewidth = to_host(wid, L.ncolors, s);
             L.eoff.assign(L.ncolors + 1, 0);
-            for (int c = 0; c < L.ncolors; ++c) {
-                int w = 1;
-                for (int r = L.coff[c]; r < L.coff[c + 1]; ++r) w = std::max(w, rp[r + 1] - rp[r]);
-                L.ewidth[c] = w;
-                L.eoff[c + 1] = L.eoff[c] + w * (L.coff[c + 1] - L.coff[c]);
-            }
+            for (int c = 0; c < L.ncolors; ++c) L.eoff[c + 1] = L.eoff[c] + L.ewidth[c] * (L.coff[c + 1] - L.coff[c]);
             const int ne = std::max(1, L.eoff[L.ncolors]);
             L.eci.alloc(ne);
             L.emap.alloc(ne);
@@ -1541,13 +1756,14 @@ void precond_symbolic(gl_precond *pre, hipStream_t s)
     Level &L0 = pre->L[0];
     L0.n = n0;
     L0.A.n = L0.A.m = n0;
+    SymTmp T;
     {
-        DevBuf<int> cnt(n0);
-        if (m->g.simplicial) k_l0s_count<<<nb0, kBlock, 0, s>>>(n0, m->g.rp, cnt.get());
-        else if (m->g.dim == 2) k_l0_count<2><<<nb0, kBlock, 0, s>>>(m->g, cnt.get());
-        else k_l0_count<3><<<nb0, kBlock, 0, s>>>(m->g, cnt.get());
+        int *cnt = need(T.a, n0);
+        if (m->g.simplicial) k_l0s_count<<<nb0, kBlock, 0, s>>>(n0, m->g.rp, cnt);
+        else if (m->g.dim == 2) k_l0_count<2><<<nb0, kBlock, 0, s>>>(m->g, cnt);
+        else k_l0_count<3><<<nb0, kBlock, 0, s>>>(m->g, cnt);
         GLK_CHECK_LAUNCH();
-        alloc_rowptr(L0.A, cnt.get(), s);
+        alloc_rowptr(L0.A, cnt, T, s);
         if (m->g.simplicial)
             k_l0s_cols<<<nb0, kBlock, 0, s>>>(n0, m->g.rp, m->g.ci, L0.A.rp.get(), L0.A.ci.get());
         else if (m->g.dim == 2) k_l0_cols<2><<<nb0, kBlock, 0, s>>>(m->g, L0.A.rp.get(), L0.A.ci.get());
@@ -1557,10 +1773,10 @@ void precond_symbolic(gl_precond *pre, hipStream_t s)
     const int max_levels = std::min(pre->opts.max_levels, kMaxLevels);
     int l = 0;
     for (;;) {
-        colour_level(pre, l, s);
+        colour_level(pre, l, T, s);
         Level &L = pre->L[l];
         if (L.n <= pre->opts.max_coarse || l == max_levels - 1) break;
-        const int nc = aggregate_level(pre, l, s);
+        const int nc = aggregate_level(pre, l, T, s);
         if ((double)nc > 0.85 * (double)L.n) {
             L.agg.release();
             L.root.release();
@@ -1568,14 +1784,14 @@ void precond_symbolic(gl_precond *pre, hipStream_t s)
             L.nc = 0;
             break;
         }
-        transfer_patterns(pre, l, s);
+        transfer_patterns(pre, l, T, s);
         ++l;
     }
     pre->nlev = l + 1;
     if (pre->L[l].n > kMaxDense)
         fail(GL_ERR_UNSUPPORTED, "coarsest level too large for the dense solve");
     alloc_values(pre);
-    build_apply_copies(pre, s);
+    build_apply_copies(pre, T, s);
     bottom_descriptors(pre, s);
     GLK_HIP(hipStreamSynchronize(s));
 }
@@ -1602,10 +1818,19 @@ void precond_numeric_enqueue(gl_precond *pre, const double2 *psi, const Launch &
         L.run(nb, PValues{n, lv.A.rp.get(), lv.A.ci.get(), lv.A.v64.get(), lv.diag64.get(), lv.agg.get(),
                           lv.aggsize.get(), lv.rho.get(), lv.P.rp.get(), lv.P.ci.get(), lv.P.v64.get()});
         L.run(blocks_for(lv.R.nnz), RValues{lv.R.nnz, lv.rsrc.get(), lv.P.v64.get(), lv.R.v64.get()});
+        // A P: about a lane per entry of a row
+        auto ap = [&](auto lanes) {
+            constexpr int LPR = decltype(lanes)::value;
+            L.run(blocks_for((int64_t)n * LPR),
+                  ApValues<LPR>{n, lv.A.rp.get(), lv.A.ci.get(), lv.A.v64.get(), lv.P.rp.get(), lv.P.ci.get(),
+                                lv.P.v64.get(), lv.AP.rp.get(), lv.AP.ci.get(), lv.AP.v64.get()});
+        };
+        if (lv.AP.nnz <= 5 * (int64_t)n) ap(std::integral_constant<int, 4>{});
+        else if (lv.AP.nnz <= 12 * (int64_t)n) ap(std::integral_constant<int, 8>{});
+        else ap(std::integral_constant<int, 16>{});
         L.run(blocks_for((int64_t)Nx.A.nnz * kRapLanes),
-              RapValues{Nx.A.nnz, lv.rap_tp.get(), lv.rap_trip.get(), lv.R.v64.get(), lv.A.v64.get(), lv.P.v64.get(),
+              RapValues{Nx.A.nnz, lv.rap_tp.get(), lv.rap_pair.get(), lv.rap_mir.get(), lv.R.v64.get(), lv.AP.v64.get(),
                         Nx.A.v64.get()});
-        L.run(blocks_for(lv.nc), RapMirror{lv.nc, Nx.A.rp.get(), Nx.A.ci.get(), Nx.A.v64.get()});
     }
     const int last = pre->nlev - 1;
     Level &Lc = pre->L[last];
