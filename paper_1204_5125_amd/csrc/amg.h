@@ -27,6 +27,32 @@ struct Csr {
     DevBuf<float2> v32;
 };
 
+// A level's rows cut into compact patches, so that one work-group can run a
+// whole symmetric Gauss-Seidel sweep on its patch (vcycle.hip).  Slots 0 ..
+// rows - 1 of a patch are the rows it updates (the patch itself and the rows
+// whose values the later passes need), in ascending row order, which is colour
+// order; the slots after them hold rows whose starting value is read only.
+constexpr int kPatchRows = 512;    // rows of a patch, a thread each
+constexpr int kPatchSlots = 1024;  // with the read-only ones
+constexpr int kPatchWidth = 16;    // off-diagonal entries of a row at most
+
+struct PatchSet {
+    int np = 0;                 // patches (0: the level runs a dispatch per colour pass)
+    int W = 0;                  // entries held per row: 8, 12 or 16
+    DevBuf<int> size;           // per patch: rows, slots
+    DevBuf<int> rowid;          // [np][kPatchSlots] row of a slot
+    DevBuf<int> info;           // [np][kPatchRows] colour (255: no row) | last pass + 1 << 8 | own << 16 | entries << 20
+    DevBuf<unsigned short> idx; // [np][W][kPatchRows] slot of entry k (kPatchSlots: none)
+    DevBuf<int> map;            // its entry of Aa, -1: none
+    DevBuf<double2> v64;        // its value
+    DevBuf<float2> v32;
+    // the prolongation to the level, rows padded to PW entries (0 of column 0)
+    int PW = 0;
+    DevBuf<int> pci, pmap;      // [n][PW]; pmap: the entry of Pa, -1: none
+    DevBuf<double2> pv64;
+    DevBuf<float2> pv32;
+};
+
 struct Level {
     int n = 0;
     Csr A;
@@ -67,6 +93,8 @@ struct Level {
     DevBuf<int> eci, emap;          // emap: entry of Aa, or -1 for padding
     DevBuf<double2> ev64;
     DevBuf<float2> ev32;
+    PatchSet patch;
+    DevBuf<int> origin;         // level-0 node of each row's root (old order)
     // V-cycle vectors (new order on levels >= 1; level 0: split by colour, the
     // node of colour c in red-black pair t at c * npair + t, 2 npair entries)
     DevBuf<double2> b64, x64, r64;
@@ -284,6 +312,7 @@ void gl_residual_enqueue(const gl_mesh *m, const double2 *psi, double2 *out, dou
 void jacobian_enqueue(const gl_mesh *m, const double2 *psi, const double2 *phi, double2 *out,
                       hipStream_t s);
 void precond_numeric(gl_precond *pre, const double2 *psi, hipStream_t s);
+void patch_values_enqueue(gl_precond *pre, const Launch &L);  // of the levels that run in patches
 // A numeric setup in two halves, so that many instances can be recorded and
 // run as batched dispatches: every kernel (launched or recorded; the coarsest
 // factor's failure flag is left in pre->status), then, with that flag read,

@@ -1366,6 +1366,18 @@ __global__ void k_ell_fill(int row0, int count, int W, const int *rp, const int 
     }
 }
 
+// the rows of the prolongation padded to W entries: (column 0, no entry)
+__global__ void k_pell_fill(int n, int W, const int *rp, const int *ci, int *pci, int *pmap)
+{
+    const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r >= n) return;
+    const int b = rp[r], len = rp[r + 1] - rp[r];
+    for (int k = 0; k < W; ++k) {
+        pci[(size_t)r * W + k] = k < len ? ci[b + k] : 0;
+        pmap[(size_t)r * W + k] = k < len ? b + k : -1;
+    }
+}
+
 struct EllValues {
     int n;
     const int *emap;
@@ -1382,6 +1394,166 @@ struct EllValues {
         d32[q] = make_float2((float)v.x, (float)v.y);
     }
 };
+
+// ----------------------------------------------------------- patches --
+// The level-0 node of every aggregate's root, through the levels' roots.
+__global__ void k_origin(int nc, const int *root, const int *origin, int *out)
+{
+    const int a = blockIdx.x * kBlock + threadIdx.x;
+    if (a < nc) out[a] = origin ? origin[root[a]] : root[a];
+}
+
+// Tile of each row (new order): the place of its level-0 node in a kx x ky
+// grid of tiles over the domain.
+struct TileGrid {
+    int simplicial;
+    int N0, N1;            // grid
+    const double *x;       // simplicial: node coordinates (3 per node)
+    double lo[2], inv[2];  // simplicial: lower corner, 1 / extent
+    int k[2];
+};
+
+__global__ void k_tile_of(int n, const int *perm, const int *origin, TileGrid t, int *tile)
+{
+    const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r >= n) return;
+    const int o = perm[r], i = origin ? origin[o] : o;
+    int c[2];
+    if (t.simplicial) {
+        for (int a = 0; a < 2; ++a)
+            c[a] = min(t.k[a] - 1, max(0, (int)((t.x[3 * (size_t)i + a] - t.lo[a]) * t.inv[a] * t.k[a])));
+    } else {
+        c[0] = (int)((int64_t)(i % t.N0) * t.k[0] / t.N0);
+        c[1] = (int)((int64_t)(i / t.N0 % t.N1) * t.k[1] / t.N1);
+    }
+    tile[r] = c[1] * t.k[0] + c[0];
+}
+
+__global__ void k_tile_fill(int n, const int *tile, const int *rp, int *fill, int *rows)
+{
+    const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r >= n) return;
+    const int t = tile[r];
+    rows[rp[t] + atomicAdd(&fill[t], 1)] = r;
+}
+
+// Patch blockIdx.x from its own rows own[beg .. end): going back from the end
+// of the sweep, pass t needs every value its rows read, so a row joins the
+// patch when the first of its neighbours' passes after which it is needed is
+// met, and is then updated in every earlier pass of its colour.  (Rows of one
+// colour are not adjacent, so a pass widens the patch only around its own
+// colour: a symmetric sweep of 5-8 colours on the 2D hierarchies reaches three
+// or four rows out, not one per pass.)  The residual and the own rows' last
+// pass need the neighbours' final values.  Overflow: err 32.
+__global__ __launch_bounds__(kPatchRows) void k_patch_build(const int *__restrict__ tile_rp,
+                                                            const int *__restrict__ tile_rows,
+                                                            const int *__restrict__ rp, const int *__restrict__ ci,
+                                                            const int *__restrict__ perm, const int *__restrict__ color,
+                                                            int ncol, int W, int *size, int *rowid, int *info,
+                                                            unsigned short *idx, int *map, int *total, int *err)
+{
+    constexpr int H = 2 * kPatchSlots;
+    __shared__ int key[H], val[H], row[kPatchSlots], last[kPatchSlots], place[kPatchSlots];
+    __shared__ unsigned char col[kPatchSlots], done[kPatchSlots];
+    __shared__ int cnt, nrows, bad;
+    const int p = blockIdx.x, tid = threadIdx.x;
+    const int beg = tile_rp[p], end = tile_rp[p + 1];
+    for (int t = tid; t < H; t += kPatchRows) key[t] = -1;
+    for (int t = tid; t < kPatchSlots; t += kPatchRows) {
+        done[t] = 0;
+        rowid[(size_t)p * kPatchSlots + t] = 0;  // slots without a row read row 0 and write nothing
+    }
+    info[(size_t)p * kPatchRows + tid] = 255;
+    if (tid == 0) cnt = nrows = bad = 0;
+    __syncthreads();
+    auto insert = [&](int g, int e) {
+        unsigned h = ((unsigned)g * 2654435761u) % H;
+        for (int tries = 0; tries < H; ++tries, h = (h + 1) % H) {
+            const int old = atomicCAS(&key[h], -1, g);
+            if (old == g) return;
+            if (old != -1) continue;
+            const int slot = atomicAdd(&cnt, 1);
+            if (slot >= kPatchSlots) {
+                bad = 1;
+                return;
+            }
+            val[h] = slot;
+            row[slot] = g;
+            last[slot] = e;
+            col[slot] = (unsigned char)color[perm[g]];
+            return;
+        }
+        bad = 1;
+    };
+    const int T = 2 * ncol - 1;
+    for (int q = beg + tid; q < end; q += kPatchRows) insert(tile_rows[q], T);
+    __syncthreads();
+    for (int q = beg + tid; q < end; q += kPatchRows) {
+        const int g = tile_rows[q];
+        for (int k = rp[g]; k < rp[g + 1]; ++k) insert(ci[k], T);
+    }
+    __syncthreads();
+    for (int t = T - 1; t >= 0; --t) {
+        const int c = t < ncol ? t : 2 * ncol - 2 - t;
+        const int n0 = min(cnt, kPatchSlots), over = bad;
+        __syncthreads();
+        if (over) break;
+        for (int s = tid; s < n0; s += kPatchRows)
+            if (col[s] == c && last[s] > t && !done[s]) {
+                done[s] = 1;
+                const int g = row[s];
+                for (int k = rp[g]; k < rp[g + 1]; ++k) insert(ci[k], t);
+            }
+        __syncthreads();
+    }
+    __syncthreads();
+    const int n = min(cnt, kPatchSlots);
+    if (!bad)
+        for (int s = tid; s < n; s += kPatchRows)
+            if (done[s]) atomicAdd(&nrows, 1);
+    __syncthreads();
+    const int nr = nrows;
+    if (bad || nr > kPatchRows) {
+        if (tid == 0) atomicOr(err, 32);
+        return;
+    }
+    // the places: updated rows first, then the others, each in row order
+    for (int s = tid; s < n; s += kPatchRows) {
+        int rank = done[s] ? 0 : nr;
+        for (int q = 0; q < n; ++q) rank += done[q] == done[s] && row[q] < row[s];
+        place[s] = rank;
+        rowid[(size_t)p * kPatchSlots + rank] = row[s];
+    }
+    if (tid == 0) {
+        size[2 * p] = nr;
+        size[2 * p + 1] = n;
+        atomicAdd(total, nr);
+    }
+    __syncthreads();
+    const size_t base = (size_t)p * W * kPatchRows;
+    for (int t = tid; t < W * kPatchRows; t += kPatchRows) {
+        idx[base + t] = kPatchSlots;
+        map[base + t] = -1;
+    }
+    __syncthreads();
+    for (int s = tid; s < n; s += kPatchRows) {
+        if (!done[s]) continue;
+        const int g = row[s], r = place[s];
+        int own = 0;
+        for (int q = beg; q < end; ++q) own |= tile_rows[q] == g;
+        int k = 0;
+        for (int q = rp[g]; q < rp[g + 1]; ++q) {
+            const int j = ci[q];
+            if (j == g) continue;
+            unsigned h = ((unsigned)j * 2654435761u) % H;
+            for (int tries = 0; tries < H && key[h] != j; ++tries) h = (h + 1) % H;
+            idx[base + (size_t)k * kPatchRows + r] = (unsigned short)place[val[h]];
+            map[base + (size_t)k * kPatchRows + r] = q;
+            ++k;
+        }
+        info[(size_t)p * kPatchRows + r] = col[s] | last[s] << 8 | own << 16 | k << 20;
+    }
+}
 
 struct GatherR {
     int n;
@@ -1665,6 +1837,8 @@ static void permuted_copy(const Csr &M, const int *rowperm, const int *colmap, C
     out.v32.alloc(std::max(1, out.nnz));
 }
 
+static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s);
+
 // the colour-ordered copies the V-cycle works on
 static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
 {
@@ -1672,6 +1846,13 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
     // it is not the coarsest, which is applied as a dense inverse in node order)
     const bool simp = pre->mesh->g.simplicial && pre->nlev > 1;
     const int lfirst = simp ? 0 : 1;
+    for (int l = 1; l < pre->nlev; ++l) {
+        Level &L = pre->L[l];
+        L.origin.alloc(L.n);
+        k_origin<<<blocks_for(L.n), kBlock, 0, s>>>(L.n, pre->L[l - 1].root.get(), pre->L[l - 1].origin.get(),
+                                                    L.origin.get());
+        GLK_CHECK_LAUNCH();
+    }
     for (int l = lfirst; l < pre->nlev; ++l) {
         Level &L = pre->L[l];
         L.perm.alloc(L.n);
@@ -1744,9 +1925,97 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
                                                              L.emap.get() + L.eoff[c]);
                 GLK_CHECK_LAUNCH();
             }
+            if (l + 1 < pre->nlev) build_patches(pre, l, T, s);
         }
     }
     GLK_HIP(hipStreamSynchronize(s));
+}
+
+// Patches of level l (its colour-ordered copy Aa exists): tiles of about
+// `own` rows by the rows' places in the plane.  A level keeps its dispatch per
+// colour pass where patches do not pay or do not fit: rows of more than
+// kPatchWidth neighbours (the 3D hierarchies: 30 entries and 15-30 colours reach
+// over the whole level), a patch of more than kPatchRows rows, or more than
+// kPatchMost updated rows per row of the level.  (Measured on the 2D levels:
+// 3-5 with 96 rows of a patch's own.)
+constexpr double kPatchMost = 8.0;
+constexpr int kPatchLevel = 1 << 20;  // rows of a level in patches at most
+
+static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
+{
+    Level &L = pre->L[l];
+    const gl_mesh *m = pre->mesh;
+    const int n = L.n, nb = blocks_for(n);
+    int wmax = 0;
+    for (int w : L.ewidth) wmax = std::max(wmax, w - 1);
+    if (n > kPatchLevel || m->g.dim != 2 || wmax > kPatchWidth || L.ncolors < 2 || L.ncolors > kMaxColors) return;
+    PatchSet &S = L.patch;
+    S.W = wmax <= 8 ? 8 : wmax <= 12 ? 12 : 16;
+    TileGrid t{};
+    t.simplicial = m->g.simplicial;
+    double ext[2];
+    if (t.simplicial) {
+        t.x = m->s_x.get();
+        for (int a = 0; a < 2; ++a) {
+            t.lo[a] = m->s_lo[a];
+            ext[a] = m->s_hi[a] - m->s_lo[a];
+            t.inv[a] = ext[a] > 0.0 ? 1.0 / ext[a] : 0.0;
+        }
+    } else {
+        t.N0 = m->g.N[0];
+        t.N1 = m->g.N[1];
+        ext[0] = t.N0;
+        ext[1] = t.N1;
+    }
+    for (int own : {96, 64, 40}) {
+        const double tiles = std::max(1.0, (double)n / own);
+        t.k[0] = (int)std::max(1.0, std::min(tiles, std::round(std::sqrt(tiles * ext[0] / std::max(ext[1], 1e-300)))));
+        t.k[1] = std::max(1, (int)std::round(tiles / t.k[0]));
+        const int nt = t.k[0] * t.k[1];
+        int *tile = need(T.a, n), *cnt = need(T.b, nt), *trp = need(T.c, (size_t)nt + 1);
+        int *rows = need(T.d, n), *srt = need(T.e, 2 * (size_t)n), *err = need(T.err, 1);
+        k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
+        k_fill_int<<<blocks_for(nt), kBlock, 0, s>>>(cnt, nt, 0);
+        k_tile_of<<<nb, kBlock, 0, s>>>(n, L.perm.get(), L.origin.get(), t, tile);
+        k_col_count<<<nb, kBlock, 0, s>>>(n, tile, cnt);
+        GLK_CHECK_LAUNCH();
+        scan_excl(cnt, trp, nt, T, s);
+        k_fill_int<<<blocks_for(nt), kBlock, 0, s>>>(cnt, nt, 0);
+        k_tile_fill<<<nb, kBlock, 0, s>>>(n, tile, trp, cnt, rows);
+        k_sort_rows<<<(nt + kRowWaves - 1) / kRowWaves, kBlock, 0, s>>>(nt, trp, rows, rows, srt, srt + n);
+        S.size.alloc(2 * (size_t)nt + 1);
+        S.rowid.alloc((size_t)nt * kPatchSlots);
+        S.info.alloc((size_t)nt * kPatchRows);
+        S.idx.alloc((size_t)nt * S.W * kPatchRows);
+        S.map.alloc((size_t)nt * S.W * kPatchRows);
+        int *total = S.size.get() + 2 * (size_t)nt;
+        k_fill_int<<<1, 64, 0, s>>>(total, 1, 0);
+        k_patch_build<<<nt, kPatchRows, 0, s>>>(trp, srt, L.Aa.rp.get(), L.Aa.ci.get(), L.perm.get(), L.color.get(),
+                                                L.ncolors, S.W, S.size.get(), S.rowid.get(), S.info.get(), S.idx.get(),
+                                                S.map.get(), total, err);
+        GLK_CHECK_LAUNCH();
+        const bool fits = read_int(err, s) == 0;
+        if (fits && read_int(total, s) <= kPatchMost * n) {
+            S.np = nt;
+            S.v64.alloc((size_t)nt * S.W * kPatchRows);
+            S.v32.alloc((size_t)nt * S.W * kPatchRows);
+            int *row0 = need(T.a, 2), *wid = need(T.b, 1);
+            to_device(row0, std::vector<int>{0, n}, s);
+            k_row_widths<<<1, kBlock, 0, s>>>(L.Pa.rp.get(), row0, wid);
+            GLK_CHECK_LAUNCH();
+            S.PW = read_int(wid, s);
+            const size_t np = (size_t)n * S.PW;
+            S.pci.alloc(np);
+            S.pmap.alloc(np);
+            S.pv64.alloc(np);
+            S.pv32.alloc(np);
+            k_pell_fill<<<nb, kBlock, 0, s>>>(n, S.PW, L.Pa.rp.get(), L.Pa.ci.get(), S.pci.get(), S.pmap.get());
+            GLK_CHECK_LAUNCH();
+            return;
+        }
+        if (fits) break;
+    }
+    S = PatchSet();
 }
 
 void precond_symbolic(gl_precond *pre, hipStream_t s)
@@ -1794,6 +2063,20 @@ void precond_symbolic(gl_precond *pre, hipStream_t s)
     build_apply_copies(pre, T, s);
     bottom_descriptors(pre, s);
     GLK_HIP(hipStreamSynchronize(s));
+}
+
+// The patches' copies of the matrix values, for the levels above the bottom
+// kernel and the dense operator.
+void patch_values_enqueue(gl_precond *pre, const Launch &L)
+{
+    for (int l = 0; l < pre->bottom; ++l) {
+        Level &lv = pre->L[l];
+        if (lv.patch.np == 0) continue;
+        const int ne = lv.patch.np * lv.patch.W * kPatchRows;
+        L.run(blocks_for(ne), EllValues{ne, lv.patch.map.get(), lv.Aa.v64.get(), lv.patch.v64.get(), lv.patch.v32.get()});
+        const int nq = lv.n * lv.patch.PW;
+        L.run(blocks_for(nq), EllValues{nq, lv.patch.pmap.get(), lv.Pa.v64.get(), lv.patch.pv64.get(), lv.patch.pv32.get()});
+    }
 }
 
 void precond_numeric_enqueue(gl_precond *pre, const double2 *psi, const Launch &L)
@@ -1858,6 +2141,7 @@ void precond_numeric_enqueue(gl_precond *pre, const double2 *psi, const Launch &
             }
         }
     }
+    patch_values_enqueue(pre, L);
     // coarsest: Cholesky in FP64 (positive definiteness check), then the inverse
     // in the V-cycle's row order, applied as a dense product
     const Csr &Mc = last > 0 ? Lc.Aa : Lc.A;
@@ -2020,6 +2304,7 @@ gl_status gl_precond_set_tiles(gl_precond *pre, const gl_tiles *tiles)
         hipStream_t s = pre->mesh->ws;
         GLK_HIP(hipStreamSynchronize(s));  // no pending use of the buffers re-made here
         bottom_descriptors(pre, s);
+        if (pre->has_values) patch_values_enqueue(pre, Launch{s});  // levels that were below the split
         form_tail(pre, s);
         GLK_HIP(hipStreamSynchronize(s));
     });

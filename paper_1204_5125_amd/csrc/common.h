@@ -367,6 +367,7 @@ struct gl_mesh {
     glk::DevBuf<int> s_erp, s_eo;    // per entry: its cells' other vertices (2D: one and -1; 3D: the opposite edge)
     glk::DevBuf<int> s_trp, s_tv;    // per node: the dim other vertices of each cell at the node
     glk::DevBuf<double> s_x;         // node coordinates (x, y, z), z = 0 in 2D
+    double s_lo[2] = {0.0, 0.0}, s_hi[2] = {0.0, 0.0};  // their bounds in x and y
     glk::DevBuf<double> s_alpha, s_phi, s_ks64, s_vol64;
     glk::DevBuf<float> s_ks32, s_vol32;
     glk::DevBuf<double2> s_kw64;

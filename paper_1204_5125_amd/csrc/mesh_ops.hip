@@ -941,6 +941,13 @@ gl_status gl_mesh_create_simplicial(const gl_simplicial_desc *desc, gl_stream st
             upload(m->s_trp, trp);
             upload(m->s_tv, tv);
             upload(m->s_x, pts);
+            for (int a = 0; a < 2; ++a) {
+                m->s_lo[a] = m->s_hi[a] = pts[a];
+                for (size_t i = 0; i < pts.size(); i += 3) {
+                    m->s_lo[a] = std::min(m->s_lo[a], pts[i + a]);
+                    m->s_hi[a] = std::max(m->s_hi[a], pts[i + a]);
+                }
+            }
             m->s_alpha.alloc(std::max(1, nnz));
             m->s_phi.alloc(std::max(1, nnz));
             m->s_kw64.alloc(std::max(1, nnz));

@@ -734,6 +734,175 @@ struct CsrSpmv {
     }
 };
 
+// ----------------------------------------------------- patch sweeps ---
+// A whole symmetric Gauss-Seidel sweep of a level in one dispatch: a
+// work-group runs every colour pass on its patch (PatchSet), a thread per row
+// with the row's entries in registers and the iterate in LDS.  A pass is a
+// handful of LDS reads and a barrier (0.25 us) where a dispatch per pass took
+// 3-4 us, most of it launch and two dependent round trips to memory; the price
+// is the rows that more than one patch updates (3-5 per row of the level).
+// Every row's value is the update of the per-pass kernels, so the sweep is the
+// same up to the order of the row sums.  The starting value of a row beyond
+// the patch is read, never written, and the sweep's result goes to another
+// vector (r, whose content is used up by then), so patches do not disturb one
+// another.
+template <class T, int W>
+struct PatchArrays {
+    const int *size, *rowid, *info;
+    const unsigned short *idx;
+    const C<T> *v;
+    const T *diag;
+    int ncol;
+};
+
+template <class T, int W>
+struct PatchRow {
+    int g, colour, last;
+    bool own;
+    int wide;  // entries of the wave's longest row: 8, 12 or 16
+    T d;
+    C<T> b, v[W];
+    int idx[W];
+};
+
+// Every load that depends on no other first, then those through the row's
+// index.  Most waves have no row of more than eight neighbours (the interior of
+// the 2D hierarchies): the entries after the eighth are read, and summed, by the
+// others only.
+template <class T, int W>
+__device__ __forceinline__ PatchRow<T, W> patch_load(const PatchArrays<T, W> &A, int p, const C<T> *b)
+{
+    PatchRow<T, W> R;
+    const int i = threadIdx.x;
+    const size_t base = (size_t)p * W * kPatchRows + i;
+    R.g = A.rowid[(size_t)p * kPatchSlots + i];
+    const int inf = A.info[(size_t)p * kPatchRows + i];
+    auto part = [&](auto k0, auto k1) {
+#pragma unroll
+        for (int k = decltype(k0)::value; k < decltype(k1)::value; ++k) {
+            R.v[k] = A.v[base + (size_t)k * kPatchRows];
+            R.idx[k] = A.idx[base + (size_t)k * kPatchRows];
+        }
+    };
+    part(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
+    R.d = A.diag[R.g];
+    R.b = b[R.g];
+    R.colour = inf & 255;
+    R.last = (inf >> 8) & 255;
+    R.own = (inf >> 16 & 1) != 0;
+    const int cnt = inf >> 20;
+    R.wide = 8;
+    if constexpr (W > 8)
+        if (__any(cnt > 8)) {
+            R.wide = 12;
+            part(std::integral_constant<int, 8>{}, std::integral_constant<int, 12>{});
+        }
+    if constexpr (W > 12)
+        if (__any(cnt > 12)) {
+            R.wide = 16;
+            part(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
+        }
+    return R;
+}
+
+// sum of the row's products
+template <class T, int W>
+__device__ __forceinline__ C<T> patch_sum(const PatchRow<T, W> &R, const C<T> *xs)
+{
+    C<T> s = mk<T>(0, 0);
+    auto part = [&](auto k0, auto k1) {
+#pragma unroll
+        for (int k = decltype(k0)::value; k < decltype(k1)::value; ++k) s = cadd(s, cmul(R.v[k], xs[R.idx[k]]));
+    };
+    part(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
+    if constexpr (W > 8)
+        if (R.wide > 8) part(std::integral_constant<int, 8>{}, std::integral_constant<int, 12>{});
+    if constexpr (W > 12)
+        if (R.wide > 12) part(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
+    return s;
+}
+
+template <class T, int W>
+__device__ __forceinline__ void patch_sweep(const PatchRow<T, W> &R, int ncol, C<T> *xs)
+{
+    const T inv = (T)1 / R.d;
+    for (int t = 0; t < 2 * ncol - 1; ++t) {
+        const int c = t < ncol ? t : 2 * ncol - 2 - t;
+        if (R.colour == c && t < R.last) xs[threadIdx.x] = cscale(csub(R.b, patch_sum<T, W>(R, xs)), inv);
+        __syncthreads();
+    }
+}
+
+// x = the sweep from zero, r = b - A x, on the patch's own rows
+template <class T, int W>
+struct PatchPre {
+    PatchArrays<T, W> A;
+    const C<T> *b;
+    C<T> *x, *r;
+    const int *gate;
+    __device__ void operator()(int bx, int) const
+    {
+        GATE_LOAD();
+        __shared__ C<T> xs[kPatchSlots + 1];
+        const PatchRow<T, W> R = patch_load<T, W>(A, bx, b);
+        for (int q = threadIdx.x; q <= kPatchSlots; q += kPatchRows) xs[q] = mk<T>(0, 0);
+        __syncthreads();
+        patch_sweep<T, W>(R, A.ncol, xs);
+        if (!R.own || !gate_go) return;
+        const C<T> xi = xs[threadIdx.x];
+        x[R.g] = xi;
+        r[R.g] = csub(csub(R.b, cscale(xi, R.d)), patch_sum<T, W>(R, xs));
+    }
+};
+
+// xo = the sweep from x + P x_c on the patch's own rows (TX: the precision of
+// x_c; P's rows padded to PW entries)
+template <class T, class TX, int W>
+struct PatchPost {
+    PatchArrays<T, W> A;
+    const C<T> *b, *x;
+    int PW;
+    const int *pci;
+    const C<T> *pv;
+    const C<TX> *xc;
+    C<T> *xo;
+    const int *gate;
+    __device__ C<T> start(int g) const
+    {
+        C<T> s = x[g];
+        const size_t o = (size_t)g * PW;
+        for (int k = 0; k < PW; k += 4) {
+            int c[4];
+            C<T> pk[4], xk[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                c[u] = k + u < PW ? pci[o + k + u] : 0;
+                pk[u] = k + u < PW ? pv[o + k + u] : mk<T>(0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) xk[u] = as_c<T>(xc[c[u]]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s = cadd(s, cmul(pk[u], xk[u]));
+        }
+        return s;
+    }
+    __device__ void operator()(int bx, int) const
+    {
+        GATE_LOAD();
+        __shared__ C<T> xs[kPatchSlots + 1];
+        const int ns = A.size[2 * bx + 1];
+        const int g1 = A.rowid[(size_t)bx * kPatchSlots + kPatchRows + threadIdx.x];
+        const PatchRow<T, W> R = patch_load<T, W>(A, bx, b);
+        xs[threadIdx.x] = start(R.g);
+        if (kPatchRows + (int)threadIdx.x < ns) xs[kPatchRows + threadIdx.x] = start(g1);
+        if (threadIdx.x == 0) xs[kPatchSlots] = mk<T>(0, 0);
+        __syncthreads();
+        patch_sweep<T, W>(R, A.ncol, xs);
+        if (R.own && gate_go) xo[R.g] = xs[threadIdx.x];
+    }
+};
+static_assert(kPatchSlots == 2 * kPatchRows, "a thread starts two slots");
+
 template <class T>
 struct FillZero {
     int n;
@@ -1336,6 +1505,71 @@ static void csr_residual(Level &Lv, int shift, const int *gate, const Launch &L)
     });
 }
 
+// ---- a level in patches
+template <class T> static const C<T> *pvals(const PatchSet &S);
+template <> const double2 *pvals<double>(const PatchSet &S) { return S.v64.get(); }
+template <> const float2 *pvals<float>(const PatchSet &S) { return S.v32.get(); }
+
+template <class T> static const C<T> *ppvals(const PatchSet &S);
+template <> const double2 *ppvals<double>(const PatchSet &S) { return S.pv64.get(); }
+template <> const float2 *ppvals<float>(const PatchSet &S) { return S.pv32.get(); }
+
+// calls f with the patch arrays of the level's row width
+template <class T, class F>
+static void with_patch(const Level &Lv, F &&f)
+{
+    const PatchSet &S = Lv.patch;
+    auto go = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        f(PatchArrays<T, W>{S.size.get(), S.rowid.get(), S.info.get(), S.idx.get(), pvals<T>(S), dgn<T>(Lv), Lv.ncolors},
+          w);
+    };
+    if (S.W == 8) go(std::integral_constant<int, 8>{});
+    else if (S.W == 12) go(std::integral_constant<int, 12>{});
+    else go(std::integral_constant<int, 16>{});
+}
+
+// algorithmic bytes of a sweep: the level's entries, b, the diagonal and x once
+template <class T>
+static double patch_bytes(const Level &Lv)
+{
+    return (double)Lv.Aa.nnz * (sizeof(C<T>) + 4.0) + Lv.n * (2.0 * sizeof(C<T>) + sizeof(T));
+}
+
+template <class T>
+static void patch_pre(Level &Lv, const int *gate, const Launch &L)
+{
+    prof_launch(PROF_COARSE_SWEEP, patch_bytes<T>(Lv), L, [&] {
+        with_patch<T>(Lv, [&](auto A, auto w) {
+            constexpr int W = decltype(w)::value;
+            L.run<PatchPre<T, W>, kPatchRows>(Lv.patch.np,
+                                              PatchPre<T, W>{A, vec_b<T>(Lv), vec_x<T>(Lv), vec_r<T>(Lv), gate});
+        });
+    });
+}
+
+// result in vec_r
+template <class T, class TX = T>
+static void patch_post(Level &Lv, const C<TX> *xc, const int *gate, const Launch &L)
+{
+    prof_launch(PROF_COARSE_SWEEP, patch_bytes<T>(Lv), L, [&] {
+        with_patch<T>(Lv, [&](auto A, auto w) {
+            constexpr int W = decltype(w)::value;
+            L.run<PatchPost<T, TX, W>, kPatchRows>(
+                Lv.patch.np, PatchPost<T, TX, W>{A, vec_b<T>(Lv), vec_x<T>(Lv), Lv.patch.PW, Lv.patch.pci.get(),
+                                                 ppvals<T>(Lv.patch), xc, vec_r<T>(Lv), gate});
+        });
+    });
+}
+
+// where the cycle leaves the iterate of level l
+template <class T>
+static C<T> *cycle_result(gl_precond *pre, int l)
+{
+    Level &Lv = pre->L[l];
+    return l < pre->bottom && Lv.patch.np ? vec_r<T>(Lv) : vec_x<T>(Lv);
+}
+
 // calls f with the tile shape of gl_tiles.l0_tiled (1, 2 or 3)
 template <class F>
 static void l0_tiled_shape(int which, F &&f)
@@ -1360,8 +1594,12 @@ static void coarse_levels(gl_precond *pre, const int *gate, const Launch &L)
     const int sh = pre->lane_shift;
     for (int l = 1; l < nb_first; ++l) {
         Level &Lv = pre->L[l];
-        csr_sgs<TC>(Lv, sh, true, gate, L);
-        csr_residual<TC>(Lv, sh, gate, L);
+        if (Lv.patch.np) {
+            patch_pre<TC>(Lv, gate, L);
+        } else {
+            csr_sgs<TC>(Lv, sh, true, gate, L);
+            csr_residual<TC>(Lv, sh, gate, L);
+        }
         csr_spmv<TC>(Lv.Ra, vec_r<TC>(Lv), vec_b<TC>(pre->L[l + 1]), false, sh, gate, L);
     }
     if (pre->bottom < pre->tail) {
@@ -1373,8 +1611,13 @@ static void coarse_levels(gl_precond *pre, const int *gate, const Launch &L)
     }
     for (int l = nb_first - 1; l >= 1; --l) {
         Level &Lv = pre->L[l];
-        csr_spmv<TC>(Lv.Pa, vec_x<TC>(pre->L[l + 1]), vec_x<TC>(Lv), true, sh, gate, L);
-        csr_sgs<TC>(Lv, sh, false, gate, L);
+        const C<TC> *xc = cycle_result<TC>(pre, l + 1);
+        if (Lv.patch.np) {
+            patch_post<TC>(Lv, xc, gate, L);
+        } else {
+            csr_spmv<TC>(Lv.Pa, xc, vec_x<TC>(Lv), true, sh, gate, L);
+            csr_sgs<TC>(Lv, sh, false, gate, L);
+        }
     }
 }
 
@@ -1450,6 +1693,7 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
     });
     // levels >= 1: b of level 1 in, x of level 1 out
     coarse_levels<TC>(pre, gate, L);
+    const C<TC> *x1 = cycle_result<TC>(pre, 1);
     // level 0, up: red with the coarse correction, black, red + output
     // black coarse correction, then the red pass (fusing the two reads every
     // black correction four times and was measured slower); in 2D by default
@@ -1467,19 +1711,18 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
                 if (add)
                     L.run<L0PostTile<T, TC, 1, S>, S::threads>(
                         nbt, L0PostTile<T, TC, 1, S>{g, b0, x0, hd, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
-                                                     vec_x<TC>(L1), z, vdot, slot, want, ntx, gate});
+                                                     x1, z, vdot, slot, want, ntx, gate});
                 else
                     L.run<L0PostTile<T, TC, 0, S>, S::threads>(
                         nbt, L0PostTile<T, TC, 0, S>{g, b0, x0, hd, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
-                                                     vec_x<TC>(L1), z, vdot, slot, want, ntx, gate});
+                                                     x1, z, vdot, slot, want, ntx, gate});
             });
         });
         if (want) launch_finalize(slot.partials, nbt, fmode, ks, store, gate, L);
         return;
     }
     prof_launch(PROF_L0_TRANSFER, b_prol, L, [&] {
-        L.run(nbp, L0ProlongBlack<DIM, T, TC>{g, x0, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
-                                              vec_x<TC>(L1), gate});
+        L.run(nbp, L0ProlongBlack<DIM, T, TC>{g, x0, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb), x1, gate});
     });
     prof_launch(PROF_L0_SWEEP, b_sweep, L, [&] {
         L.run(nbp, L0Sweep<DIM, T>{g, 0, b0, x0, U, hs, gate});
@@ -1523,12 +1766,22 @@ static void vcycle_once_simplicial(const gl_precond *cpre, const double2 *v, con
     const int *perm = L0.perm.get();
     C<T> *x0 = vec_x<T>(L0);
     L.run(nb0, NarrowPerm<T>{n0, v, perm, vec_b<T>(L0), gate});
-    csr_sgs<T>(L0, sh, true, gate, L);
-    csr_residual<T>(L0, sh, gate, L);
+    if (L0.patch.np) {
+        patch_pre<T>(L0, gate, L);
+    } else {
+        csr_sgs<T>(L0, sh, true, gate, L);
+        csr_residual<T>(L0, sh, gate, L);
+    }
     csr_spmv<TC, T>(L0.Ra, vec_r<T>(L0), vec_b<TC>(L1), false, sh, gate, L);
     coarse_levels<TC>(pre, gate, L);
-    csr_spmv<T, TC>(L0.Pa, vec_x<TC>(L1), x0, true, sh, gate, L);
-    csr_sgs<T>(L0, sh, false, gate, L);
+    const C<TC> *x1 = cycle_result<TC>(pre, 1);
+    if (L0.patch.np) {
+        patch_post<T, TC>(L0, x1, gate, L);
+        x0 = vec_r<T>(L0);
+    } else {
+        csr_spmv<T, TC>(L0.Pa, x1, x0, true, sh, gate, L);
+        csr_sgs<T>(L0, sh, false, gate, L);
+    }
     if (add) L.run(nb0, OutputPerm<T, 1>{n0, x0, perm, vdot, z, slot, want, gate});
     else L.run(nb0, OutputPerm<T, 0>{n0, x0, perm, vdot, z, slot, want, gate});
     if (want) launch_finalize(slot.partials, nb0, fmode, ks, store, gate, L);
@@ -1869,6 +2122,10 @@ void bottom_descriptors(gl_precond *pre, hipStream_t s)
             if (L.n > pre->bottom_rows || L.ncolors > kMaxColors) break;
             first = l;
         }
+    // a level in patches takes two dispatches whatever its size and stays out
+    // of the bottom kernel (106 rows of 9 colours above a dense one of 8: 17 us
+    // with its transfers and the dense product; 49 us in the bottom kernel)
+    while (first < tail && pre->L[first].patch.np) ++first;
     pre->bottom = first;
     if (tail < last) {
         const int nt = pre->L[tail].n;
