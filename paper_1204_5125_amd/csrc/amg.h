@@ -241,8 +241,19 @@ __device__ __forceinline__ void minres_finalize(KrylovScalars *ks, int mode, dou
     }
 }
 
+// What happens to one total: stored to *out (FIN_STORE) or given to
+// minres_finalize.
+struct FinTask {
+    const double *partials = nullptr;
+    int mode = FIN_STORE;
+    double *out = nullptr;
+};
+
 // Sum nparts block partials in a fixed order (one work-group) and act on the
-// total: store it to *out (FIN_STORE) or update the Krylov scalars.
+// total: store it to *out (FIN_STORE) or update the Krylov scalars.  The second
+// form sums two arrays of partials and acts on a's total, then b's.
+void launch_finalize2(const FinTask &a, const FinTask &b, int nparts, KrylovScalars *ks, const int *gate,
+                      const Launch &L);
 void launch_finalize(const double *partials, int nparts, int mode, KrylovScalars *ks, double *out,
                      const int *gate, const Launch &L);
 inline void launch_finalize(const double *partials, int nparts, int mode, KrylovScalars *ks, double *out,
@@ -294,15 +305,41 @@ struct gl_precond {
 };
 
 namespace glk {
+// Deflated solves: the kernel that writes the preconditioner's output z also
+// reduces <u, z>_R = sum d Im(conj(psi) z), u = i psi (psi == nullptr: not asked).
+struct DeflDot {
+    const double2 *psi = nullptr;
+    const double *vol = nullptr;  // |V_i| of a simplicial mesh
+    int N[3] = {1, 1, 1};
+    double h[3] = {1.0, 1.0, 1.0};
+    RedSlot slot{nullptr};
+    // the term of node i at grid coordinates c
+    template <int DIM>
+    __device__ __forceinline__ double term(int i, const int c[3], double2 z) const
+    {
+        double d = 1.0;
+        if constexpr (DIM == 0) {
+            d = vol[i];
+        } else {
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) d *= c[a] == 0 || c[a] == N[a] - 1 ? 0.5 * h[a] : h[a];
+        }
+        const double2 p = psi[i];
+        return d * (p.x * z.y - p.y * z.x);
+    }
+};
+
 // V-cycle entry used by gl_precond_apply and by MINRES: z = AMG_k(H, v).
 // gate (nullable): skip all work when *gate == 0.  When ks != nullptr the
 // kernel that writes z also reduces Re<v, z> and the total is handed to
-// minres_finalize(ks, mode, total).
+// minres_finalize(ks, mode, total); with dd.psi set also <u, z>_R, handed on as
+// FIN_DEFL_Y after it.
 // prec: the precision of this application (the handle holds both).
 void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
-                    KrylovScalars *ks, int mode, const Launch &L, gl_precision prec);
+                    KrylovScalars *ks, int mode, const Launch &L, gl_precision prec, const DeflDot &dd = DeflDot{});
 void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
                     KrylovScalars *ks, int mode, const Launch &L);  // in the handle's precision
+DeflDot defl_dot(const gl_mesh *m, const double2 *psi);
 void gl_residual_enqueue(const gl_mesh *m, const double2 *psi, double2 *out, double *dresult,
                          hipStream_t s);
 // the same two dispatches (residual with block partials, fixed-order sum),

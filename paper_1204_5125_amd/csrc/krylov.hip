@@ -888,15 +888,18 @@ static Ksolve make_ksolve(const gl_mesh *m, const double2 *psi, const gl_precond
                   pre ? pre->opts.precision : GL_FP64, defl};
 }
 
-// z = Pi z after a new preconditioner output (deflated solves)
+// z = Pi z after a new preconditioner output (deflated solves); dotted: the
+// kernel that wrote z has reduced <u, z>_R
 template <int DIM>
-static void defl_project_z(const Ksolve &k, double2 *z, const Launch &L)
+static void defl_project_z(const Ksolve &k, double2 *z, bool dotted, const Launch &L)
 {
     const gl_mesh *m = k.m;
     const int n = m->g.n, nb = blocks_for(n);
     KrylovScalars *ks = reinterpret_cast<KrylovScalars *>(m->kscal.get());
-    L.run(nb, DeflZ<DIM>{geom_t<double>(m->g), k.psi, z, ks, red_slot(m, 3)});
-    launch_finalize(red_slot(m, 3).partials, nb, FIN_DEFL_Y, ks, nullptr, nullptr, L);
+    if (!dotted) {
+        L.run(nb, DeflZ<DIM>{geom_t<double>(m->g), k.psi, z, ks, red_slot(m, 3)});
+        launch_finalize(red_slot(m, 3).partials, nb, FIN_DEFL_Y, ks, nullptr, nullptr, L);
+    }
     L.run(nb, DeflApply{n, k.psi, z, ks});
 }
 
@@ -922,19 +925,20 @@ static void ksolve_init(const Ksolve &k, double rtol, int max_iter, const Launch
     L.run<KsInit, 64>(1, KsInit{ks, rtol, max_iter});
     if (k.defl) {
         L.run(nb, DeflInit<DIM>{g, k.psi, k.rhs, red_slot(m, 2), red_slot(m, 3)});
-        launch_finalize(red_slot(m, 2).partials, nb, FIN_STORE, nullptr, &ks->defl_c, nullptr, L);
-        launch_finalize(red_slot(m, 3).partials, nb, FIN_STORE, nullptr, &ks->defl_sq, nullptr, L);
+        launch_finalize2(FinTask{red_slot(m, 2).partials, FIN_STORE, &ks->defl_c},
+                         FinTask{red_slot(m, 3).partials, FIN_STORE, &ks->defl_sq}, nb, nullptr, nullptr, L);
         L.run(nb, MinresInitDefl<DIM>{g, k.psi, k.rhs, k.v, k.vp, k.w, k.wp, k.x, ks});
     } else {
         L.run(nb, MinresInit<DIM>{g, k.rhs, k.v, k.vp, k.w, k.wp, k.x});
     }
     if (k.pre) {
-        vcycle_enqueue(k.pre, k.v, k.z, nullptr, ks, FIN_MINRES_INIT, L, k.prec);
+        vcycle_enqueue(k.pre, k.v, k.z, nullptr, ks, FIN_MINRES_INIT, L, k.prec,
+                       k.defl ? defl_dot(m, k.psi) : DeflDot{});
     } else {
         L.run(nb, Unprec<DIM>{g, k.v, k.z, nullptr, red_slot(m, 1)});
         launch_finalize(red_slot(m, 1).partials, nb, FIN_MINRES_INIT, ks, nullptr, nullptr, L);
     }
-    if (k.defl) defl_project_z<DIM>(k, k.z, L);
+    if (k.defl) defl_project_z<DIM>(k, k.z, k.pre != nullptr, L);
 }
 
 template <int DIM>
@@ -957,9 +961,9 @@ static void enqueue_iteration(Ksolve &k, const Launch &L)
         L.run(nb, MinresJapply<DIM>{g, k.psi, k.z, link_tab<double>(m), k.q, k.zn, k.w, k.wp, k.x, ks,
                                     red_slot(m, 0), red_slot(m, 2), k.defl ? 1 : 0, zb, zbh});
     });
-    launch_finalize(red_slot(m, 0).partials, nb, FIN_DELTA, ks, nullptr, gate, L);
+    launch_finalize2(FinTask{red_slot(m, 0).partials, FIN_DELTA, nullptr},
+                     k.defl ? FinTask{red_slot(m, 2).partials, FIN_STORE, &ks->defl_sq} : FinTask{}, nb, ks, gate, L);
     if (k.defl) {
-        launch_finalize(red_slot(m, 2).partials, nb, FIN_STORE, nullptr, &ks->defl_sq, gate, L);
         prof_launch(PROF_VUPDATE, 80.0 * n, L,
                     [&] { L.run(nb, MinresVupdateDefl<DIM>{g, k.psi, k.q, k.v, k.vp, ks, vb, vb32}); });
     } else {
@@ -981,12 +985,12 @@ static void enqueue_iteration(Ksolve &k, const Launch &L)
         }
     }
     if (k.pre) {
-        vcycle_enqueue(k.pre, k.vp, k.zn, gate, ks, fin, L, k.prec);
+        vcycle_enqueue(k.pre, k.vp, k.zn, gate, ks, fin, L, k.prec, k.defl ? defl_dot(m, k.psi) : DeflDot{});
     } else {
         L.run(nb, Unprec<DIM>{g, k.vp, k.zn, gate, red_slot(m, 1)});
         launch_finalize(red_slot(m, 1).partials, nb, fin, ks, nullptr, gate, L);
     }
-    if (k.defl) defl_project_z<DIM>(k, k.zn, L);
+    if (k.defl) defl_project_z<DIM>(k, k.zn, k.pre != nullptr, L);
     if (k.rb) L.run<ReorthColumn, 64>(1, ReorthColumn{k.kmax, R.R, R.cs, R.sn, R.gv, R.h, ks});
     std::swap(k.v, k.vp);
     std::swap(k.z, k.zn);
@@ -1083,18 +1087,18 @@ static void true_residual(const gl_mesh *m, const double2 *psi, const double2 *x
         k_residual_vec<DIM><<<nb, kBlock, 0, s>>>(g, psi, x, b, link_tab<double>(m), r);
         k_defl_dots<DIM><<<nb, kBlock, 0, s>>>(g, psi, r, b, red_slot(m, 0), red_slot(m, 1));
         GLK_CHECK_LAUNCH();
-        launch_finalize(red_slot(m, 0).partials, nb, FIN_STORE, nullptr, &ks->res_u_num, nullptr, s);
-        launch_finalize(red_slot(m, 1).partials, nb, FIN_STORE, nullptr, &ks->res_u_den, nullptr, s);
+        launch_finalize2(FinTask{red_slot(m, 0).partials, FIN_STORE, &ks->res_u_num},
+                         FinTask{red_slot(m, 1).partials, FIN_STORE, &ks->res_u_den}, nb, ks, nullptr, Launch{s});
         k_defl_norms<DIM><<<nb, kBlock, 0, s>>>(g, psi, r, b, ks, red_slot(m, 2), red_slot(m, 3));
         GLK_CHECK_LAUNCH();
-        launch_finalize(red_slot(m, 2).partials, nb, FIN_RESNUM, ks, nullptr, nullptr, s);
-        launch_finalize(red_slot(m, 3).partials, nb, FIN_RESDEN, ks, nullptr, nullptr, s);
+        launch_finalize2(FinTask{red_slot(m, 2).partials, FIN_RESNUM, nullptr},
+                         FinTask{red_slot(m, 3).partials, FIN_RESDEN, nullptr}, nb, ks, nullptr, Launch{s});
         return;
     }
     k_true_residual<DIM><<<nb, kBlock, 0, s>>>(g, psi, x, b, link_tab<double>(m), red_slot(m, 2), red_slot(m, 3));
     GLK_CHECK_LAUNCH();
-    launch_finalize(red_slot(m, 2).partials, nb, FIN_RESNUM, ks, nullptr, nullptr, s);
-    launch_finalize(red_slot(m, 3).partials, nb, FIN_RESDEN, ks, nullptr, nullptr, s);
+    launch_finalize2(FinTask{red_slot(m, 2).partials, FIN_RESNUM, nullptr},
+                     FinTask{red_slot(m, 3).partials, FIN_RESDEN, nullptr}, nb, ks, nullptr, Launch{s});
 }
 
 template <int DIM>

@@ -299,6 +299,7 @@ struct L0Last {
     const double2 *vdot;
     RedSlot slot;
     int want_dot;
+    DeflDot dd;
     const int *gate;
     __device__ void operator()(int bx, int nbx) const
     {
@@ -317,7 +318,7 @@ struct L0Last {
         C<T> xr = mk<T>(0, 0);
         const C<T> xb = black ? x[g.npair + t] : mk<T>(0, 0);
         double2 zq[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
-        double part = 0.0;
+        double part = 0.0, part_u = 0.0;
         if (red) {
             const int c[3] = {P.c[0] + sr, P.c[1], P.c[2]};
             const C<T> bi = b[t];
@@ -334,6 +335,10 @@ struct L0Last {
                 if (ADD) zi = cadd(z[i], zi);
                 zq[q] = zi;
                 if (want_dot) part += redot(vdot[i], zi);
+                if (dd.psi) {
+                    const int c[3] = {P.c[0] + q, P.c[1], P.c[2]};
+                    part_u += dd.term<DIM>(i, c, zi);
+                }
             }
         }
         if (!gate_go) return;
@@ -342,6 +347,7 @@ struct L0Last {
             if (P.odd) z[P.ie + 1] = zq[1];
         }
         if (want_dot) block_reduce_store(part, slot, sm, bx);
+        if (dd.psi) block_reduce_store(part_u, dd.slot, sm, bx);
     }
 };
 
@@ -536,6 +542,7 @@ struct L0PostTile {
     const double2 *vdot;
     RedSlot slot;
     int want_dot;
+    DeflDot dd;
     int ntx;
     const int *gate;
     __device__ void operator()(int bx, int nbx) const
@@ -580,7 +587,7 @@ struct L0PostTile {
             __syncthreads();
         }
         // last red on the tile, into z only; z on every node of the tile
-        double part = 0.0;
+        double part = 0.0, part_u = 0.0;
         l0_tile_nodes<S>(T0, g.N, [&](int q, int gx, int gy) {
             C<T> xi = sx[q];
             if (((gx + gy) & 1) == 0)
@@ -589,9 +596,14 @@ struct L0PostTile {
             double2 zi = widen(xi);
             if (ADD) zi = cadd(z[i], zi);
             if (want_dot) part += redot(vdot[i], zi);
+            if (dd.psi) {
+                const int c[3] = {gx, gy, 0};
+                part_u += dd.term<2>(i, c, zi);
+            }
             if (gate_go) z[i] = zi;
         });
         if (want_dot && gate_go) block_reduce_store(part, slot, sm, bx);
+        if (dd.psi && gate_go) block_reduce_store(part_u, dd.slot, sm, bx);
     }
 };
 
@@ -738,9 +750,14 @@ struct CsrSpmv {
 // A whole symmetric Gauss-Seidel sweep of a level in one dispatch: a
 // work-group runs every colour pass on its patch (PatchSet), a thread per row
 // with the row's entries in registers and the iterate in LDS.  A pass is a
-// handful of LDS reads and a barrier (0.25 us) where a dispatch per pass took
-// 3-4 us, most of it launch and two dependent round trips to memory; the price
-// is the rows that more than one patch updates (3-5 per row of the level).
+// handful of LDS reads, a chain of FP64 adds and a barrier (0.5 us) where a
+// dispatch per pass took 3-4 us, most of it launch and two dependent round trips
+// to memory; loading the patch takes 4-6 us (latency: rows, then what they
+// index), and the price is the rows that more than one patch updates (3-5 per
+// row of the level).  FP64, down / up: 4 923 and 545 rows of 7 and 8 colours 12 /
+// 14 us (46 / 50 as 14-16 dispatches), 44 075 rows of 5 colours 13 / 19 us (35 /
+// 31); FP32, 175 446 rows of 4 colours 21 / 38 us (42 / 40): there it is bound
+// by the traffic of the shared rows, and about even.
 // Every row's value is the update of the per-pass kernels, so the sweep is the
 // same up to the order of the row sums.  The starting value of a row beyond
 // the patch is read, never written, and the sweep's result goes to another
@@ -931,7 +948,7 @@ struct Narrow {
 };
 
 // z = x (ADD = 0) or z += x (ADD = 1); partial sums of Re<vdot, z>
-template <class T, int ADD>
+template <int DIM, class T, int ADD>
 struct Output {
     int n;
     const C<T> *x;
@@ -939,20 +956,27 @@ struct Output {
     double2 *z;
     RedSlot slot;
     int want_dot;
+    DeflDot dd;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
         GATE();
         __shared__ double sm[kBlock / 64];
         const int i = bx * kBlock + threadIdx.x;
-        double part = 0.0;
+        double part = 0.0, part_u = 0.0;
         if (i < n) {
             double2 zi = widen(x[i]);
             if (ADD) zi = cadd(z[i], zi);
             z[i] = zi;
             if (want_dot) part = redot(vdot[i], zi);
+            if (dd.psi) {
+                int c[3];
+                node_coords<DIM>(dd.N, i, c);
+                part_u = dd.term<DIM>(i, c, zi);
+            }
         }
         if (want_dot) block_reduce_store(part, slot, sm, bx);
+        if (dd.psi) block_reduce_store(part_u, dd.slot, sm, bx);
     }
 };
 
@@ -983,21 +1007,27 @@ struct OutputPerm {
     double2 *z;
     RedSlot slot;
     int want_dot;
+    DeflDot dd;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
         GATE();
         __shared__ double sm[kBlock / 64];
         const int r = bx * kBlock + threadIdx.x;
-        double part = 0.0;
+        double part = 0.0, part_u = 0.0;
         if (r < n) {
             const int i = perm[r];
             double2 zi = widen(x[r]);
             if (ADD) zi = cadd(z[i], zi);
             z[i] = zi;
             if (want_dot) part = redot(vdot[i], zi);
+            if (dd.psi) {
+                const int c[3] = {i, 0, 0};
+                part_u = dd.term<0>(i, c, zi);
+            }
         }
         if (want_dot) block_reduce_store(part, slot, sm, bx);
+        if (dd.psi) block_reduce_store(part_u, dd.slot, sm, bx);
     }
 };
 
@@ -1621,10 +1651,31 @@ static void coarse_levels(gl_precond *pre, const int *gate, const Launch &L)
     }
 }
 
+// the totals of the output kernel's partials: Re<vdot, z> and, when asked, <u, z>_R
+static void finish_dots(RedSlot slot, int nb, int mode, KrylovScalars *ks, double *store, const DeflDot &dd,
+                        const int *gate, const Launch &L)
+{
+    const FinTask a{slot.partials, mode, store};
+    launch_finalize2(a, dd.psi ? FinTask{dd.slot.partials, FIN_DEFL_Y, nullptr} : FinTask{}, nb, ks, gate, L);
+}
+
+DeflDot defl_dot(const gl_mesh *m, const double2 *psi)
+{
+    DeflDot d;
+    d.psi = psi;
+    d.vol = m->g.vol64;
+    for (int a = 0; a < 3; ++a) {
+        d.N[a] = m->g.N[a];
+        d.h[a] = m->g.h[a];
+    }
+    d.slot = red_slot(m, 3);
+    return d;
+}
+
 template <int DIM, class T, class TC>
 static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const double2 *vdot, double2 *z,
                         const int *gate, KrylovScalars *ks, int mode, int add, const Launch &L,
-                        double *store = nullptr)
+                        double *store, const DeflDot &dd)
 {
     gl_precond *pre = const_cast<gl_precond *>(cpre);
     const gl_mesh *m = pre->mesh;
@@ -1644,9 +1695,9 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
         C<TC> *xc0 = vec_x<TC>(L0);
         L.run(nb0, Narrow<TC>{n0, v, vec_b<TC>(L0), gate});
         L.run(blocks_for((int64_t)n0 * 64), DenseApply<TC>{n0, cinv<TC>(pre), vec_b<TC>(L0), xc0, gate});
-        if (add) L.run(nb0, Output<TC, 1>{n0, xc0, vdot, z, slot, want, gate});
-        else L.run(nb0, Output<TC, 0>{n0, xc0, vdot, z, slot, want, gate});
-        if (want) launch_finalize(slot.partials, nb0, fmode, ks, store, gate, L);
+        if (add) L.run(nb0, Output<DIM, TC, 1>{n0, xc0, vdot, z, slot, want, dd, gate});
+        else L.run(nb0, Output<DIM, TC, 0>{n0, xc0, vdot, z, slot, want, dd, gate});
+        if (want) finish_dots(slot, nb0, fmode, ks, store, dd, gate, L);
         return;
     }
     const T *hd = diag<T>(L0), *hs = hsplit<T>(L0);
@@ -1711,14 +1762,14 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
                 if (add)
                     L.run<L0PostTile<T, TC, 1, S>, S::threads>(
                         nbt, L0PostTile<T, TC, 1, S>{g, b0, x0, hd, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
-                                                     x1, z, vdot, slot, want, ntx, gate});
+                                                     x1, z, vdot, slot, want, dd, ntx, gate});
                 else
                     L.run<L0PostTile<T, TC, 0, S>, S::threads>(
                         nbt, L0PostTile<T, TC, 0, S>{g, b0, x0, hd, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
-                                                     x1, z, vdot, slot, want, ntx, gate});
+                                                     x1, z, vdot, slot, want, dd, ntx, gate});
             });
         });
-        if (want) launch_finalize(slot.partials, nbt, fmode, ks, store, gate, L);
+        if (want) finish_dots(slot, nbt, fmode, ks, store, dd, gate, L);
         return;
     }
     prof_launch(PROF_L0_TRANSFER, b_prol, L, [&] {
@@ -1731,10 +1782,10 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
         L.run(nbp, L0Sweep<DIM, T>{g, 1, b0, x0, U, hs, gate});
     });
     prof_launch(PROF_L0_SWEEP, b_last, L, [&] {
-        if (add) L.run(nbp, L0Last<DIM, T, 1>{g, b0, x0, U, hs, z, vdot, slot, want, gate});
-        else L.run(nbp, L0Last<DIM, T, 0>{g, b0, x0, U, hs, z, vdot, slot, want, gate});
+        if (add) L.run(nbp, L0Last<DIM, T, 1>{g, b0, x0, U, hs, z, vdot, slot, want, dd, gate});
+        else L.run(nbp, L0Last<DIM, T, 0>{g, b0, x0, U, hs, z, vdot, slot, want, dd, gate});
     });
-    if (want) launch_finalize(slot.partials, nbp, fmode, ks, store, gate, L);
+    if (want) finish_dots(slot, nbp, fmode, ks, store, dd, gate, L);
 }
 
 // Level 0 of a simplicial mesh is a CSR level like the coarse ones: its
@@ -1743,7 +1794,7 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
 template <class T, class TC>
 static void vcycle_once_simplicial(const gl_precond *cpre, const double2 *v, const double2 *vdot, double2 *z,
                                    const int *gate, KrylovScalars *ks, int mode, int add, const Launch &L,
-                                   double *store)
+                                   double *store, const DeflDot &dd)
 {
     gl_precond *pre = const_cast<gl_precond *>(cpre);
     const gl_mesh *m = pre->mesh;
@@ -1756,9 +1807,9 @@ static void vcycle_once_simplicial(const gl_precond *cpre, const double2 *v, con
         C<TC> *xc0 = vec_x<TC>(L0);
         L.run(nb0, Narrow<TC>{n0, v, vec_b<TC>(L0), gate});
         L.run(blocks_for((int64_t)n0 * 64), DenseApply<TC>{n0, cinv<TC>(pre), vec_b<TC>(L0), xc0, gate});
-        if (add) L.run(nb0, Output<TC, 1>{n0, xc0, vdot, z, slot, want, gate});
-        else L.run(nb0, Output<TC, 0>{n0, xc0, vdot, z, slot, want, gate});
-        if (want) launch_finalize(slot.partials, nb0, fmode, ks, store, gate, L);
+        if (add) L.run(nb0, Output<0, TC, 1>{n0, xc0, vdot, z, slot, want, dd, gate});
+        else L.run(nb0, Output<0, TC, 0>{n0, xc0, vdot, z, slot, want, dd, gate});
+        if (want) finish_dots(slot, nb0, fmode, ks, store, dd, gate, L);
         return;
     }
     Level &L1 = pre->L[1];
@@ -1782,19 +1833,19 @@ static void vcycle_once_simplicial(const gl_precond *cpre, const double2 *v, con
         csr_spmv<T, TC>(L0.Pa, x1, x0, true, sh, gate, L);
         csr_sgs<T>(L0, sh, false, gate, L);
     }
-    if (add) L.run(nb0, OutputPerm<T, 1>{n0, x0, perm, vdot, z, slot, want, gate});
-    else L.run(nb0, OutputPerm<T, 0>{n0, x0, perm, vdot, z, slot, want, gate});
-    if (want) launch_finalize(slot.partials, nb0, fmode, ks, store, gate, L);
+    if (add) L.run(nb0, OutputPerm<T, 1>{n0, x0, perm, vdot, z, slot, want, dd, gate});
+    else L.run(nb0, OutputPerm<T, 0>{n0, x0, perm, vdot, z, slot, want, dd, gate});
+    if (want) finish_dots(slot, nb0, fmode, ks, store, dd, gate, L);
 }
 
 // One V-cycle on H x = D v from x = 0 (DIM 0: a simplicial mesh)
 template <int DIM, class T, class TC>
 static void vcycle_once(const gl_precond *cpre, const double2 *v, const double2 *vdot, double2 *z,
                         const int *gate, KrylovScalars *ks, int mode, int add, const Launch &L,
-                        double *store = nullptr)
+                        double *store = nullptr, const DeflDot &dd = DeflDot{})
 {
-    if constexpr (DIM == 0) vcycle_once_simplicial<T, TC>(cpre, v, vdot, z, gate, ks, mode, add, L, store);
-    else vcycle_once_grid<DIM, T, TC>(cpre, v, vdot, z, gate, ks, mode, add, L, store);
+    if constexpr (DIM == 0) vcycle_once_simplicial<T, TC>(cpre, v, vdot, z, gate, ks, mode, add, L, store, dd);
+    else vcycle_once_grid<DIM, T, TC>(cpre, v, vdot, z, gate, ks, mode, add, L, store, dd);
 }
 
 // ------------------------------------------------------------- R_inf ---
@@ -1925,7 +1976,7 @@ static PcgBufs pcg_bufs(const gl_precond *pre)
 // m steps of CG; z = x with the Krylov partials of Re<vdot, z> when ks is set
 template <int DIM, class T, class TC>
 static void vcycle_pcg(const gl_precond *pre, const double2 *v, double2 *z, const int *gate, KrylovScalars *ks,
-                       int mode, const Launch &L)
+                       int mode, const Launch &L, const DeflDot &dd)
 {
     const gl_mesh *m = pre->mesh;
     const GeomT<double> g = geom_t<double>(m->g);
@@ -1946,8 +1997,8 @@ static void vcycle_pcg(const gl_precond *pre, const double2 *v, double2 *z, cons
         }
     }
     const RedSlot slot = red_slot(m, 1);
-    L.run(nb, Output<double, 0>{n, B.x, v, z, slot, ks != nullptr, gate});
-    if (ks) launch_finalize(slot.partials, nb, mode, ks, nullptr, gate, L);
+    L.run(nb, Output<DIM, double, 0>{n, B.x, v, z, slot, ks != nullptr, dd, gate});
+    if (ks) finish_dots(slot, nb, mode, ks, nullptr, dd, gate, L);
 }
 
 template <int DIM>
@@ -2004,15 +2055,15 @@ void pcg_calibrate(gl_precond *pre, hipStream_t s)
 
 template <int DIM, class T, class TC>
 static void vcycle_k(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
-                     KrylovScalars *ks, int mode, const Launch &L)
+                     KrylovScalars *ks, int mode, const Launch &L, const DeflDot &dd)
 {
     const int k = pre->opts.cycles;
     if (k == 0) {
-        vcycle_pcg<DIM, T, TC>(pre, v, z, gate, ks, mode, L);
+        vcycle_pcg<DIM, T, TC>(pre, v, z, gate, ks, mode, L, dd);
         return;
     }
     if (k <= 1) {
-        vcycle_once<DIM, T, TC>(pre, v, v, z, gate, ks, mode, 0, L);
+        vcycle_once<DIM, T, TC>(pre, v, v, z, gate, ks, mode, 0, L, nullptr, dd);
         return;
     }
     // x <- x + V(v - H x), k times from x = 0
@@ -2024,18 +2075,19 @@ static void vcycle_k(const gl_precond *pre, const double2 *v, double2 *z, const 
         L.run(nb0, L0ResidualFull<DIM>{g, v, z, link_tab<double>(m), pre->L[0].diag64.get(), pre->cyc_r.get(),
                                        gate});
         const bool lastc = (c == k - 1);
-        vcycle_once<DIM, T, TC>(pre, pre->cyc_r.get(), v, z, gate, lastc ? ks : nullptr, mode, 1, L);
+        vcycle_once<DIM, T, TC>(pre, pre->cyc_r.get(), v, z, gate, lastc ? ks : nullptr, mode, 1, L, nullptr,
+                                lastc ? dd : DeflDot{});
     }
 }
 
 void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
-                    KrylovScalars *ks, int mode, const Launch &L, gl_precision p)
+                    KrylovScalars *ks, int mode, const Launch &L, gl_precision p, const DeflDot &dd)
 {
     with_dim(pre->mesh->g, [&](auto D) {
         constexpr int K = decltype(D)::value;
-        if (p == GL_FP32) vcycle_k<K, float, float>(pre, v, z, gate, ks, mode, L);
-        else if (p == GL_MIXED) vcycle_k<K, float, double>(pre, v, z, gate, ks, mode, L);
-        else vcycle_k<K, double, double>(pre, v, z, gate, ks, mode, L);
+        if (p == GL_FP32) vcycle_k<K, float, float>(pre, v, z, gate, ks, mode, L, dd);
+        else if (p == GL_MIXED) vcycle_k<K, float, double>(pre, v, z, gate, ks, mode, L, dd);
+        else vcycle_k<K, double, double>(pre, v, z, gate, ks, mode, L, dd);
     });
 }
 
