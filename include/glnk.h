@@ -268,7 +268,8 @@ void gl_precond_destroy(gl_precond *pre);
  *     times 2^lane_shift, clamped to 1 .. 32; -2 .. 2, default 0;
  *   bottom_rows: levels >= 1 with at most this many rows (and at most 64
  *     colours), and all coarser ones, run inside one work-group; 0 = default
- *     512, at most 65536;
+ *     512, at most 65536 (levels of 2D meshes whose sweeps run on patches, at
+ *     most 24 neighbours per row, take two dispatches each and are not counted);
  *   dense_rows: the first level >= 1 with at most this many rows has the
  *     V-cycle below it (its smoothing sweeps, residual, transfers and every
  *     coarser level: a linear map of its right-hand side) formed as an
@@ -291,8 +292,11 @@ typedef struct {
                            correction, the three passes and the output) on
                            tiles of 32 x 32 (1024 threads), 32 x 16 (512) or
                            16 x 16 nodes (256); 0 (default) one dispatch per
-                           pass; the same operator up to rounding.  3D grids
-                           always use one dispatch per pass */
+                           pass; the same operator up to rounding.  A handle
+                           whose tiles were never changed takes form 2 where
+                           it is the faster one (FP32, and FP64 up to 2^19
+                           nodes).  3D grids always use one dispatch per
+                           pass */
 } gl_tiles;
 
 gl_status gl_precond_set_tiles(gl_precond *pre, const gl_tiles *tiles);

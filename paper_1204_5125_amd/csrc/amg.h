@@ -34,11 +34,11 @@ struct Csr {
 // order; the slots after them hold rows whose starting value is read only.
 constexpr int kPatchRows = 512;    // rows of a patch, a thread each
 constexpr int kPatchSlots = 1024;  // with the read-only ones
-constexpr int kPatchWidth = 16;    // off-diagonal entries of a row at most
+constexpr int kPatchWidth = 24;    // off-diagonal entries of a row at most
 
 struct PatchSet {
     int np = 0;                 // patches (0: the level runs a dispatch per colour pass)
-    int W = 0;                  // entries held per row: 8, 12 or 16
+    int W = 0;                  // entries held per row: 8, 12, 16 or 24
     DevBuf<int> size;           // per patch: rows, slots
     DevBuf<int> rowid;          // [np][kPatchSlots] row of a slot
     DevBuf<int> info;           // [np][kPatchRows] colour (255: no row) | last pass + 1 << 8 | own << 16 | entries << 20
@@ -275,6 +275,7 @@ struct gl_precond {
     int lane_shift = 0;
     int dense_rows = 0;
     int l0_tiled = 0;              // 1: 2D level-0 passes in two LDS-tiled kernels
+    bool l0_auto = true;           // until gl_precond_set_tiles changes the tiles: by size
     bool has_values = false;       // a numeric setup has run
     glk::Level L[glk::kMaxLevels];
     glk::DevBuf<double2> cfac;     // Cholesky factor of the coarsest operator

@@ -1950,7 +1950,7 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     for (int w : L.ewidth) wmax = std::max(wmax, w - 1);
     if (n > kPatchLevel || m->g.dim != 2 || wmax > kPatchWidth || L.ncolors < 2 || L.ncolors > kMaxColors) return;
     PatchSet &S = L.patch;
-    S.W = wmax <= 8 ? 8 : wmax <= 12 ? 12 : 16;
+    S.W = wmax <= 8 ? 8 : wmax <= 12 ? 12 : wmax <= 16 ? 16 : 24;
     TileGrid t{};
     t.simplicial = m->g.simplicial;
     double ext[2];
@@ -2300,6 +2300,7 @@ gl_status gl_precond_set_tiles(gl_precond *pre, const gl_tiles *tiles)
         pre->lane_shift = tiles->lane_shift;
         pre->dense_rows = tiles->dense_rows;
         pre->l0_tiled = tiles->l0_tiled;
+        pre->l0_auto = false;
         pre->uid = new_precond_uid();  // captured graphs of the old shape are stale
         hipStream_t s = pre->mesh->ws;
         GLK_HIP(hipStreamSynchronize(s));  // no pending use of the buffers re-made here

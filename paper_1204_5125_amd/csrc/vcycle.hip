@@ -776,7 +776,7 @@ template <class T, int W>
 struct PatchRow {
     int g, colour, last;
     bool own;
-    int wide;  // entries of the wave's longest row: 8, 12 or 16
+    int wide;  // entries of the wave's longest row: 8, 12, 16 or 24
     T d;
     C<T> b, v[W];
     int idx[W];
@@ -819,6 +819,11 @@ __device__ __forceinline__ PatchRow<T, W> patch_load(const PatchArrays<T, W> &A,
             R.wide = 16;
             part(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
         }
+    if constexpr (W > 16)
+        if (__any(cnt > 16)) {
+            R.wide = W;
+            part(std::integral_constant<int, 16>{}, std::integral_constant<int, W>{});
+        }
     return R;
 }
 
@@ -836,6 +841,8 @@ __device__ __forceinline__ C<T> patch_sum(const PatchRow<T, W> &R, const C<T> *x
         if (R.wide > 8) part(std::integral_constant<int, 8>{}, std::integral_constant<int, 12>{});
     if constexpr (W > 12)
         if (R.wide > 12) part(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
+    if constexpr (W > 16)
+        if (R.wide > 16) part(std::integral_constant<int, 16>{}, std::integral_constant<int, W>{});
     return s;
 }
 
@@ -1556,7 +1563,8 @@ static void with_patch(const Level &Lv, F &&f)
     };
     if (S.W == 8) go(std::integral_constant<int, 8>{});
     else if (S.W == 12) go(std::integral_constant<int, 12>{});
-    else go(std::integral_constant<int, 16>{});
+    else if (S.W == 16) go(std::integral_constant<int, 16>{});
+    else go(std::integral_constant<int, 24>{});
 }
 
 // algorithmic bytes of a sweep: the level's entries, b, the diagonal and x once
@@ -1598,6 +1606,19 @@ static C<T> *cycle_result(gl_precond *pre, int l)
 {
     Level &Lv = pre->L[l];
     return l < pre->bottom && Lv.patch.np ? vec_r<T>(Lv) : vec_x<T>(Lv);
+}
+
+// The form of level 0 of a 2D grid: as gl_precond_set_tiles asked; on a handle
+// whose tiles were never changed, tiles of 32 x 16 as long as the seven
+// dispatches of the per-pass form cost more than the tiles' halo does: in FP32
+// always, in FP64 up to 2^19 nodes.  Microseconds per MINRES iteration, a
+// dispatch per pass / tiles, FP64: 33^2 67 / 59, 129^2 97 / 88, 257^2 107 / 95,
+// 513^2 172 / 169, 769^2 213 / 213, 1025^2 356 / 362; FP32: 33^2 65 / 56, 257^2 101 /
+// 90, 513^2 151 / 138, 1025^2 285 / 282.
+static int l0_form(const gl_precond *pre, bool f32)
+{
+    if (!pre->l0_auto) return pre->l0_tiled;
+    return f32 || pre->L[0].n <= 1 << 19 ? 2 : 0;
 }
 
 // calls f with the tile shape of gl_tiles.l0_tiled (1, 2 or 3)
@@ -1716,7 +1737,7 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
     // black, red, black residual, restriction; in 2D by default the three
     // passes in one LDS-tiled kernel (L0PreTile)
     const int nbp = blocks_for(g.npair);
-    const int tiled = DIM == 2 ? pre->l0_tiled : 0;
+    const int tiled = DIM == 2 ? l0_form(pre, f32) : 0;
     if (tiled) {
         // each array once (the halo's re-reads come from cache)
         const double b_tile = nn * 16 + nn * szr + 2 * nn * sz + mc * sz;
