@@ -32,17 +32,18 @@ struct Csr {
 // rows - 1 of a patch are the rows it updates (the patch itself and the rows
 // whose values the later passes need), in ascending row order, which is colour
 // order; the slots after them hold rows whose starting value is read only.
-constexpr int kPatchRows = 512;    // rows of a patch, a thread each
-constexpr int kPatchSlots = 1024;  // with the read-only ones
+// A patch has at most `rows` of the former (512 or, where the level's colours
+// reach further, 1024: a thread each) and twice as many slots in all.
 constexpr int kPatchWidth = 24;    // off-diagonal entries of a row at most
 
 struct PatchSet {
     int np = 0;                 // patches (0: the level runs a dispatch per colour pass)
+    int rows = 512;
     int W = 0;                  // entries held per row: 8, 12, 16 or 24
     DevBuf<int> size;           // per patch: rows, slots
-    DevBuf<int> rowid;          // [np][kPatchSlots] row of a slot
-    DevBuf<int> info;           // [np][kPatchRows] colour (255: no row) | last pass + 1 << 8 | own << 16 | entries << 20
-    DevBuf<unsigned short> idx; // [np][W][kPatchRows] slot of entry k (kPatchSlots: none)
+    DevBuf<int> rowid;          // [np][2 rows] row of a slot
+    DevBuf<int> info;           // [np][rows] colour (255: no row) | last pass + 1 << 8 | own << 16 | entries << 20
+    DevBuf<unsigned short> idx; // [np][W][rows] slot of entry k (2 rows: none)
     DevBuf<int> map;            // its entry of Aa, -1: none
     DevBuf<double2> v64;        // its value
     DevBuf<float2> v32;

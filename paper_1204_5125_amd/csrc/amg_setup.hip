@@ -1445,25 +1445,26 @@ __global__ void k_tile_fill(int n, const int *tile, const int *rp, int *fill, in
 // colour: a symmetric sweep of 5-8 colours on the 2D hierarchies reaches three
 // or four rows out, not one per pass.)  The residual and the own rows' last
 // pass need the neighbours' final values.  Overflow: err 32.
-__global__ __launch_bounds__(kPatchRows) void k_patch_build(const int *__restrict__ tile_rp,
+template <int NR>
+__global__ __launch_bounds__(NR) void k_patch_build(const int *__restrict__ tile_rp,
                                                             const int *__restrict__ tile_rows,
                                                             const int *__restrict__ rp, const int *__restrict__ ci,
                                                             const int *__restrict__ perm, const int *__restrict__ color,
                                                             int ncol, int W, int *size, int *rowid, int *info,
                                                             unsigned short *idx, int *map, int *total, int *err)
 {
-    constexpr int H = 2 * kPatchSlots;
-    __shared__ int key[H], val[H], row[kPatchSlots], last[kPatchSlots], place[kPatchSlots];
-    __shared__ unsigned char col[kPatchSlots], done[kPatchSlots];
+    constexpr int NS = 2 * NR, H = 2 * NS;
+    __shared__ int key[H], val[H], row[NS], last[NS], place[NS];
+    __shared__ unsigned char col[NS], done[NS];
     __shared__ int cnt, nrows, bad;
     const int p = blockIdx.x, tid = threadIdx.x;
     const int beg = tile_rp[p], end = tile_rp[p + 1];
-    for (int t = tid; t < H; t += kPatchRows) key[t] = -1;
-    for (int t = tid; t < kPatchSlots; t += kPatchRows) {
+    for (int t = tid; t < H; t += NR) key[t] = -1;
+    for (int t = tid; t < NS; t += NR) {
         done[t] = 0;
-        rowid[(size_t)p * kPatchSlots + t] = 0;  // slots without a row read row 0 and write nothing
+        rowid[(size_t)p * NS + t] = 0;  // slots without a row read row 0 and write nothing
     }
-    info[(size_t)p * kPatchRows + tid] = 255;
+    info[(size_t)p * NR + tid] = 255;
     if (tid == 0) cnt = nrows = bad = 0;
     __syncthreads();
     auto insert = [&](int g, int e) {
@@ -1473,7 +1474,7 @@ __global__ __launch_bounds__(kPatchRows) void k_patch_build(const int *__restric
             if (old == g) return;
             if (old != -1) continue;
             const int slot = atomicAdd(&cnt, 1);
-            if (slot >= kPatchSlots) {
+            if (slot >= NS) {
                 bad = 1;
                 return;
             }
@@ -1486,19 +1487,19 @@ __global__ __launch_bounds__(kPatchRows) void k_patch_build(const int *__restric
         bad = 1;
     };
     const int T = 2 * ncol - 1;
-    for (int q = beg + tid; q < end; q += kPatchRows) insert(tile_rows[q], T);
+    for (int q = beg + tid; q < end; q += NR) insert(tile_rows[q], T);
     __syncthreads();
-    for (int q = beg + tid; q < end; q += kPatchRows) {
+    for (int q = beg + tid; q < end; q += NR) {
         const int g = tile_rows[q];
         for (int k = rp[g]; k < rp[g + 1]; ++k) insert(ci[k], T);
     }
     __syncthreads();
     for (int t = T - 1; t >= 0; --t) {
         const int c = t < ncol ? t : 2 * ncol - 2 - t;
-        const int n0 = min(cnt, kPatchSlots), over = bad;
+        const int n0 = min(cnt, NS), over = bad;
         __syncthreads();
         if (over) break;
-        for (int s = tid; s < n0; s += kPatchRows)
+        for (int s = tid; s < n0; s += NR)
             if (col[s] == c && last[s] > t && !done[s]) {
                 done[s] = 1;
                 const int g = row[s];
@@ -1507,22 +1508,22 @@ __global__ __launch_bounds__(kPatchRows) void k_patch_build(const int *__restric
         __syncthreads();
     }
     __syncthreads();
-    const int n = min(cnt, kPatchSlots);
+    const int n = min(cnt, NS);
     if (!bad)
-        for (int s = tid; s < n; s += kPatchRows)
+        for (int s = tid; s < n; s += NR)
             if (done[s]) atomicAdd(&nrows, 1);
     __syncthreads();
     const int nr = nrows;
-    if (bad || nr > kPatchRows) {
+    if (bad || nr > NR) {
         if (tid == 0) atomicOr(err, 32);
         return;
     }
     // the places: updated rows first, then the others, each in row order
-    for (int s = tid; s < n; s += kPatchRows) {
+    for (int s = tid; s < n; s += NR) {
         int rank = done[s] ? 0 : nr;
         for (int q = 0; q < n; ++q) rank += done[q] == done[s] && row[q] < row[s];
         place[s] = rank;
-        rowid[(size_t)p * kPatchSlots + rank] = row[s];
+        rowid[(size_t)p * NS + rank] = row[s];
     }
     if (tid == 0) {
         size[2 * p] = nr;
@@ -1530,13 +1531,13 @@ __global__ __launch_bounds__(kPatchRows) void k_patch_build(const int *__restric
         atomicAdd(total, nr);
     }
     __syncthreads();
-    const size_t base = (size_t)p * W * kPatchRows;
-    for (int t = tid; t < W * kPatchRows; t += kPatchRows) {
-        idx[base + t] = kPatchSlots;
+    const size_t base = (size_t)p * W * NR;
+    for (int t = tid; t < W * NR; t += NR) {
+        idx[base + t] = NS;
         map[base + t] = -1;
     }
     __syncthreads();
-    for (int s = tid; s < n; s += kPatchRows) {
+    for (int s = tid; s < n; s += NR) {
         if (!done[s]) continue;
         const int g = row[s], r = place[s];
         int own = 0;
@@ -1547,11 +1548,11 @@ __global__ __launch_bounds__(kPatchRows) void k_patch_build(const int *__restric
             if (j == g) continue;
             unsigned h = ((unsigned)j * 2654435761u) % H;
             for (int tries = 0; tries < H && key[h] != j; ++tries) h = (h + 1) % H;
-            idx[base + (size_t)k * kPatchRows + r] = (unsigned short)place[val[h]];
-            map[base + (size_t)k * kPatchRows + r] = q;
+            idx[base + (size_t)k * NR + r] = (unsigned short)place[val[h]];
+            map[base + (size_t)k * NR + r] = q;
             ++k;
         }
-        info[(size_t)p * kPatchRows + r] = col[s] | last[s] << 8 | own << 16 | k << 20;
+        info[(size_t)p * NR + r] = col[s] | last[s] << 8 | own << 16 | k << 20;
     }
 }
 
@@ -1935,8 +1936,8 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
 // `own` rows by the rows' places in the plane.  A level keeps its dispatch per
 // colour pass where patches do not pay or do not fit: rows of more than
 // kPatchWidth neighbours (the 3D hierarchies: 30 entries and 15-30 colours reach
-// over the whole level), a patch of more than kPatchRows rows, or more than
-// kPatchMost updated rows per row of the level.  (Measured on the 2D levels:
+// over the whole level), a patch of more than 1024 rows, or more than kPatchMost
+// updated rows per row of the level.  (Measured on the 2D levels:
 // 3-5 with 96 rows of a patch's own.)
 constexpr double kPatchMost = 8.0;
 constexpr int kPatchLevel = 1 << 20;  // rows of a level in patches at most
@@ -1950,7 +1951,6 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     for (int w : L.ewidth) wmax = std::max(wmax, w - 1);
     if (n > kPatchLevel || m->g.dim != 2 || wmax > kPatchWidth || L.ncolors < 2 || L.ncolors > kMaxColors) return;
     PatchSet &S = L.patch;
-    S.W = wmax <= 8 ? 8 : wmax <= 12 ? 12 : wmax <= 16 ? 16 : 24;
     TileGrid t{};
     t.simplicial = m->g.simplicial;
     double ext[2];
@@ -1967,7 +1967,14 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         ext[0] = t.N0;
         ext[1] = t.N1;
     }
-    for (int own : {96, 64, 40}) {
+    // (rows of a patch, of these its own): smaller patches where 512 rows do not
+    // hold a patch's reach, then 1024 rows (513^2 FP64, its level of 4 923 rows:
+    // 169 us per MINRES iteration with 64 rows of 512, 175 with 112 of 1024;
+    // 769^2 FP32, its level of 1 121 rows: 288 without patches, 238 with 1024)
+    const int tries[4][2] = {{512, 96}, {512, 64}, {1024, 112}, {1024, 64}};
+    for (const auto &[NR, own] : tries) {
+        S.rows = NR;
+        S.W = NR == 512 && wmax <= 8 ? 8 : NR == 512 && wmax <= 12 ? 12 : wmax <= 16 ? 16 : 24;
         const double tiles = std::max(1.0, (double)n / own);
         t.k[0] = (int)std::max(1.0, std::min(tiles, std::round(std::sqrt(tiles * ext[0] / std::max(ext[1], 1e-300)))));
         t.k[1] = std::max(1, (int)std::round(tiles / t.k[0]));
@@ -1984,21 +1991,25 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         k_tile_fill<<<nb, kBlock, 0, s>>>(n, tile, trp, cnt, rows);
         k_sort_rows<<<(nt + kRowWaves - 1) / kRowWaves, kBlock, 0, s>>>(nt, trp, rows, rows, srt, srt + n);
         S.size.alloc(2 * (size_t)nt + 1);
-        S.rowid.alloc((size_t)nt * kPatchSlots);
-        S.info.alloc((size_t)nt * kPatchRows);
-        S.idx.alloc((size_t)nt * S.W * kPatchRows);
-        S.map.alloc((size_t)nt * S.W * kPatchRows);
+        S.rowid.alloc((size_t)nt * 2 * NR);
+        S.info.alloc((size_t)nt * NR);
+        S.idx.alloc((size_t)nt * S.W * NR);
+        S.map.alloc((size_t)nt * S.W * NR);
         int *total = S.size.get() + 2 * (size_t)nt;
         k_fill_int<<<1, 64, 0, s>>>(total, 1, 0);
-        k_patch_build<<<nt, kPatchRows, 0, s>>>(trp, srt, L.Aa.rp.get(), L.Aa.ci.get(), L.perm.get(), L.color.get(),
-                                                L.ncolors, S.W, S.size.get(), S.rowid.get(), S.info.get(), S.idx.get(),
-                                                S.map.get(), total, err);
+        auto build = [&](auto kern) {
+            kern<<<nt, S.rows, 0, s>>>(trp, srt, L.Aa.rp.get(), L.Aa.ci.get(), L.perm.get(), L.color.get(), L.ncolors,
+                                       S.W, S.size.get(), S.rowid.get(), S.info.get(), S.idx.get(), S.map.get(), total,
+                                       err);
+        };
+        if (NR == 512) build(k_patch_build<512>);
+        else build(k_patch_build<1024>);
         GLK_CHECK_LAUNCH();
         const bool fits = read_int(err, s) == 0;
         if (fits && read_int(total, s) <= kPatchMost * n) {
             S.np = nt;
-            S.v64.alloc((size_t)nt * S.W * kPatchRows);
-            S.v32.alloc((size_t)nt * S.W * kPatchRows);
+            S.v64.alloc((size_t)nt * S.W * NR);
+            S.v32.alloc((size_t)nt * S.W * NR);
             int *row0 = need(T.a, 2), *wid = need(T.b, 1);
             to_device(row0, std::vector<int>{0, n}, s);
             k_row_widths<<<1, kBlock, 0, s>>>(L.Pa.rp.get(), row0, wid);
@@ -2072,7 +2083,7 @@ void patch_values_enqueue(gl_precond *pre, const Launch &L)
     for (int l = 0; l < pre->bottom; ++l) {
         Level &lv = pre->L[l];
         if (lv.patch.np == 0) continue;
-        const int ne = lv.patch.np * lv.patch.W * kPatchRows;
+        const int ne = lv.patch.np * lv.patch.W * lv.patch.rows;
         L.run(blocks_for(ne), EllValues{ne, lv.patch.map.get(), lv.Aa.v64.get(), lv.patch.v64.get(), lv.patch.v32.get()});
         const int nq = lv.n * lv.patch.PW;
         L.run(blocks_for(nq), EllValues{nq, lv.patch.pmap.get(), lv.Pa.v64.get(), lv.patch.pv64.get(), lv.patch.pv32.get()});

@@ -763,42 +763,50 @@ struct CsrSpmv {
 // the patch is read, never written, and the sweep's result goes to another
 // vector (r, whose content is used up by then), so patches do not disturb one
 // another.
-template <class T, int W>
+template <class T, int W, int NR>
 struct PatchArrays {
     const int *size, *rowid, *info;
     const unsigned short *idx;
     const C<T> *v;
     const T *diag;
     int ncol;
+    int planes;  // entries per row in the arrays, W of them held in registers
 };
 
-template <class T, int W>
+template <class T, int W, int NR>
 struct PatchRow {
-    int g, colour, last;
+    int g, colour, last, cnt;
     bool own;
-    int wide;  // entries of the wave's longest row: 8, 12, 16 or 24
+    int wide;  // entries of the wave's longest row: 8, 12, 16, or more than W
     T d;
     C<T> b, v[W];
-    int idx[W];
+    unsigned idx[W / 2];  // two slots each
+    const C<T> *vg;
+    const unsigned short *ig;
 };
 
 // Every load that depends on no other first, then those through the row's
 // index.  Most waves have no row of more than eight neighbours (the interior of
 // the 2D hierarchies): the entries after the eighth are read, and summed, by the
-// others only.
-template <class T, int W>
-__device__ __forceinline__ PatchRow<T, W> patch_load(const PatchArrays<T, W> &A, int p, const C<T> *b)
+// others only.  The few rows with more than 16 read the rest in every pass
+// (24 held entries leave one work-group per CU, and spill with 1024 rows: 66 us
+// instead of 25 for 1 121 rows in FP64).
+template <class T, int W, int NR>
+__device__ __forceinline__ PatchRow<T, W, NR> patch_load(const PatchArrays<T, W, NR> &A, int p, const C<T> *b)
 {
-    PatchRow<T, W> R;
+    PatchRow<T, W, NR> R;
     const int i = threadIdx.x;
-    const size_t base = (size_t)p * W * kPatchRows + i;
-    R.g = A.rowid[(size_t)p * kPatchSlots + i];
-    const int inf = A.info[(size_t)p * kPatchRows + i];
+    const size_t base = (size_t)p * A.planes * NR + i;
+    R.vg = A.v + base;
+    R.ig = A.idx + base;
+    R.g = A.rowid[(size_t)p * 2 * NR + i];
+    const int inf = A.info[(size_t)p * NR + i];
     auto part = [&](auto k0, auto k1) {
 #pragma unroll
         for (int k = decltype(k0)::value; k < decltype(k1)::value; ++k) {
-            R.v[k] = A.v[base + (size_t)k * kPatchRows];
-            R.idx[k] = A.idx[base + (size_t)k * kPatchRows];
+            R.v[k] = R.vg[(size_t)k * NR];
+            const unsigned at = R.ig[(size_t)k * NR];
+            R.idx[k / 2] = k & 1 ? R.idx[k / 2] | at << 16 : at;
         }
     };
     part(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
@@ -807,83 +815,80 @@ __device__ __forceinline__ PatchRow<T, W> patch_load(const PatchArrays<T, W> &A,
     R.colour = inf & 255;
     R.last = (inf >> 8) & 255;
     R.own = (inf >> 16 & 1) != 0;
-    const int cnt = inf >> 20;
+    R.cnt = inf >> 20;
     R.wide = 8;
     if constexpr (W > 8)
-        if (__any(cnt > 8)) {
+        if (__any(R.cnt > 8)) {
             R.wide = 12;
             part(std::integral_constant<int, 8>{}, std::integral_constant<int, 12>{});
         }
     if constexpr (W > 12)
-        if (__any(cnt > 12)) {
-            R.wide = 16;
+        if (__any(R.cnt > 12)) {
+            R.wide = __any(R.cnt > 16) ? W + 1 : 16;
             part(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
-        }
-    if constexpr (W > 16)
-        if (__any(cnt > 16)) {
-            R.wide = W;
-            part(std::integral_constant<int, 16>{}, std::integral_constant<int, W>{});
         }
     return R;
 }
 
 // sum of the row's products
-template <class T, int W>
-__device__ __forceinline__ C<T> patch_sum(const PatchRow<T, W> &R, const C<T> *xs)
+template <class T, int W, int NR>
+__device__ __forceinline__ C<T> patch_sum(const PatchRow<T, W, NR> &R, const C<T> *xs)
 {
     C<T> s = mk<T>(0, 0);
     auto part = [&](auto k0, auto k1) {
 #pragma unroll
-        for (int k = decltype(k0)::value; k < decltype(k1)::value; ++k) s = cadd(s, cmul(R.v[k], xs[R.idx[k]]));
+        for (int k = decltype(k0)::value; k < decltype(k1)::value; ++k)
+            s = cadd(s, cmul(R.v[k], xs[k & 1 ? R.idx[k / 2] >> 16 : R.idx[k / 2] & 0xFFFFu]));
     };
     part(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
     if constexpr (W > 8)
         if (R.wide > 8) part(std::integral_constant<int, 8>{}, std::integral_constant<int, 12>{});
-    if constexpr (W > 12)
+    if constexpr (W > 12) {
         if (R.wide > 12) part(std::integral_constant<int, 12>{}, std::integral_constant<int, 16>{});
-    if constexpr (W > 16)
-        if (R.wide > 16) part(std::integral_constant<int, 16>{}, std::integral_constant<int, W>{});
+        if (R.wide > W)
+            for (int k = W; k < R.cnt; ++k) s = cadd(s, cmul(R.vg[(size_t)k * NR], xs[R.ig[(size_t)k * NR]]));
+    }
     return s;
 }
 
-template <class T, int W>
-__device__ __forceinline__ void patch_sweep(const PatchRow<T, W> &R, int ncol, C<T> *xs)
+template <class T, int W, int NR>
+__device__ __forceinline__ void patch_sweep(const PatchRow<T, W, NR> &R, int ncol, C<T> *xs)
 {
     const T inv = (T)1 / R.d;
     for (int t = 0; t < 2 * ncol - 1; ++t) {
         const int c = t < ncol ? t : 2 * ncol - 2 - t;
-        if (R.colour == c && t < R.last) xs[threadIdx.x] = cscale(csub(R.b, patch_sum<T, W>(R, xs)), inv);
+        if (R.colour == c && t < R.last) xs[threadIdx.x] = cscale(csub(R.b, patch_sum<T, W, NR>(R, xs)), inv);
         __syncthreads();
     }
 }
 
 // x = the sweep from zero, r = b - A x, on the patch's own rows
-template <class T, int W>
+template <class T, int W, int NR>
 struct PatchPre {
-    PatchArrays<T, W> A;
+    PatchArrays<T, W, NR> A;
     const C<T> *b;
     C<T> *x, *r;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
         GATE_LOAD();
-        __shared__ C<T> xs[kPatchSlots + 1];
-        const PatchRow<T, W> R = patch_load<T, W>(A, bx, b);
-        for (int q = threadIdx.x; q <= kPatchSlots; q += kPatchRows) xs[q] = mk<T>(0, 0);
+        __shared__ C<T> xs[2 * NR + 1];
+        const PatchRow<T, W, NR> R = patch_load<T, W, NR>(A, bx, b);
+        for (int q = threadIdx.x; q <= 2 * NR; q += NR) xs[q] = mk<T>(0, 0);
         __syncthreads();
-        patch_sweep<T, W>(R, A.ncol, xs);
+        patch_sweep<T, W, NR>(R, A.ncol, xs);
         if (!R.own || !gate_go) return;
         const C<T> xi = xs[threadIdx.x];
         x[R.g] = xi;
-        r[R.g] = csub(csub(R.b, cscale(xi, R.d)), patch_sum<T, W>(R, xs));
+        r[R.g] = csub(csub(R.b, cscale(xi, R.d)), patch_sum<T, W, NR>(R, xs));
     }
 };
 
 // xo = the sweep from x + P x_c on the patch's own rows (TX: the precision of
 // x_c; P's rows padded to PW entries)
-template <class T, class TX, int W>
+template <class T, class TX, int W, int NR>
 struct PatchPost {
-    PatchArrays<T, W> A;
+    PatchArrays<T, W, NR> A;
     const C<T> *b, *x;
     int PW;
     const int *pci;
@@ -913,20 +918,18 @@ struct PatchPost {
     __device__ void operator()(int bx, int) const
     {
         GATE_LOAD();
-        __shared__ C<T> xs[kPatchSlots + 1];
+        __shared__ C<T> xs[2 * NR + 1];
         const int ns = A.size[2 * bx + 1];
-        const int g1 = A.rowid[(size_t)bx * kPatchSlots + kPatchRows + threadIdx.x];
-        const PatchRow<T, W> R = patch_load<T, W>(A, bx, b);
+        const int g1 = A.rowid[(size_t)bx * 2 * NR + NR + threadIdx.x];
+        const PatchRow<T, W, NR> R = patch_load<T, W, NR>(A, bx, b);
         xs[threadIdx.x] = start(R.g);
-        if (kPatchRows + (int)threadIdx.x < ns) xs[kPatchRows + threadIdx.x] = start(g1);
-        if (threadIdx.x == 0) xs[kPatchSlots] = mk<T>(0, 0);
+        if (NR + (int)threadIdx.x < ns) xs[NR + threadIdx.x] = start(g1);
+        if (threadIdx.x == 0) xs[2 * NR] = mk<T>(0, 0);
         __syncthreads();
-        patch_sweep<T, W>(R, A.ncol, xs);
+        patch_sweep<T, W, NR>(R, A.ncol, xs);
         if (R.own && gate_go) xo[R.g] = xs[threadIdx.x];
     }
 };
-static_assert(kPatchSlots == 2 * kPatchRows, "a thread starts two slots");
-
 template <class T>
 struct FillZero {
     int n;
@@ -1551,20 +1554,26 @@ template <class T> static const C<T> *ppvals(const PatchSet &S);
 template <> const double2 *ppvals<double>(const PatchSet &S) { return S.pv64.get(); }
 template <> const float2 *ppvals<float>(const PatchSet &S) { return S.pv32.get(); }
 
-// calls f with the patch arrays of the level's row width
+// calls f with the patch arrays of the level's row width and patch size
 template <class T, class F>
 static void with_patch(const Level &Lv, F &&f)
 {
     const PatchSet &S = Lv.patch;
-    auto go = [&](auto w) {
-        constexpr int W = decltype(w)::value;
-        f(PatchArrays<T, W>{S.size.get(), S.rowid.get(), S.info.get(), S.idx.get(), pvals<T>(S), dgn<T>(Lv), Lv.ncolors},
-          w);
+    auto go = [&](auto w, auto nr) {
+        constexpr int W = decltype(w)::value, NR = decltype(nr)::value;
+        f(PatchArrays<T, W, NR>{S.size.get(), S.rowid.get(), S.info.get(), S.idx.get(), pvals<T>(S), dgn<T>(Lv),
+                                Lv.ncolors, S.W},
+          w, nr);
     };
-    if (S.W == 8) go(std::integral_constant<int, 8>{});
-    else if (S.W == 12) go(std::integral_constant<int, 12>{});
-    else if (S.W == 16) go(std::integral_constant<int, 16>{});
-    else go(std::integral_constant<int, 24>{});
+    using std::integral_constant;
+    if (S.rows == 512) {
+        constexpr integral_constant<int, 512> nr{};
+        if (S.W == 8) go(integral_constant<int, 8>{}, nr);
+        else if (S.W == 12) go(integral_constant<int, 12>{}, nr);
+        else go(integral_constant<int, 16>{}, nr);
+    } else {
+        go(integral_constant<int, 16>{}, integral_constant<int, 1024>{});
+    }
 }
 
 // algorithmic bytes of a sweep: the level's entries, b, the diagonal and x once
@@ -1578,10 +1587,10 @@ template <class T>
 static void patch_pre(Level &Lv, const int *gate, const Launch &L)
 {
     prof_launch(PROF_COARSE_SWEEP, patch_bytes<T>(Lv), L, [&] {
-        with_patch<T>(Lv, [&](auto A, auto w) {
-            constexpr int W = decltype(w)::value;
-            L.run<PatchPre<T, W>, kPatchRows>(Lv.patch.np,
-                                              PatchPre<T, W>{A, vec_b<T>(Lv), vec_x<T>(Lv), vec_r<T>(Lv), gate});
+        with_patch<T>(Lv, [&](auto A, auto w, auto nr) {
+            constexpr int W = decltype(w)::value, NR = decltype(nr)::value;
+            L.run<PatchPre<T, W, NR>, NR>(Lv.patch.np,
+                                          PatchPre<T, W, NR>{A, vec_b<T>(Lv), vec_x<T>(Lv), vec_r<T>(Lv), gate});
         });
     });
 }
@@ -1591,10 +1600,10 @@ template <class T, class TX = T>
 static void patch_post(Level &Lv, const C<TX> *xc, const int *gate, const Launch &L)
 {
     prof_launch(PROF_COARSE_SWEEP, patch_bytes<T>(Lv), L, [&] {
-        with_patch<T>(Lv, [&](auto A, auto w) {
-            constexpr int W = decltype(w)::value;
-            L.run<PatchPost<T, TX, W>, kPatchRows>(
-                Lv.patch.np, PatchPost<T, TX, W>{A, vec_b<T>(Lv), vec_x<T>(Lv), Lv.patch.PW, Lv.patch.pci.get(),
+        with_patch<T>(Lv, [&](auto A, auto w, auto nr) {
+            constexpr int W = decltype(w)::value, NR = decltype(nr)::value;
+            L.run<PatchPost<T, TX, W, NR>, NR>(
+                Lv.patch.np, PatchPost<T, TX, W, NR>{A, vec_b<T>(Lv), vec_x<T>(Lv), Lv.patch.PW, Lv.patch.pci.get(),
                                                  ppvals<T>(Lv.patch), xc, vec_r<T>(Lv), gate});
         });
     });
