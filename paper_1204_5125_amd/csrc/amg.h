@@ -272,11 +272,16 @@ struct gl_precond {
     int nlev = 0;
     int bottom = 0;                // first level handled by the bottom kernel
     int tail = 0;                  // level whose sub-cycle is one dense product (the coarsest if none)
+    // Solves on a handle whose tiles were never changed apply the sub-cycle of
+    // level stail (0: none) as an explicit matrix, formed by the first solve
+    // after a numeric setup (solver_tail_enqueue)
+    int stail = 0;
+    bool stail_current = false;
     int bottom_rows = glk::kBottomRows;  // tile choices (gl_precond_set_tiles)
     int lane_shift = 0;
     int dense_rows = 0;
     int l0_tiled = 0;              // 1: 2D level-0 passes in two LDS-tiled kernels
-    bool l0_auto = true;           // until gl_precond_set_tiles changes the tiles: by size
+    bool auto_tiles = true;        // gl_precond_set_tiles has not changed them: chosen by size
     bool has_values = false;       // a numeric setup has run
     glk::Level L[glk::kMaxLevels];
     glk::DevBuf<double2> cfac;     // Cholesky factor of the coarsest operator
@@ -336,9 +341,10 @@ struct DeflDot {
 // kernel that writes z also reduces Re<v, z> and the total is handed to
 // minres_finalize(ks, mode, total); with dd.psi set also <u, z>_R, handed on as
 // FIN_DEFL_Y after it.
-// prec: the precision of this application (the handle holds both).
+// prec: the precision of this application (the handle holds both); solver: one
+// of the many of a solve (see gl_precond::stail).
 void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
-                    KrylovScalars *ks, int mode, const Launch &L, gl_precision prec, const DeflDot &dd = DeflDot{});
+                    KrylovScalars *ks, int mode, const Launch &L, gl_precision prec, const DeflDot &dd, bool solver);
 void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
                     KrylovScalars *ks, int mode, const Launch &L);  // in the handle's precision
 DeflDot defl_dot(const gl_mesh *m, const double2 *psi);
@@ -364,5 +370,6 @@ constexpr int kPcgMaxSteps = 64;
 void scale_by_volume(const gl_mesh *m, const double2 *x, double2 *y, hipStream_t s);
 void bottom_descriptors(gl_precond *pre, hipStream_t s);
 void form_tail(gl_precond *pre, hipStream_t s);  // after a numeric setup
+void solver_tail_enqueue(const gl_precond *pre, const Launch &L);  // at the start of a solve
 uint64_t new_precond_uid();
 }  // namespace glk

@@ -2080,7 +2080,7 @@ void precond_symbolic(gl_precond *pre, hipStream_t s)
 // kernel and the dense operator.
 void patch_values_enqueue(gl_precond *pre, const Launch &L)
 {
-    for (int l = 0; l < pre->bottom; ++l) {
+    for (int l = 0; l < std::max(pre->bottom, pre->stail); ++l) {
         Level &lv = pre->L[l];
         if (lv.patch.np == 0) continue;
         const int ne = lv.patch.np * lv.patch.W * lv.patch.rows;
@@ -2097,6 +2097,7 @@ void precond_numeric_enqueue(gl_precond *pre, const double2 *psi, const Launch &
     const int n0 = L0.n;
     const GeomT<double> g = geom_t<double>(m->g);
     const bool simp = m->g.simplicial;
+    pre->stail_current = false;
     if (simp)
         L.run(blocks_for(n0), L0sValues{g, L0.A.rp.get(), L0.A.ci.get(), psi, L0.A.v64.get(), L0.diag64.get()});
     else if (m->g.dim == 2)
@@ -2311,7 +2312,7 @@ gl_status gl_precond_set_tiles(gl_precond *pre, const gl_tiles *tiles)
         pre->lane_shift = tiles->lane_shift;
         pre->dense_rows = tiles->dense_rows;
         pre->l0_tiled = tiles->l0_tiled;
-        pre->l0_auto = false;
+        pre->auto_tiles = false;
         pre->uid = new_precond_uid();  // captured graphs of the old shape are stale
         hipStream_t s = pre->mesh->ws;
         GLK_HIP(hipStreamSynchronize(s));  // no pending use of the buffers re-made here

@@ -922,6 +922,7 @@ static void ksolve_init(const Ksolve &k, double rtol, int max_iter, const Launch
     const int n = m->g.n, nb = blocks_for(n);
     const GeomT<double> g = geom_t<double>(m->g);
     KrylovScalars *ks = reinterpret_cast<KrylovScalars *>(m->kscal.get());
+    if (k.pre) solver_tail_enqueue(k.pre, L);
     L.run<KsInit, 64>(1, KsInit{ks, rtol, max_iter});
     if (k.defl) {
         L.run(nb, DeflInit<DIM>{g, k.psi, k.rhs, red_slot(m, 2), red_slot(m, 3)});
@@ -933,7 +934,7 @@ static void ksolve_init(const Ksolve &k, double rtol, int max_iter, const Launch
     }
     if (k.pre) {
         vcycle_enqueue(k.pre, k.v, k.z, nullptr, ks, FIN_MINRES_INIT, L, k.prec,
-                       k.defl ? defl_dot(m, k.psi) : DeflDot{});
+                       k.defl ? defl_dot(m, k.psi) : DeflDot{}, true);
     } else {
         L.run(nb, Unprec<DIM>{g, k.v, k.z, nullptr, red_slot(m, 1)});
         launch_finalize(red_slot(m, 1).partials, nb, FIN_MINRES_INIT, ks, nullptr, nullptr, L);
@@ -985,7 +986,7 @@ static void enqueue_iteration(Ksolve &k, const Launch &L)
         }
     }
     if (k.pre) {
-        vcycle_enqueue(k.pre, k.vp, k.zn, gate, ks, fin, L, k.prec, k.defl ? defl_dot(m, k.psi) : DeflDot{});
+        vcycle_enqueue(k.pre, k.vp, k.zn, gate, ks, fin, L, k.prec, k.defl ? defl_dot(m, k.psi) : DeflDot{}, true);
     } else {
         L.run(nb, Unprec<DIM>{g, k.vp, k.zn, gate, red_slot(m, 1)});
         launch_finalize(red_slot(m, 1).partials, nb, fin, ks, nullptr, gate, L);

@@ -1229,7 +1229,7 @@ struct Bottom {
 // kTailUnroll, every gather of a group issued before any is used, and sums
 // them in order.  A null right-hand side stands for columns bid .. bid +
 // kTailBlock - 1 of the identity.
-constexpr int kTailBlock = 16;
+constexpr int kTailBlock = 8;
 constexpr int kTailRows = kBottomThreads / kTailBlock;  // rows per round
 constexpr int kTailUnroll = 8;
 
@@ -1626,7 +1626,7 @@ static C<T> *cycle_result(gl_precond *pre, int l)
 // 90, 513^2 151 / 138, 1025^2 285 / 282.
 static int l0_form(const gl_precond *pre, bool f32)
 {
-    if (!pre->l0_auto) return pre->l0_tiled;
+    if (!pre->auto_tiles) return pre->l0_tiled;
     return f32 || pre->L[0].n <= 1 << 19 ? 2 : 0;
 }
 
@@ -2110,9 +2110,26 @@ static void vcycle_k(const gl_precond *pre, const double2 *v, double2 *z, const 
     }
 }
 
+// The split of the levels while a solve's V-cycles are enqueued
+struct SolverSplit {
+    gl_precond *p;
+    const int bottom, tail;
+    SolverSplit(const gl_precond *pre, bool solver)
+        : p(const_cast<gl_precond *>(pre)), bottom(pre->bottom), tail(pre->tail)
+    {
+        if (solver && pre->stail) p->bottom = p->tail = pre->stail;
+    }
+    ~SolverSplit()
+    {
+        p->bottom = bottom;
+        p->tail = tail;
+    }
+};
+
 void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
-                    KrylovScalars *ks, int mode, const Launch &L, gl_precision p, const DeflDot &dd)
+                    KrylovScalars *ks, int mode, const Launch &L, gl_precision p, const DeflDot &dd, bool solver)
 {
+    const SolverSplit split(pre, solver);
     with_dim(pre->mesh->g, [&](auto D) {
         constexpr int K = decltype(D)::value;
         if (p == GL_FP32) vcycle_k<K, float, float>(pre, v, z, gate, ks, mode, L, dd);
@@ -2124,7 +2141,41 @@ void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const i
 void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const int *gate,
                     KrylovScalars *ks, int mode, const Launch &L)
 {
-    vcycle_enqueue(pre, v, z, gate, ks, mode, L, pre->opts.precision);
+    vcycle_enqueue(pre, v, z, gate, ks, mode, L, pre->opts.precision, DeflDot{}, false);
+}
+
+// The level whose sub-cycle a solve applies as an explicit matrix when the
+// tiles were never changed (0: none): the one that saves most over
+// kSolverCycles V-cycles, its formation counted.  Microseconds, from
+// measurements: a level in patches 30, else 3.2 per dispatch of its 4 C, or 1.4
+// per step inside the bottom kernel; a dense product 4 and its bytes at 4 TB/s;
+// the formation 3 per step of the cycle, and its gathers, about 85 bytes per
+// column and stored entry, at 7 TB/s (545 rows: 0.17 ms for 29 us a cycle; 195
+// rows: 0.04 for 16; 5 592 rows of 31 colours: 22 ms for 270 us, not taken).
+constexpr int kSolverCycles = 24, kSolverTail = 2048;
+
+static int solver_tail(const gl_precond *pre)
+{
+    const int last = pre->nlev - 1;
+    if (!pre->auto_tiles || pre->tail < last) return 0;
+    int best = 0;
+    double best_gain = 0.0;
+    double saved = 4.0, steps = 3.0, nnz = (double)pre->L[last].n * pre->L[last].n;
+    for (int l = last - 1; l >= 1; --l) {
+        const Level &L = pre->L[l];
+        if (L.n > kSolverTail || L.ncolors > kMaxColors) break;
+        saved += l >= pre->bottom ? 1.4 * (4 * L.ncolors + 1) : L.patch.np ? 30.0 : 3.2 * 4 * L.ncolors;
+        steps += 4 * L.ncolors + 3;
+        nnz += L.A.nnz;
+        const double dense = 4.0 + 16.0 * L.n * (double)L.n / 4e6;
+        const double form = 3.0 * steps + 85.0 * L.n * nnz / 7e6;
+        const double gain = kSolverCycles * (saved - dense) - form;
+        if (gain > best_gain) {
+            best = l;
+            best_gain = gain;
+        }
+    }
+    return best;
 }
 
 // Device descriptors of the bottom levels (pointers fixed after setup).
@@ -2209,23 +2260,25 @@ void bottom_descriptors(gl_precond *pre, hipStream_t s)
     // with its transfers and the dense product; 49 us in the bottom kernel)
     while (first < tail && pre->L[first].patch.np) ++first;
     pre->bottom = first;
-    if (tail < last) {
-        const int nt = pre->L[tail].n;
+    pre->stail = solver_tail(pre);
+    pre->stail_current = false;
+    if (const int ex = tail < last ? tail : pre->stail) {  // the level with an explicit sub-cycle
+        const int nt = pre->L[ex].n;
         pre->tinv64.alloc((size_t)nt * nt);
         pre->tinv32.alloc((size_t)nt * nt);
         size_t col = 0;
-        for (int l = tail; l <= last; ++l) col += 3 * (size_t)pre->L[l].n;
+        for (int l = ex; l <= last; ++l) col += 3 * (size_t)pre->L[l].n;
         pre->tws_col = col * kTailBlock;  // elements per block of columns
         const int nblk = (nt + kTailBlock - 1) / kTailBlock;
         const size_t fit = kTailWorkspace / (pre->tws_col * sizeof(double2));
         pre->tws_cols = (int)std::max<size_t>(1, std::min<size_t>(nblk, fit));  // blocks per launch
         pre->tws.alloc(pre->tws_col * pre->tws_cols);
-        // formation: levels tail .. coarsest with the coarsest inverse
+        // formation: levels ex .. coarsest with the coarsest inverse
         BottomDesc<double> dt;
         const int keep = pre->tail;
         pre->tail = last;
         const int keep_b = pre->bottom;
-        pre->bottom = tail;
+        pre->bottom = ex;
         fill_bottom<double>(pre, dt);
         pre->tail = keep;
         pre->bottom = keep_b;
@@ -2256,12 +2309,10 @@ void bottom_descriptors(gl_precond *pre, hipStream_t s)
 // The explicit sub-cycle of level `tail` from the current values: FP64
 // columns, kTailBlock per work-group and as many work-groups per launch as
 // the workspace holds, then the FP32 copy.
-void form_tail(gl_precond *pre, hipStream_t s)
+static void tail_columns(gl_precond *pre, int ex, const Launch &L)
 {
-    if (!pre->has_values || pre->tail >= pre->nlev - 1) return;
-    const int nt = pre->L[pre->tail].n;
+    const int nt = pre->L[ex].n;
     const auto *D = reinterpret_cast<const BottomDesc<double> *>(pre->tdesc64.get());
-    const Launch L{s};
     const int nblk = (nt + kTailBlock - 1) / kTailBlock;
     for (int b0 = 0; b0 < nblk; b0 += pre->tws_cols) {
         const int nb = std::min(pre->tws_cols, nblk - b0);
@@ -2270,6 +2321,19 @@ void form_tail(gl_precond *pre, hipStream_t s)
     }
     const int64_t nn = (int64_t)nt * nt;
     L.run(blocks_for(nn), Narrow<float>{(int)nn, pre->tinv64.get(), pre->tinv32.get(), nullptr});
+}
+
+void form_tail(gl_precond *pre, hipStream_t s)
+{
+    if (pre->has_values && pre->tail < pre->nlev - 1) tail_columns(pre, pre->tail, Launch{s});
+}
+
+void solver_tail_enqueue(const gl_precond *cpre, const Launch &L)
+{
+    gl_precond *pre = const_cast<gl_precond *>(cpre);
+    if (!pre->stail || pre->stail_current) return;
+    tail_columns(pre, pre->stail, L);
+    pre->stail_current = true;
 }
 
 }  // namespace glk

@@ -93,3 +93,26 @@ def test_splits_on_one_handle(glnk):
         glnk.gl_precond_set_tiles(pre, *tiles)
         z = vcycle(pre, r, mo.n)
         assert np.abs(z - want).max() <= 1e-11 * np.abs(want).max(), tiles
+
+
+@pytest.mark.parametrize("name", ["ragged", "disc"])
+def test_solves_follow_the_values(glnk, name):
+    """The explicit sub-cycle that solves use belongs to the values of the last
+    setup: after an update, with applications in between and across precisions,
+    a kept handle solves as a fresh one does."""
+    mg, mo = pair(glnk, name)
+    b = torch.from_numpy(inputs.random_complex(mo.n, seed=5)).cuda()
+    x, y, z = (torch.empty_like(b) for _ in range(3))
+    states = [torch.from_numpy(inputs.random_phase_state(mo.n, seed=s)).cuda() for s in (1, 2, 3)]
+    kept = glnk.Precond(mg, states[0], max_coarse=8)
+    glnk.gl_jacobian_solve(mg, states[0], kept, b, x, max_iter=5, raise_on_fail=False)
+    for psi, prec in ((states[1], glnk.GL_FP64), (states[2], glnk.GL_FP32), (states[1], glnk.GL_MIXED)):
+        kept.update(psi, precision=prec)
+        kept.apply(b, z)
+        fresh = glnk.Precond(mg, psi, precision=prec, max_coarse=8)
+        for p, out in ((kept, x), (fresh, y)):
+            rc, info = glnk.gl_jacobian_solve(mg, psi, p, b, out, max_iter=6, inner_rtol=1e-3, raise_on_fail=False)
+            assert info["iterations"] == 6
+        assert torch.equal(x, y)
+        fresh.apply(b, x)
+        assert torch.equal(x, z)
