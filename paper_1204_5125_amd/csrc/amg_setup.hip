@@ -1938,9 +1938,10 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
 // kPatchWidth neighbours (the 3D hierarchies: 30 entries and 15-30 colours reach
 // over the whole level), a patch of more than 1024 rows, or more than kPatchMost
 // updated rows per row of the level.  (Measured on the 2D levels:
-// 3-5 with 96 rows of a patch's own.)
+// 3-5 with 96 rows of a patch's own, 2.3-2.7 with 256-380.)
 constexpr double kPatchMost = 8.0;
 constexpr int kPatchLevel = 1 << 20;  // rows of a level in patches at most
+constexpr int kPatchLarge = 65536;    // rows from which a level takes the largest patches that fit
 
 static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
 {
@@ -1970,11 +1971,18 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     // (rows of a patch, of these its own): smaller patches where 512 rows do not
     // hold a patch's reach, then 1024 rows (513^2 FP64, its level of 4 923 rows:
     // 169 us per MINRES iteration with 64 rows of 512, 175 with 112 of 1024;
-    // 769^2 FP32, its level of 1 121 rows: 288 without patches, 238 with 1024)
-    const int tries[4][2] = {{512, 96}, {512, 64}, {1024, 112}, {1024, 64}};
-    for (const auto &[NR, own] : tries) {
+    // 769^2 FP32, its level of 1 121 rows: 288 without patches, 238 with 1024).
+    // A level that fills the chip several times over is bound by the rows that
+    // patches share, so it starts from the largest (us per iteration with 96
+    // rows of 512, then the first of these that fits: 1025^2 FP32, 175 446
+    // rows, 253 and 225; 769^2 FP64, 98 000 rows, 216 and 186; 601^2, below
+    // the line, 147 either way; 513^2, 44 075 rows, 143 and 141)
+    const int tries[8][2] = {{1024, 380}, {1024, 340}, {1024, 300}, {1024, 256},
+                             {512, 96}, {512, 64}, {1024, 112}, {1024, 64}};
+    for (int k = n >= kPatchLarge ? 0 : 4; k < 8; ++k) {
+        const int NR = tries[k][0], own = tries[k][1];
         S.rows = NR;
-        S.W = NR == 512 && wmax <= 8 ? 8 : NR == 512 && wmax <= 12 ? 12 : wmax <= 16 ? 16 : 24;
+        S.W = wmax <= 8 ? 8 : wmax <= 12 ? 12 : wmax <= 16 ? 16 : 24;
         const double tiles = std::max(1.0, (double)n / own);
         t.k[0] = (int)std::max(1.0, std::min(tiles, std::round(std::sqrt(tiles * ext[0] / std::max(ext[1], 1e-300)))));
         t.k[1] = std::max(1, (int)std::round(tiles / t.k[0]));

@@ -754,10 +754,10 @@ struct CsrSpmv {
 // dispatch per pass took 3-4 us, most of it launch and two dependent round trips
 // to memory; loading the patch takes 4-6 us (latency: rows, then what they
 // index), and the price is the rows that more than one patch updates (3-5 per
-// row of the level).  FP64, down / up: 4 923 and 545 rows of 7 and 8 colours 12 /
+// row of the level; 2.3-2.7 in the large patches of large levels, which that
+// traffic bounds).  FP64, down / up: 4 923 and 545 rows of 7 and 8 colours 12 /
 // 14 us (46 / 50 as 14-16 dispatches), 44 075 rows of 5 colours 13 / 19 us (35 /
-// 31); FP32, 175 446 rows of 4 colours 21 / 38 us (42 / 40): there it is bound
-// by the traffic of the shared rows, and about even.
+// 31); FP32, 175 446 rows of 4 colours 14 / 22 us (42 / 40; 21 / 38 in patches of 512).
 // Every row's value is the update of the per-pass kernels, so the sweep is the
 // same up to the order of the row sums.  The starting value of a row beyond
 // the patch is read, never written, and the sweep's result goes to another
@@ -1572,7 +1572,10 @@ static void with_patch(const Level &Lv, F &&f)
         else if (S.W == 12) go(integral_constant<int, 12>{}, nr);
         else go(integral_constant<int, 16>{}, nr);
     } else {
-        go(integral_constant<int, 16>{}, integral_constant<int, 1024>{});
+        constexpr integral_constant<int, 1024> nr{};
+        if (S.W == 8) go(integral_constant<int, 8>{}, nr);
+        else if (S.W == 12) go(integral_constant<int, 12>{}, nr);
+        else go(integral_constant<int, 16>{}, nr);
     }
 }
 

@@ -116,3 +116,17 @@ def test_solves_follow_the_values(glnk, name):
         assert torch.equal(x, y)
         fresh.apply(b, x)
         assert torch.equal(x, z)
+
+
+@pytest.mark.parametrize("shape", [(660, 650), (9000, 50)])
+def test_large_levels(glnk, shape):
+    """Levels of more than 65 536 rows take larger patches; bounds as above."""
+    side = tuple(0.25 * (n - 1) for n in shape)
+    mg, mo = glnk.Mesh(2, shape, side, mu=0.6), oracle.Mesh(2, shape, side, mu=0.6)
+    psi = inputs.random_phase_state(mo.n, seed=4)
+    r = inputs.random_complex(mo.n, seed=5)
+    want = oracle.Amg.for_state(mo, psi, max_coarse=64).precond(mo, r, cycles=1)
+    for prec, tol in ((glnk.GL_FP64, 1e-11), (glnk.GL_FP32, 1e-5)):
+        pre = glnk.Precond(mg, torch.from_numpy(psi).cuda(), precision=prec, cycles=1, max_coarse=64)
+        z = vcycle(pre, r, mo.n)
+        assert np.abs(z - want).max() <= tol * np.abs(want).max(), prec
