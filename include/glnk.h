@@ -290,13 +290,11 @@ typedef struct {
                            V-cycle as two LDS-tiled kernels (down: the three
                            sweep passes and the residual; up: the coarse
                            correction, the three passes and the output) on
-                           tiles of 32 x 32 (1024 threads), 32 x 16 (512) or
-                           16 x 16 nodes (256); 0 (default) one dispatch per
+                           tiles of 32 x 32 (768 threads), 32 x 16 (448) or
+                           16 x 16 nodes (320); 0 (default) one dispatch per
                            pass; the same operator up to rounding.  A handle
-                           whose tiles were never changed takes form 2 where
-                           it is the faster one (FP32, and FP64 up to 2^19
-                           nodes).  3D grids always use one dispatch per
-                           pass */
+                           whose tiles were never changed takes form 2.  3D
+                           grids always use one dispatch per pass */
 } gl_tiles;
 
 gl_status gl_precond_set_tiles(gl_precond *pre, const gl_tiles *tiles);

@@ -320,9 +320,9 @@ struct DeflDot {
     int N[3] = {1, 1, 1};
     double h[3] = {1.0, 1.0, 1.0};
     RedSlot slot{nullptr};
-    // the term of node i at grid coordinates c
+    // |V| of node i at grid coordinates c
     template <int DIM>
-    __device__ __forceinline__ double term(int i, const int c[3], double2 z) const
+    __device__ __forceinline__ double weight(int i, const int c[3]) const
     {
         double d = 1.0;
         if constexpr (DIM == 0) {
@@ -331,8 +331,14 @@ struct DeflDot {
 #pragma unroll
             for (int a = 0; a < DIM; ++a) d *= c[a] == 0 || c[a] == N[a] - 1 ? 0.5 * h[a] : h[a];
         }
+        return d;
+    }
+    // the node's term
+    template <int DIM>
+    __device__ __forceinline__ double term(int i, const int c[3], double2 z) const
+    {
         const double2 p = psi[i];
-        return d * (p.x * z.y - p.y * z.x);
+        return weight<DIM>(i, c) * (p.x * z.y - p.y * z.x);
     }
 };
 

@@ -362,106 +362,130 @@ struct L0Last {
 // order), so the cycle's output agrees with theirs to rounding (the compiler
 // may contract multiply-adds differently in the two); the partial sums of
 // Re<vdot, z> are grouped by tile.
-// Tile shapes (gl_tiles.l0_tiled 1, 2, 3): fewer threads and smaller tiles
-// keep more tiles resident per CU at the price of a larger halo share.
-template <int X, int Y, int NT>
+// A thread has one red-black pair in registers (right-hand side, diagonal and its
+// reciprocal, links, coefficients); LDS holds the iterate alone, by colour and
+// pair, so a pass is three conflict-free LDS reads, the update and a barrier.
+// The halo is three rows below and above and four columns left and right (pairs stay
+// whole).  A link across the grid's edge is zero, so its term drops out without a
+// branch.
+// Tile shapes (gl_tiles.l0_tiled 1, 2, 3): smaller tiles keep more of them resident
+// per CU at the price of a larger halo share.
+// What bounds it: on large grids the traffic (about 96 bytes per node up with
+// both dot products, 19 us for 1025^2 at the rate of a copy) and the halo's share
+// of the instructions; on small ones the chain row pointers - P's row - x_c, the
+// passes and the launch.  Down / up, us per dispatch, against threads that looped
+// over single nodes with every operand in LDS: 1025^2 FP32 18.5 / 33.1 (19.8 /
+// 45.3), twelve grids of 129-513^2 FP64 13.0 / 21.4 (18 / 28), 33^2 FP64 4.5 /
+// 7.8 (5.5 / 9.8).
+template <int X, int Y>
 struct L0Shape {
-    static constexpr int TX = X, TY = Y, H = 3, LX = X + 2 * H, LY = Y + 2 * H, LN = LX * LY, threads = NT;
+    static constexpr int TX = X, TY = Y, HX = 4, HY = 3, LX = X + 2 * HX, LY = Y + 2 * HY;
+    static constexpr int PX = LX / 2, pairs = PX * LY, threads = (pairs + 63) / 64 * 64;
 };
-using L0Shape1 = L0Shape<32, 32, 1024>;  // about 1.4 LDS nodes per thread and pass
-using L0Shape2 = L0Shape<32, 16, 512>;
-using L0Shape3 = L0Shape<16, 16, 256>;
+using L0Shape1 = L0Shape<32, 32>;
+using L0Shape2 = L0Shape<32, 16>;
+using L0Shape3 = L0Shape<16, 16>;
 
-// the forward links of node (gx, gy) along x and y (0 past the grid's edge),
-// loaded once per tile so that the passes read only LDS
+// a or b by value (a choice between lvalues is one between addresses, and puts
+// both in memory)
+template <class V>
+__device__ __forceinline__ V l0_pick(bool which, V a, V b)
+{
+    return V{which ? a.x : b.x, which ? a.y : b.y};
+}
+
+// one node of a pair
 template <class T>
-__device__ __forceinline__ void l0_links(const GeomT<T> &g, const LinkTab<T> &U, int gx, int gy, C<T> &ux, C<T> &uy)
-{
-    const int c[3] = {gx, gy, 0};
-    ux = gx < g.N[0] - 1 ? link_u<2, T>(U, 0, c, gx) : mk<T>(0, 0);
-    uy = gy < g.N[1] - 1 ? link_u<2, T>(U, 1, c, gy) : mk<T>(0, 0);
-}
+struct L0Node {
+    int gx, ring;  // ring: distance from the border of the tile's halo
+    bool in, odd;  // in the grid; the pair's second node
+    T a0, a1;      // edge coefficients alpha = |V| s_a / h_a^2 along x and y
+    C<T> ul, ur, ud, uu;  // links of the edges to the lower and upper neighbours along x, y
+    T d, w;        // diagonal, 1 / d
+    C<T> b, x;
 
-// The edge coefficients alpha = |V| s_a / h_a^2 of node (gx, gy) along x and
-// y (the expression the one-pass kernels evaluate per node and pass), stored
-// per LDS node in the tile's load phase.
-template <class T>
-__device__ __forceinline__ void l0_alphas(const GeomT<T> &g, int gx, int gy, T &a0, T &a1)
-{
-    const int c[3] = {gx, gy, 0};
-    T s[3];
-    const T d = node_volume<2, T>(g, c, s);
-    a0 = d * s[0] * g.inv_h2[0];
-    a1 = d * s[1] * g.inv_h2[1];
-}
-
-// (sum_{j != i} H_ij x_j) of node (gx, gy) at LDS position q (2D); the link
-// of the edge towards the lower neighbour is that neighbour's forward link
-template <class T, int LX>
-__device__ __forceinline__ C<T> l0_offdiag_lds(const GeomT<T> &g, int gx, int gy, int q, const C<T> *sx,
-                                               const C<T> *ux, const C<T> *uy, const T *sa0, const T *sa1)
-{
-    const T a0 = sa0[q], a1 = sa1[q];
-    C<T> acc = mk<T>(0, 0);
-    if (gx > 0) acc = csub(acc, cscale(cmul(ux[q - 1], sx[q - 1]), a0));
-    if (gx < g.N[0] - 1) acc = csub(acc, cscale(cmulc(ux[q], sx[q + 1]), a0));
-    if (gy > 0) acc = csub(acc, cscale(cmul(uy[q - LX], sx[q - LX]), a1));
-    if (gy < g.N[1] - 1) acc = csub(acc, cscale(cmulc(uy[q], sx[q + LX]), a1));
-    return acc;
-}
-
-struct L0TileAt {
-    int x0, y0;  // grid coordinates of LDS position 0
+    // sum_{j != i} H_ij x_j; far: x of the neighbour in the next pair
+    __device__ __forceinline__ C<T> offdiag(C<T> own, C<T> far, C<T> dn, C<T> up) const
+    {
+        const C<T> xl = l0_pick(odd, own, far), xr = l0_pick(odd, far, own);
+        C<T> acc = mk<T>(0, 0);
+        acc = csub(acc, cscale(cmul(ul, xl), a0));
+        acc = csub(acc, cscale(cmulc(ur, xr), a0));
+        acc = csub(acc, cscale(cmul(ud, dn), a1));
+        acc = csub(acc, cscale(cmulc(uu, up), a1));
+        return acc;
+    }
 };
 
-template <class S>
-__device__ __forceinline__ L0TileAt l0_tile(int tile, int ntx)
-{
-    return L0TileAt{(tile % ntx) * S::TX - S::H, (tile / ntx) * S::TY - S::H};
-}
+template <class T, class S>
+struct L0Pair {
+    int p, t, gy;   // place in LDS; pair of the grid; row
+    bool act, own;  // a pair of the tile with its halo; of the tile
+    L0Node<T> n[2];  // red, black
 
-// LDS position q: grid coordinates, in the grid, and its ring (distance from
-// the LDS border: 0 on the outermost ring, S::H inside the tile)
-template <class S>
-__device__ __forceinline__ void l0_pos(const L0TileAt &T0, int q, const int *N, int &gx, int &gy, bool &in,
-                                       int &ring)
-{
-    const int lx = q % S::LX, ly = q / S::LX;
-    gx = T0.x0 + lx;
-    gy = T0.y0 + ly;
-    in = gx >= 0 && gx < N[0] && gy >= 0 && gy < N[1];
-    ring = min(min(lx, S::LX - 1 - lx), min(ly, S::LY - 1 - ly));
-}
-
-// Calls f(q, gx, gy) for the LDS nodes of colour col ((gx + gy) & 1) that
-// are at least rmin rings in from the LDS border and lie in the grid, the
-// threads taking them in turn: a pass visits only the nodes it updates, with
-// no lane idle on the other colour or outside its rings.
-template <class S, class F>
-__device__ __forceinline__ void l0_colour_nodes(const L0TileAt &T0, const int *N, int col, int rmin, F &&f)
-{
-    const int w = (S::LX - 2 * rmin) / 2, h = S::LY - 2 * rmin;
-    for (int k = threadIdx.x; k < w * h; k += S::threads) {
-        const int ly = rmin + k / w;
-        const int lx = rmin + 2 * (k % w) + ((col ^ (T0.x0 + T0.y0 + ly + rmin)) & 1);
-        const int gx = T0.x0 + lx, gy = T0.y0 + ly;
-        if (gx < 0 || gx >= N[0] || gy < 0 || gy >= N[1]) continue;
-        f(ly * S::LX + lx, gx, gy);
+    __device__ __forceinline__ L0Pair(const GeomT<T> &g, const LinkTab<T> &U, const T *hs, int tile, int ntx)
+    {
+        p = threadIdx.x;
+        act = p < S::pairs;
+        const int lp = p % S::PX, ly = p / S::PX;
+        const int ge = (tile % ntx) * S::TX - S::HX + 2 * lp;  // the pair's even node
+        gy = (tile / ntx) * S::TY - S::HY + ly;
+        own = act && lp >= S::HX / 2 && lp < (S::HX + S::TX) / 2 && ly >= S::HY && ly < S::HY + S::TY;
+        const int nx = g.N[0], ny = g.N[1];
+        const bool row = act && gy >= 0 && gy < ny;
+        t = row && ge >= 0 && ge < nx ? (ge >> 1) + g.hr * gy : 0;
+        // links of the pair's seven edges (coordinates clamped into the grid,
+        // those across its edge zeroed)
+        const int cy = min(max(gy, 0), ny - 1), dy = max(cy - 1, 0);
+        C<T> ux[3], ud[2], uu[2];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int cx = min(max(ge - 1 + k, 0), nx - 1);
+            const int c[3] = {cx, cy, 0};
+            ux[k] = link_u<2, T>(U, 0, c, cx);
+            if (ge - 1 + k < 0 || ge - 1 + k >= nx - 1) ux[k] = mk<T>(0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int c[3] = {min(max(ge + k, 0), nx - 1), cy, 0};
+            ud[k] = gy > 0 ? link_u<2, T>(U, 1, c, dy) : mk<T>(0, 0);
+            uu[k] = gy < ny - 1 ? link_u<2, T>(U, 1, c, cy) : mk<T>(0, 0);
+        }
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            L0Node<T> &m = n[col];
+            m.odd = (col ^ gy) & 1;
+            m.gx = ge + m.odd;
+            m.in = row && m.gx >= 0 && m.gx < nx;
+            const int lx = 2 * lp + m.odd;
+            m.ring = m.in ? min(min(lx, S::LX - 1 - lx), min(ly, S::LY - 1 - ly)) : -1;
+            m.ul = l0_pick(m.odd, ux[1], ux[0]);
+            m.ur = l0_pick(m.odd, ux[2], ux[1]);
+            m.ud = l0_pick(m.odd, ud[1], ud[0]);
+            m.uu = l0_pick(m.odd, uu[1], uu[0]);
+            const int c[3] = {m.gx, gy, 0};
+            T sc[3];
+            const T vol = node_volume<2, T>(g, c, sc);
+            m.a0 = vol * sc[0] * g.inv_h2[0];
+            m.a1 = vol * sc[1] * g.inv_h2[1];
+            m.d = m.in ? hs[col * g.npair + t] : (T)1;
+            m.w = (T)1 / m.d;
+            m.b = m.x = mk<T>(0, 0);
+        }
     }
-}
-
-// Calls f(q, gx, gy) for the tile's own nodes (S::H rings in) that lie in the
-// grid.
-template <class S, class F>
-__device__ __forceinline__ void l0_tile_nodes(const L0TileAt &T0, const int *N, F &&f)
-{
-    for (int k = threadIdx.x; k < S::TX * S::TY; k += S::threads) {
-        const int ly = S::H + k / S::TX, lx = S::H + k % S::TX;
-        const int gx = T0.x0 + lx, gy = T0.y0 + ly;
-        if (gx >= N[0] || gy >= N[1]) continue;
-        f(ly * S::LX + lx, gx, gy);
+    // the sum above for the node of colour col, given the other colour's values
+    __device__ __forceinline__ C<T> offdiag(int col, const C<T> *other) const
+    {
+        const L0Node<T> &m = n[col];
+        return m.offdiag(n[1 - col].x, other[m.odd ? p + 1 : p - 1], other[p - S::PX], other[p + S::PX]);
     }
-}
+    // x = (b - sum) / d where the node is at least rmin rings in
+    __device__ __forceinline__ void update(int col, int rmin, const C<T> *other)
+    {
+        L0Node<T> &m = n[col];
+        if (m.ring >= rmin) m.x = cscale(csub(m.b, offdiag(col, other)), m.w);
+    }
+};
 
 // Down: b = round(v), red from zero, black, red, black residual (L0PreBlack,
 // L0Sweep(0), L0Residual); writes b and x of the tile's nodes and r of its
@@ -470,7 +494,7 @@ template <class T, class S>
 struct L0PreTile {
     GeomT<T> g;
     const double2 *v;
-    const T *hd;
+    const T *hs;
     LinkTab<T> U;
     C<T> *b, *x, *r;
     int ntx;
@@ -478,54 +502,58 @@ struct L0PreTile {
     __device__ void operator()(int bx, int nbx) const
     {
         GATE_LOAD();
-        __shared__ C<T> sb[S::LN], sx[S::LN], ux[S::LN], uy[S::LN];
-        __shared__ T sd[S::LN], sa0[S::LN], sa1[S::LN];
-        const L0TileAt T0 = l0_tile<S>(xcd_tile(bx, nbx), ntx);
-        for (int q = threadIdx.x; q < S::LN; q += S::threads) {
-            int gx, gy, ring;
-            bool in;
-            l0_pos<S>(T0, q, g.N, gx, gy, in, ring);
-            const int i = gx + g.N[0] * gy;
-            const C<T> bi = in ? narrow<T>(v[i]) : mk<T>(0, 0);
-            const T di = in ? hd[i] : (T)1;
-            C<T> lx = mk<T>(0, 0), ly = lx;
-            T a0 = (T)0, a1 = (T)0;
-            if (in) {
-                l0_links<T>(g, U, gx, gy, lx, ly);
-                l0_alphas<T>(g, gx, gy, a0, a1);
-            }
-            sb[q] = bi;
-            sd[q] = di;
-            ux[q] = lx;
-            uy[q] = ly;
-            sa0[q] = a0;
-            sa1[q] = a1;
-            // red from zero: x = b / d
-            sx[q] = in && ((gx + gy) & 1) == 0 ? cscale(bi, (T)1 / di) : mk<T>(0, 0);
-        }
-        __syncthreads();
-        // black (exact one ring in), then red (two rings in)
+        __shared__ C<T> sr[S::pairs], sb[S::pairs];
+        const int tile = xcd_tile(bx, nbx);
+        L0Pair<T, S> P(g, U, hs, tile, ntx);
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            l0_colour_nodes<S>(T0, g.N, pass == 0 ? 1 : 0, pass + 1, [&](int q, int gx, int gy) {
-                sx[q] = cscale(csub(sb[q], l0_offdiag_lds<T, S::LX>(g, gx, gy, q, sx, ux, uy, sa0, sa1)), (T)1 / sd[q]);
-            });
-            __syncthreads();
-        }
-        // the tile's nodes: b, x, and the black residual
+        for (int col = 0; col < 2; ++col)
+            if (P.n[col].in) P.n[col].b = narrow<T>(v[P.n[col].gx + g.N[0] * P.gy]);
+        P.n[0].x = cscale(P.n[0].b, P.n[0].w);  // red from zero: x = b / d
+        if (P.act) sr[P.p] = P.n[0].x;
+        __syncthreads();
+        P.update(1, 1, sr);
+        if (P.act) sb[P.p] = P.n[1].x;
+        __syncthreads();
+        P.update(0, 2, sb);
+        if (P.act) sr[P.p] = P.n[0].x;
+        __syncthreads();
+        if (!P.own || !gate_go) return;
         const int np = g.npair;
-        l0_tile_nodes<S>(T0, g.N, [&](int q, int gx, int gy) {
-            const int col = (gx + gy) & 1;
-            const int t = (gx >> 1) + g.hr * gy;
-            C<T> ri = mk<T>(0, 0);
-            if (col == 1) ri = csub(csub(sb[q], cscale(sx[q], sd[q])), l0_offdiag_lds<T, S::LX>(g, gx, gy, q, sx, ux, uy, sa0, sa1));
-            if (!gate_go) return;
-            b[col * np + t] = sb[q];
-            x[col * np + t] = sx[q];
-            if (col == 1) r[np + t] = ri;
-        });
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            if (!P.n[col].in) continue;
+            b[col * np + P.t] = P.n[col].b;
+            x[col * np + P.t] = P.n[col].x;
+        }
+        const L0Node<T> &m = P.n[1];
+        if (m.in) r[np + P.t] = csub(csub(m.b, cscale(m.x, m.d)), P.offdiag(1, sr));
     }
 };
+
+// (P x_c)_k with four entries in flight
+template <class T>
+__device__ __forceinline__ C<T> prolong_row4(const int *__restrict__ prp, const int *__restrict__ pci,
+                                             const C<T> *__restrict__ pv, const C<T> *__restrict__ xc, int k)
+{
+    C<T> s = mk<T>(0, 0);
+    const int p1 = prp[k + 1];
+    for (int p = prp[k]; p < p1; p += 4) {
+        C<T> a[4], x[4];
+        int j[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int pe = min(p + e, p1 - 1);
+            j[e] = pci[pe];
+            a[e] = pv[pe];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = xc[j[e]];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (p + e < p1) s = cadd(s, cmul(a[e], x[e]));
+    }
+    return s;
+}
 
 // Up: black += (P x_c)_b, red, black, last red; z = x on the tile's nodes (ADD:
 // z += x) and partial sums of Re<vdot, z> (L0ProlongBlack, L0Sweep(0),
@@ -534,7 +562,7 @@ template <class T, class TC, int ADD, class S>
 struct L0PostTile {
     GeomT<T> g;
     const C<T> *b, *x;
-    const T *hd;
+    const T *hs;
     LinkTab<T> U;
     const int *prp, *pci;
     const C<TC> *pv, *xc;
@@ -548,60 +576,52 @@ struct L0PostTile {
     __device__ void operator()(int bx, int nbx) const
     {
         GATE_LOAD();
-        __shared__ C<T> sb[S::LN], sx[S::LN], ux[S::LN], uy[S::LN];
-        __shared__ T sd[S::LN], sa0[S::LN], sa1[S::LN];
+        __shared__ C<T> sr[S::pairs], sb[S::pairs];
         __shared__ double sm[S::threads / 64];
-        const L0TileAt T0 = l0_tile<S>(xcd_tile(bx, nbx), ntx);
-        const int np = g.npair;
-        for (int q = threadIdx.x; q < S::LN; q += S::threads) {
-            int gx, gy, ring;
-            bool in;
-            l0_pos<S>(T0, q, g.N, gx, gy, in, ring);
-            C<T> bi = mk<T>(0, 0), xi = mk<T>(0, 0), lx = xi, ly = xi;
-            T di = (T)1, a0 = (T)0, a1 = (T)0;
-            if (in) {
-                const int col = (gx + gy) & 1;
-                const int t = (gx >> 1) + g.hr * gy;
-                bi = b[col * np + t];
-                di = hd[gx + g.N[0] * gy];
-                l0_links<T>(g, U, gx, gy, lx, ly);
-                l0_alphas<T>(g, gx, gy, a0, a1);
-                // red values are recomputed from the black ones before any use
-                if (col == 1) xi = cadd(x[np + t], as_c<T>(prolong_row<TC>(prp, pci, pv, xc, t)));
-            }
-            sb[q] = bi;
-            sx[q] = xi;
-            sd[q] = di;
-            ux[q] = lx;
-            uy[q] = ly;
-            sa0[q] = a0;
-            sa1[q] = a1;
-        }
-        __syncthreads();
-        // red (one ring in), black (two rings in)
+        const int tile = xcd_tile(bx, nbx), np = g.npair;
+        L0Pair<T, S> P(g, U, hs, tile, ntx);
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            l0_colour_nodes<S>(T0, g.N, pass, pass + 1, [&](int q, int gx, int gy) {
-                sx[q] = cscale(csub(sb[q], l0_offdiag_lds<T, S::LX>(g, gx, gy, q, sx, ux, uy, sa0, sa1)), (T)1 / sd[q]);
-            });
-            __syncthreads();
+        for (int col = 0; col < 2; ++col)
+            if (P.n[col].in) P.n[col].b = b[col * np + P.t];
+        // red values are recomputed from the black ones before any use
+        if (P.n[1].in) P.n[1].x = cadd(x[np + P.t], as_c<T>(prolong_row4<TC>(prp, pci, pv, xc, P.t)));
+        // what the tile's own nodes are multiplied with, loaded behind the passes
+        double2 vd[2], ps[2], zo[2];
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            vd[col] = ps[col] = zo[col] = make_double2(0.0, 0.0);
+            if (!P.own || !P.n[col].in) continue;
+            const int i = P.n[col].gx + g.N[0] * P.gy;
+            if (want_dot) vd[col] = vdot[i];
+            if (dd.psi) ps[col] = dd.psi[i];
+            if (ADD) zo[col] = z[i];
         }
+        if (P.act) sb[P.p] = P.n[1].x;
+        __syncthreads();
+        P.update(0, 1, sb);
+        if (P.act) sr[P.p] = P.n[0].x;
+        __syncthreads();
+        P.update(1, 2, sr);
+        if (P.act) sb[P.p] = P.n[1].x;
+        __syncthreads();
         // last red on the tile, into z only; z on every node of the tile
         double part = 0.0, part_u = 0.0;
-        l0_tile_nodes<S>(T0, g.N, [&](int q, int gx, int gy) {
-            C<T> xi = sx[q];
-            if (((gx + gy) & 1) == 0)
-                xi = cscale(csub(sb[q], l0_offdiag_lds<T, S::LX>(g, gx, gy, q, sx, ux, uy, sa0, sa1)), (T)1 / sd[q]);
-            const int i = gx + g.N[0] * gy;
-            double2 zi = widen(xi);
-            if (ADD) zi = cadd(z[i], zi);
-            if (want_dot) part += redot(vdot[i], zi);
-            if (dd.psi) {
-                const int c[3] = {gx, gy, 0};
-                part_u += dd.term<2>(i, c, zi);
+        if (P.own) {
+            P.update(0, 3, sb);
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                const L0Node<T> &m = P.n[col];
+                if (!m.in) continue;
+                double2 zi = widen(m.x);
+                if (ADD) zi = cadd(zo[col], zi);
+                if (want_dot) part += redot(vd[col], zi);
+                if (dd.psi) {
+                    const int c[3] = {m.gx, P.gy, 0};
+                    part_u += dd.weight<2>(0, c) * (ps[col].x * zi.y - ps[col].y * zi.x);
+                }
+                if (gate_go) z[m.gx + g.N[0] * P.gy] = zi;
             }
-            if (gate_go) z[i] = zi;
-        });
+        }
         if (want_dot && gate_go) block_reduce_store(part, slot, sm, bx);
         if (dd.psi && gate_go) block_reduce_store(part_u, dd.slot, sm, bx);
     }
@@ -1621,17 +1641,11 @@ static C<T> *cycle_result(gl_precond *pre, int l)
 }
 
 // The form of level 0 of a 2D grid: as gl_precond_set_tiles asked; on a handle
-// whose tiles were never changed, tiles of 32 x 16 as long as the seven
-// dispatches of the per-pass form cost more than the tiles' halo does: in FP32
-// always, in FP64 up to 2^19 nodes.  Microseconds per MINRES iteration, a
-// dispatch per pass / tiles, FP64: 33^2 67 / 59, 129^2 97 / 88, 257^2 107 / 95,
-// 513^2 172 / 169, 769^2 213 / 213, 1025^2 356 / 362; FP32: 33^2 65 / 56, 257^2 101 /
-// 90, 513^2 151 / 138, 1025^2 285 / 282.
-static int l0_form(const gl_precond *pre, bool f32)
-{
-    if (!pre->auto_tiles) return pre->l0_tiled;
-    return f32 || pre->L[0].n <= 1 << 19 ? 2 : 0;
-}
+// whose tiles were never changed, tiles of 32 x 16.  Microseconds per MINRES
+// iteration, a dispatch per pass / tiles, FP64: 513^2 147 / 136, 769^2 190 /
+// 175, 1025^2 291 / 278, 1537^2 578 / 559, 2049^2 1058 / 1048 (smaller grids and
+// FP32 gain more).
+static int l0_form(const gl_precond *pre) { return pre->auto_tiles ? 2 : pre->l0_tiled; }
 
 // calls f with the tile shape of gl_tiles.l0_tiled (1, 2 or 3)
 template <class F>
@@ -1749,7 +1763,7 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
     // black, red, black residual, restriction; in 2D by default the three
     // passes in one LDS-tiled kernel (L0PreTile)
     const int nbp = blocks_for(g.npair);
-    const int tiled = DIM == 2 ? l0_form(pre, f32) : 0;
+    const int tiled = DIM == 2 ? l0_form(pre) : 0;
     if (tiled) {
         // each array once (the halo's re-reads come from cache)
         const double b_tile = nn * 16 + nn * szr + 2 * nn * sz + mc * sz;
@@ -1758,7 +1772,7 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
                 using S = decltype(sh);
                 const int ntx = (g.N[0] + S::TX - 1) / S::TX, nbt = ntx * ((g.N[1] + S::TY - 1) / S::TY);
                 L.run<L0PreTile<T, S>, S::threads>(nbt,
-                                                   L0PreTile<T, S>{g, v, hd, U, vec_b<T>(L0), x0, vec_r<T>(L0), ntx, gate});
+                                                   L0PreTile<T, S>{g, v, hs, U, vec_b<T>(L0), x0, vec_r<T>(L0), ntx, gate});
             });
         });
     } else {
@@ -1794,11 +1808,11 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
                 nbt = ntx * ((g.N[1] + S::TY - 1) / S::TY);
                 if (add)
                     L.run<L0PostTile<T, TC, 1, S>, S::threads>(
-                        nbt, L0PostTile<T, TC, 1, S>{g, b0, x0, hd, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
+                        nbt, L0PostTile<T, TC, 1, S>{g, b0, x0, hs, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
                                                      x1, z, vdot, slot, want, dd, ntx, gate});
                 else
                     L.run<L0PostTile<T, TC, 0, S>, S::threads>(
-                        nbt, L0PostTile<T, TC, 0, S>{g, b0, x0, hd, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
+                        nbt, L0PostTile<T, TC, 0, S>{g, b0, x0, hs, U, L0.Pb.rp.get(), L0.Pb.ci.get(), vals<TC>(L0.Pb),
                                                      x1, z, vdot, slot, want, dd, ntx, gate});
             });
         });
