@@ -273,8 +273,8 @@ void gl_precond_destroy(gl_precond *pre);
  *   dense_rows: the first level >= 1 with at most this many rows has the
  *     V-cycle below it (its smoothing sweeps, residual, transfers and every
  *     coarser level: a linear map of its right-hand side) formed as an
- *     explicit matrix at every setup, in FP64 by the bottom kernel's
- *     arithmetic applied to the unit vectors, and applied as one dense
+ *     explicit matrix at every setup, in FP64 by the cycle's steps applied
+ *     to the unit vectors, and applied as one dense
  *     product; the same operator up to rounding, one dispatch in place of a
  *     few dozen latency-bound ones.  0 = off (default), else 1 .. 8192; the
  *     matrix takes 24 n^2 bytes (FP64 and FP32 copies) and its formation a

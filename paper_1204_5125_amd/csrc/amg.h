@@ -77,6 +77,7 @@ struct Level {
     // is one contiguous row range (new index r' = position in cperm).
     DevBuf<int> perm, iperm;        // new -> old, old -> new (l >= 1)
     Csr Aa, Pa, Ra;                 // Aa (l >= 1); Pa, Ra: transfers to l + 1
+    DevBuf<int> dpos;               // Aa's rows are sorted: place of the diagonal entry of each
     DevBuf<int> amap, pmap, rmap;   // value of entry q = value of entry map[q] of A, P, R
     Csr Rb;                         // level 0: Ra without the red columns (the residual is zero there),
                                     // columns numbered in the colour-split layout of the level-0 vectors
@@ -106,7 +107,7 @@ struct Level {
 template <class T>
 struct BottomLevel {
     int n, nc, ncolors;
-    const int *rp, *ci;
+    const int *rp, *ci, *dpos;
     const C<T> *v;
     const T *diag;
     int coff[kMaxColors + 1];  // colour c = rows coff[c] .. coff[c+1]-1

@@ -1241,6 +1241,16 @@ __global__ void k_perm_fill(int nrows, const int *rowperm, const int *rp, const 
     }
 }
 
+// place of the diagonal entry of each sorted row
+__global__ void k_diag_place(int n, const int *rp, const int *ci, int *dpos)
+{
+    const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r >= n) return;
+    int p = rp[r];
+    while (p < rp[r + 1] && ci[p] < r) ++p;
+    dpos[r] = p;
+}
+
 // Level-0 restriction without the red columns: the level-0 residual the
 // V-cycle restricts is zero on red nodes (their last pre-smoothing update
 // zeroes it), so those entries only ever multiply zeros.  Row r keeps the
@@ -1821,8 +1831,9 @@ static void alloc_values(gl_precond *pre)
 }
 
 // copy of M with rows taken in the order rowperm and columns relabelled by colmap
+// (sorted: rows in ascending order of the new columns)
 static void permuted_copy(const Csr &M, const int *rowperm, const int *colmap, Csr &out, DevBuf<int> &map,
-                          SymTmp &T, hipStream_t s)
+                          SymTmp &T, hipStream_t s, bool sorted = false)
 {
     out.n = M.n;
     out.m = M.m;
@@ -1831,8 +1842,12 @@ static void permuted_copy(const Csr &M, const int *rowperm, const int *colmap, C
     GLK_CHECK_LAUNCH();
     alloc_rowptr(out, cnt, T, s);
     map.alloc(std::max(1, out.nnz));
-    k_perm_fill<<<blocks_for(M.n), kBlock, 0, s>>>(M.n, rowperm, M.rp.get(), M.ci.get(), colmap, out.rp.get(),
-                                                   out.ci.get(), map.get());
+    int *fci = sorted ? need(T.b, std::max(1, out.nnz)) : out.ci.get();
+    int *fmap = sorted ? need(T.c, std::max(1, out.nnz)) : map.get();
+    k_perm_fill<<<blocks_for(M.n), kBlock, 0, s>>>(M.n, rowperm, M.rp.get(), M.ci.get(), colmap, out.rp.get(), fci, fmap);
+    if (sorted)
+        k_sort_rows<<<(M.n + kRowWaves - 1) / kRowWaves, kBlock, 0, s>>>(M.n, out.rp.get(), fci, fmap, out.ci.get(),
+                                                                         map.get());
     GLK_CHECK_LAUNCH();
     out.v64.alloc(std::max(1, out.nnz));
     out.v32.alloc(std::max(1, out.nnz));
@@ -1869,7 +1884,12 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
         const bool generic = l >= lfirst;
         const int *rowp = generic ? L.perm.get() : nullptr;
         const int *colp = generic ? L.iperm.get() : nullptr;
-        if (generic) permuted_copy(L.A, rowp, colp, L.Aa, L.amap, T, s);
+        if (generic) {
+            permuted_copy(L.A, rowp, colp, L.Aa, L.amap, T, s, true);
+            L.dpos.alloc(L.n);
+            k_diag_place<<<blocks_for(L.n), kBlock, 0, s>>>(L.n, L.Aa.rp.get(), L.Aa.ci.get(), L.dpos.get());
+            GLK_CHECK_LAUNCH();
+        }
         if (l + 1 < pre->nlev) {
             Level &Nx = pre->L[l + 1];
             permuted_copy(L.P, rowp, Nx.iperm.get(), L.Pa, L.pmap, T, s);

@@ -1240,17 +1240,32 @@ struct Bottom {
     }
 };
 
-// Block forms of the bottom kernel's steps, for forming an explicit sub-cycle
-// kTailBlock columns at a time: vectors are [n][kTailBlock] blocks (the
-// columns of a row contiguous), thread t works on row t / kTailBlock and
-// column t % kTailBlock, and the kTailBlock threads of a row read the same
-// matrix entries, so a level's matrix is read once per block of columns
-// instead of once per column.  A thread takes its row's entries in groups of
-// kTailUnroll, every gather of a group issued before any is used, and sums
-// them in order.  A null right-hand side stands for columns bid .. bid +
-// kTailBlock - 1 of the identity.
+// Forming an explicit sub-cycle kTailBlock columns at a time: vectors are
+// [n][kTailBlock] blocks (the columns of a row contiguous), thread t works on row
+// t / kTailBlock and column t % kTailBlock, and the kTailBlock threads of a row
+// read the same matrix entries, so a level's matrix is read once per block of
+// columns instead of once per column.  A thread takes its row's entries in groups
+// of kTailUnroll, every gather of a group issued before any is used, and sums them
+// in order.  A null right-hand side stands for columns bid .. bid + kTailBlock - 1
+// of the identity.
+// What bounds it is the gathers' traffic (the blocks' vectors are far larger than
+// L2), so each row is split at its diagonal, A = L + D + U by the order of the
+// colours, and no product that a pass has already formed is formed again:
+//   forward from zero   y = (D + L)^-1 b                    reads L
+//   backward            e = D^-1 U x,  x = y - e            reads U
+//   residual            r = b - A x = L e                   reads L
+//   forward again       s = b - L x,  x = D^-1 (s - U x)    reads L and U
+//   backward            x = D^-1 (s - U x)                  reads U
+// three reads of the matrix in place of five.  The sub-cycle is Hermitian, so
+// a block whose first column has colour k also skips colours below k in the first
+// pass (y = 0 there) and in the last (those rows are mirrored from the columns that
+// compute them).  5 592 rows of 31 colours, 58 entries each: 11.9 ms (21.8 with whole
+// rows and all columns); 2 173 rows of the 1025^2 hierarchy: 0.88 (1.19).  1024
+// threads and 8 columns: 512 threads 15.7 and 0.92, 16 columns 14.4 and 0.99, 4
+// columns of 256 threads 19.4 and 0.82, groups of four entries 14.8 and 0.89.
 constexpr int kTailBlock = 8;
-constexpr int kTailRows = kBottomThreads / kTailBlock;  // rows per round
+constexpr int kTailThreads = 1024;
+constexpr int kTailRows = kTailThreads / kTailBlock;  // rows per round
 constexpr int kTailUnroll = 8;
 
 template <class T>
@@ -1259,75 +1274,46 @@ __device__ __forceinline__ C<T> blk_rhs(const C<T> *b, int bid, int i, int c)
     return b ? b[(size_t)i * kTailBlock + c] : mk<T>(i == bid + c ? 1 : 0, 0);
 }
 
-// sum over k in [k0, k1) of v[k] x[idx[k]][c], skipping idx[k] == skip
+// acc += sum over k in [k0, k1) of v[k] x[idx[k]][c]
 template <class T>
-__device__ __forceinline__ C<T> blk_row_sum(const int *idx, const C<T> *v, int k0, int k1, const C<T> *x, int c,
-                                            int skip)
+__device__ __forceinline__ void blk_row_sum(const int *idx, const C<T> *v, int k0, int k1, const C<T> *x, int c,
+                                            C<T> &acc)
 {
-    C<T> acc = mk<T>(0, 0);
-    int k = k0;
-    for (; k + kTailUnroll <= k1; k += kTailUnroll) {
+    for (int k = k0; k < k1; k += kTailUnroll) {
         int j[kTailUnroll];
         C<T> a[kTailUnroll], xv[kTailUnroll];
 #pragma unroll
         for (int u = 0; u < kTailUnroll; ++u) {
-            j[u] = idx[k + u];
-            a[u] = v[k + u];
+            const int q = min(k + u, k1 - 1);
+            j[u] = idx[q];
+            a[u] = v[q];
         }
 #pragma unroll
         for (int u = 0; u < kTailUnroll; ++u) xv[u] = x[(size_t)j[u] * kTailBlock + c];
 #pragma unroll
         for (int u = 0; u < kTailUnroll; ++u)
-            if (j[u] != skip) acc = cadd(acc, cmul(a[u], xv[u]));
+            if (k + u < k1) acc = cadd(acc, cmul(a[u], xv[u]));
     }
-    for (; k < k1; ++k) {
-        const int jj = idx[k];
-        if (jj != skip) acc = cadd(acc, cmul(v[k], x[(size_t)jj * kTailBlock + c]));
-    }
-    return acc;
 }
 
-// one colour of a level, from its ELL block
-template <class T>
-__device__ __forceinline__ void blk_sgs_colour(const BottomLevel<T> &L, int colour, const C<T> *b, int bid, C<T> *x)
+// f(i) for the thread's rows of [r0, r1)
+template <class F>
+__device__ __forceinline__ void blk_rows(int r0, int r1, F &&f)
 {
-    const int cnt = L.coff[colour + 1] - L.coff[colour];
-    const int row0 = L.coff[colour];
-    const int W = L.ewidth[colour];
-    const int *eci = L.eci + L.eoff[colour];
-    const C<T> *ev = L.ev + L.eoff[colour];
-    const int c = threadIdx.x % kTailBlock;
-    for (int r = threadIdx.x / kTailBlock; r < cnt; r += kTailRows) {
-        const int i = row0 + r;
-        const C<T> bi = blk_rhs<T>(b, bid, i, c);
-        const size_t e0 = (size_t)r * W;
-        const C<T> acc = blk_row_sum<T>(eci + e0, ev + e0, 0, W, x, c, i);
-        x[(size_t)i * kTailBlock + c] = cscale(csub(bi, acc), (T)1 / L.diag[i]);
-    }
+    for (int i = r0 + threadIdx.x / kTailBlock; i < r1; i += kTailRows) f(i);
 }
 
-template <class T>
-__device__ __forceinline__ void blk_sgs(const BottomLevel<T> &L, const C<T> *b, int bid, C<T> *x)
-{
-    for (int t = 0; t < 2 * L.ncolors - 1; ++t) {
-        blk_sgs_colour<T>(L, t < L.ncolors ? t : 2 * L.ncolors - 2 - t, b, bid, x);
-        __syncthreads();
-    }
-}
-
-// MODE 0: y = M x, 1: y += M x, 2: y = b - M x
-template <class T, int MODE>
-__device__ __forceinline__ void blk_spmv(int nrows, const int *rp, const int *ci, const C<T> *v, const C<T> *x,
-                                         const C<T> *b, int bid, C<T> *y)
+// y = M x, or y += M x
+template <class T, bool ADD>
+__device__ __forceinline__ void blk_spmv(int nrows, const int *rp, const int *ci, const C<T> *v, const C<T> *x, C<T> *y)
 {
     const int c = threadIdx.x % kTailBlock;
-    for (int i = threadIdx.x / kTailBlock; i < nrows; i += kTailRows) {
-        const C<T> acc = blk_row_sum<T>(ci, v, rp[i], rp[i + 1], x, c, -1);
+    blk_rows(0, nrows, [&](int i) {
         C<T> &yi = y[(size_t)i * kTailBlock + c];
-        if (MODE == 0) yi = acc;
-        else if (MODE == 1) yi = cadd(yi, acc);
-        else yi = csub(blk_rhs<T>(b, bid, i, c), acc);
-    }
+        C<T> acc = mk<T>(0, 0);
+        blk_row_sum<T>(ci, v, rp[i], rp[i + 1], x, c, acc);
+        yi = ADD ? cadd(yi, acc) : acc;
+    });
 }
 
 // y = M b for a dense row-major n x n matrix
@@ -1335,7 +1321,7 @@ template <class T>
 __device__ __forceinline__ void blk_dense(int n, const C<T> *M, const C<T> *b, C<T> *y)
 {
     const int c = threadIdx.x % kTailBlock;
-    for (int i = threadIdx.x / kTailBlock; i < n; i += kTailRows) {
+    blk_rows(0, n, [&](int i) {
         const C<T> *row = M + (size_t)i * n;
         C<T> acc = mk<T>(0, 0);
         int j = 0;
@@ -1351,42 +1337,107 @@ __device__ __forceinline__ void blk_dense(int n, const C<T> *M, const C<T> *b, C
         }
         for (; j < n; ++j) acc = cadd(acc, cmul(row[j], b[(size_t)j * kTailBlock + c]));
         y[(size_t)i * kTailBlock + c] = acc;
-    }
+    });
 }
 
+// the first colour with rows at or past row i
+template <class T>
+__device__ __forceinline__ int blk_colour(const BottomLevel<T> &L, int i)
+{
+    int k = 0;
+    while (L.coff[k + 1] <= i) ++k;
+    return k;
+}
+
+// b of a level below the one whose columns are formed (null on that level), its
+// iterate, e (then s) and residual
+template <class T>
+struct BlkVec {
+    C<T> *b, *x, *e, *r;
+};
+
 // The V-cycle over levels D.first .. D.last on kTailBlock identity columns
-// (the steps of bottom_cycle); vec(l, k): level l's b (k = 0, unused on
-// D.first), x (1) or r (2) block.
 template <class T, class V>
 __device__ __forceinline__ void blk_cycle(const BottomDesc<T> &D, V vec, int bid)
 {
+    const int c = threadIdx.x % kTailBlock;
+    const int kfirst = blk_colour<T>(D.L[D.first], bid);
     for (int l = D.first; l < D.last; ++l) {
         const BottomLevel<T> &L = D.L[l];
-        const C<T> *b = l == D.first ? nullptr : vec(l, 0);
-        C<T> *x = vec(l, 1), *r = vec(l, 2);
-        for (int t = threadIdx.x; t < L.n * kTailBlock; t += kBottomThreads) x[t] = mk<T>(0, 0);
+        const BlkVec<T> W = vec(l);
+        const int k0 = l == D.first ? kfirst : 0;
+        blk_rows(0, L.coff[k0], [&](int i) { W.x[(size_t)i * kTailBlock + c] = mk<T>(0, 0); });
         __syncthreads();
-        blk_sgs<T>(L, b, bid, x);
-        blk_spmv<T, 2>(L.n, L.rp, L.ci, L.v, x, b, bid, r);
+        for (int k = k0; k < L.ncolors; ++k) {
+            blk_rows(L.coff[k], L.coff[k + 1], [&](int i) {
+                C<T> acc = mk<T>(0, 0);
+                blk_row_sum<T>(L.ci, L.v, L.rp[i], L.dpos[i], W.x, c, acc);
+                W.x[(size_t)i * kTailBlock + c] = cscale(csub(blk_rhs<T>(W.b, bid, i, c), acc), (T)1 / L.diag[i]);
+            });
+            __syncthreads();
+        }
+        for (int k = L.ncolors - 1; k >= 0; --k) {
+            blk_rows(L.coff[k], L.coff[k + 1], [&](int i) {
+                const size_t q = (size_t)i * kTailBlock + c;
+                C<T> acc = mk<T>(0, 0);
+                blk_row_sum<T>(L.ci, L.v, L.dpos[i] + 1, L.rp[i + 1], W.x, c, acc);
+                const C<T> e = cscale(acc, (T)1 / L.diag[i]);
+                W.e[q] = e;
+                W.x[q] = csub(W.x[q], e);
+            });
+            __syncthreads();
+        }
+        blk_rows(0, L.n, [&](int i) {
+            C<T> acc = mk<T>(0, 0);
+            blk_row_sum<T>(L.ci, L.v, L.rp[i], L.dpos[i], W.e, c, acc);
+            W.r[(size_t)i * kTailBlock + c] = acc;
+        });
         __syncthreads();
-        blk_spmv<T, 0>(L.nc, L.rrp, L.rci, L.rv, r, nullptr, 0, vec(l + 1, 0));
+        blk_spmv<T, false>(L.nc, L.rrp, L.rci, L.rv, W.r, vec(l + 1).b);
         __syncthreads();
     }
-    blk_dense<T>(D.L[D.last].n, D.cinv, vec(D.last, 0), vec(D.last, 1));
+    blk_dense<T>(D.L[D.last].n, D.cinv, vec(D.last).b, vec(D.last).x);
     __syncthreads();
     for (int l = D.last - 1; l >= D.first; --l) {
         const BottomLevel<T> &L = D.L[l];
-        C<T> *x = vec(l, 1);
-        blk_spmv<T, 1>(L.n, L.prp, L.pci, L.pv, vec(l + 1, 1), nullptr, 0, x);
+        const BlkVec<T> W = vec(l);
+        blk_spmv<T, true>(L.n, L.prp, L.pci, L.pv, vec(l + 1).x, W.x);
         __syncthreads();
-        blk_sgs<T>(L, l == D.first ? nullptr : vec(l, 0), bid, x);
+        for (int k = 0; k < L.ncolors; ++k) {
+            blk_rows(L.coff[k], L.coff[k + 1], [&](int i) {
+                const size_t q = (size_t)i * kTailBlock + c;
+                C<T> lo = mk<T>(0, 0), up = mk<T>(0, 0);
+                blk_row_sum<T>(L.ci, L.v, L.rp[i], L.dpos[i], W.x, c, lo);
+                blk_row_sum<T>(L.ci, L.v, L.dpos[i] + 1, L.rp[i + 1], W.x, c, up);
+                const C<T> sl = csub(blk_rhs<T>(W.b, bid, i, c), lo);
+                W.e[q] = sl;
+                W.x[q] = cscale(csub(sl, up), (T)1 / L.diag[i]);
+            });
+            __syncthreads();
+        }
+        // (the last colour's rows have no U: they stay)
+        const int k0 = l == D.first ? kfirst : 0;
+        for (int k = L.ncolors - 2; k >= k0; --k) {
+            blk_rows(L.coff[k], L.coff[k + 1], [&](int i) {
+                const size_t q = (size_t)i * kTailBlock + c;
+                C<T> up = mk<T>(0, 0);
+                blk_row_sum<T>(L.ci, L.v, L.dpos[i] + 1, L.rp[i + 1], W.x, c, up);
+                W.x[q] = cscale(csub(W.e[q], up), (T)1 / L.diag[i]);
+            });
+            __syncthreads();
+        }
     }
 }
 
+// vectors of a level in the workspace: the first level needs no b, the coarsest no more
+// than b and x
+inline __host__ __device__ int tail_vectors(bool first, bool last) { return last ? 2 : first ? 3 : 4; }
+
 // Columns of the explicit sub-cycle of level D.first: work-group g forms
 // columns col0 + g kTailBlock .. + kTailBlock - 1 (those below n) with
-// blocks of its own (ws + g * ws_blk: b, x, r of each level in turn) and
-// stores them into the row-major n x n matrix out.
+// blocks of its own (ws + g * ws_blk: each level's vectors in turn) and stores
+// them, from the diagonal down, and their mirror into the row-major n x n matrix
+// out.
 template <class T>
 struct TailColumns {
     const BottomDesc<T> *Dp;
@@ -1400,16 +1451,20 @@ struct TailColumns {
         const BottomDesc<T> &D = *Dp;
         const int n = D.L[D.first].n, bid = col0 + bx * kTailBlock;
         C<T> *base = ws + (size_t)bx * ws_blk;
-        auto vec = [&](int l, int k) -> C<T> * {
-            size_t off = 0;
-            for (int q = D.first; q < l; ++q) off += 3 * (size_t)D.L[q].n;
-            return base + (off + (size_t)k * D.L[l].n) * kTailBlock;
+        auto vec = [&](int l) -> BlkVec<T> {
+            C<T> *p = base;
+            for (int q = D.first; q < l; ++q) p += tail_vectors(q == D.first, false) * (size_t)D.L[q].n * kTailBlock;
+            const size_t len = (size_t)D.L[l].n * kTailBlock;
+            if (l == D.first) return BlkVec<T>{nullptr, p, p + len, p + 2 * len};
+            return BlkVec<T>{p, p + len, p + 2 * len, p + 3 * len};
         };
         blk_cycle<T>(D, vec, bid);
-        const C<T> *x = vec(D.first, 1);
-        for (int t = threadIdx.x; t < n * kTailBlock; t += kBottomThreads) {
+        const C<T> *x = vec(D.first).x;
+        for (int t = bid * kTailBlock + threadIdx.x; t < n * kTailBlock; t += kTailThreads) {
             const int i = t / kTailBlock, col = bid + t % kTailBlock;
-            if (col < n) out[(size_t)i * n + col] = x[t];
+            if (col > i) continue;
+            out[(size_t)i * n + col] = x[t];
+            if (col < i) out[(size_t)col * n + i] = mk<T>(x[t].x, -x[t].y);
         }
     }
 };
@@ -2166,9 +2221,9 @@ void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const i
 // kSolverCycles V-cycles, its formation counted.  Microseconds, from
 // measurements: a level in patches 30, else 3.2 per dispatch of its 4 C, or 1.4
 // per step inside the bottom kernel; a dense product 4 and its bytes at 4 TB/s;
-// the formation 3 per step of the cycle, and its gathers, about 85 bytes per
+// the formation 3 per step of the cycle, and its gathers, about 46 bytes per
 // column and stored entry, at 7 TB/s (545 rows: 0.17 ms for 29 us a cycle; 195
-// rows: 0.04 for 16; 5 592 rows of 31 colours: 22 ms for 270 us, not taken).
+// rows: 0.04 for 16; 5 592 rows of 31 colours: 12 ms for 270 us, not taken).
 constexpr int kSolverCycles = 24, kSolverTail = 2048;
 
 static int solver_tail(const gl_precond *pre)
@@ -2185,7 +2240,7 @@ static int solver_tail(const gl_precond *pre)
         steps += 4 * L.ncolors + 3;
         nnz += L.A.nnz;
         const double dense = 4.0 + 16.0 * L.n * (double)L.n / 4e6;
-        const double form = 3.0 * steps + 85.0 * L.n * nnz / 7e6;
+        const double form = 3.0 * steps + 46.0 * L.n * nnz / 7e6;
         const double gain = kSolverCycles * (saved - dense) - form;
         if (gain > best_gain) {
             best = l;
@@ -2211,6 +2266,7 @@ static void fill_bottom(gl_precond *pre, BottomDesc<T> &D)
         B.ncolors = L.ncolors;
         B.rp = L.Aa.rp.get();
         B.ci = L.Aa.ci.get();
+        B.dpos = L.dpos.get();
         B.v = vals<T>(L.Aa);
         B.diag = dgn<T>(L);
         for (int c = 0; c <= L.ncolors && c <= kMaxColors && c < (int)L.coff.size(); ++c) B.coff[c] = L.coff[c];
@@ -2284,7 +2340,7 @@ void bottom_descriptors(gl_precond *pre, hipStream_t s)
         pre->tinv64.alloc((size_t)nt * nt);
         pre->tinv32.alloc((size_t)nt * nt);
         size_t col = 0;
-        for (int l = ex; l <= last; ++l) col += 3 * (size_t)pre->L[l].n;
+        for (int l = ex; l <= last; ++l) col += tail_vectors(l == ex, l == last) * (size_t)pre->L[l].n;
         pre->tws_col = col * kTailBlock;  // elements per block of columns
         const int nblk = (nt + kTailBlock - 1) / kTailBlock;
         const size_t fit = kTailWorkspace / (pre->tws_col * sizeof(double2));
@@ -2333,7 +2389,7 @@ static void tail_columns(gl_precond *pre, int ex, const Launch &L)
     const int nblk = (nt + kTailBlock - 1) / kTailBlock;
     for (int b0 = 0; b0 < nblk; b0 += pre->tws_cols) {
         const int nb = std::min(pre->tws_cols, nblk - b0);
-        L.run<TailColumns<double>, kBottomThreads>(
+        L.run<TailColumns<double>, kTailThreads>(
             nb, TailColumns<double>{D, pre->tws.get(), pre->tws_col, b0 * kTailBlock, nb, pre->tinv64.get()});
     }
     const int64_t nn = (int64_t)nt * nt;
