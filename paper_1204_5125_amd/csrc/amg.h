@@ -267,6 +267,7 @@ inline void launch_finalize(const double *partials, int nparts, int mode, Krylov
 }  // namespace glk
 
 struct gl_precond {
+    glk::Arena arena;              // the buffers of its first setup
     const gl_mesh *mesh = nullptr;
     uint64_t uid = 0;              // unique per handle (keys cached graphs)
     gl_amg_opts opts{};

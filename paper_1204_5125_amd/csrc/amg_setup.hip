@@ -80,15 +80,19 @@ __global__ void k_scan_add(int *out, const int *boff, const int *bsum, int n, in
 // Scratch of one symbolic phase, grown as needed and kept until it ends (an
 // allocation per use cost more than most of the kernels it served).
 struct SymTmp {
+    Arena arena;                  // of the work arrays (they do not belong to the handle)
     DevBuf<int> scan;             // tile sums and offsets
     DevBuf<int> a, b, c, d, e, f; // per-row work arrays
     DevBuf<int> flags;            // "undecided nodes are left" of a batch of rounds
     DevBuf<int> err;
 };
 
-static int *need(DevBuf<int> &b, size_t n)
+static int *need(SymTmp &T, DevBuf<int> &b, size_t n)
 {
-    if (b.count < n) b.alloc(n);
+    if (b.count < n) {
+        const ArenaScope own(&T.arena);
+        b.alloc(n);
+    }
     return b.get();
 }
 
@@ -108,7 +112,7 @@ static void scan_tiles(const int *in, int *out, int n, int *tmp, hipStream_t s)
 static int64_t scan_excl(const int *in, int *out, int n, SymTmp &T, hipStream_t s)
 {
     if (n <= 0) return 0;
-    scan_tiles(in, out, n, need(T.scan, 4 * ((size_t)n / kScanTile + 4) + 64), s);
+    scan_tiles(in, out, n, need(T, T.scan, 4 * ((size_t)n / kScanTile + 4) + 64), s);
     int total = 0;
     GLK_HIP(hipMemcpyAsync(&total, out + n, sizeof(int), hipMemcpyDeviceToHost, s));
     GLK_HIP(hipStreamSynchronize(s));
@@ -1618,7 +1622,7 @@ template <class Round>
 static void run_rounds(int n, SymTmp &T, hipStream_t s, const char *what, Round &&round)
 {
     constexpr int slots = 256;
-    int *flags = need(T.flags, slots), slot = 0;
+    int *flags = need(T, T.flags, slots), slot = 0;
     int64_t done = 0;
     for (;;) {
         if (done > (int64_t)n + 8) fail(GL_ERR_HIP, std::string(what) + " did not terminate");
@@ -1644,7 +1648,7 @@ static void colour_level(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         GLK_CHECK_LAUNCH();
         L.ncolors = n > 1 ? 2 : 1;
     } else {
-        int *err = need(T.err, 1);
+        int *err = need(T, T.err, 1);
         k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
         k_fill_int<<<nb, kBlock, 0, s>>>(L.color.get(), n, -1);
         run_rounds(n, T, s, "colouring", [&](int *flag) {
@@ -1652,7 +1656,7 @@ static void colour_level(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         });
         check_err(T.err, s, "colouring");
         // class sizes and the number of colours
-        int *hist = need(T.a, 257);
+        int *hist = need(T, T.a, 257);
         std::vector<int> h;
         int nc = 0;
         auto count = [&] {
@@ -1667,7 +1671,7 @@ static void colour_level(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         count();
         // iterated greedy: never more colours, often fewer (each colour costs
         // two dependent passes per symmetric sweep)
-        int *nw = need(T.b, n);
+        int *nw = need(T, T.b, n);
         for (int pass = 0; pass < kRecolourPasses; ++pass) {
             k_fill_int<<<nb, kBlock, 0, s>>>(nw, n, -1);
             for (int c = nc - 1; c >= 0; --c)
@@ -1682,7 +1686,7 @@ static void colour_level(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         L.cperm.alloc(n);
         L.coff.assign(nc + 1, 0);
         for (int c = 0; c < nc; ++c) L.coff[c + 1] = L.coff[c] + h[c];
-        int *bc = need(T.b, (size_t)nc * nb), *off = need(T.c, (size_t)nc * nb + 1);
+        int *bc = need(T, T.b, (size_t)nc * nb), *off = need(T, T.c, (size_t)nc * nb + 1);
         k_colour_count<<<nb, kBlock, 0, s>>>(n, L.color.get(), nb, nc, bc);
         scan_excl(bc, off, nc * nb, T, s);
         k_colour_place<<<nb, kBlock, 0, s>>>(n, L.color.get(), nb, off, L.cperm.get());
@@ -1696,8 +1700,8 @@ static int aggregate_level(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     Level &L = pre->L[l];
     const int n = L.n, nb = blocks_for(n);
     const int *rp = L.A.rp.get(), *ci = L.A.ci.get();
-    int *state = need(T.a, n), *rootA = need(T.b, n), *rootB = need(T.c, n), *flag = need(T.d, n);
-    int *id = need(T.e, (size_t)n + 1), *err = need(T.err, 1);
+    int *state = need(T, T.a, n), *rootA = need(T, T.b, n), *rootB = need(T, T.c, n), *flag = need(T, T.d, n);
+    int *id = need(T, T.e, (size_t)n + 1), *err = need(T, T.err, 1);
     k_fill_int<<<nb, kBlock, 0, s>>>(state, n, 0);
     k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
     run_rounds(n, T, s, "aggregation",
@@ -1724,7 +1728,7 @@ static void transfer_patterns(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     Level &Nx = pre->L[l + 1];
     const int n = L.n, nc = L.nc, nb = blocks_for(n);
     const int nbw = (nc + kRowWaves - 1) / kRowWaves;  // a wave per coarse row
-    int *cnt = need(T.a, std::max(n, nc)), *err = need(T.err, 1);
+    int *cnt = need(T, T.a, std::max(n, nc)), *err = need(T, T.err, 1);
     k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
     // P: n x nc
     L.P.n = n;
@@ -1743,7 +1747,7 @@ static void transfer_patterns(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     GLK_CHECK_LAUNCH();
     alloc_rowptr(L.R, cnt, T, s);
     L.rsrc.alloc(std::max(1, L.R.nnz));
-    int *fill = need(T.b, nc), *tci = need(T.c, std::max(1, L.R.nnz)), *tsrc = need(T.d, std::max(1, L.R.nnz));
+    int *fill = need(T, T.b, nc), *tci = need(T, T.c, std::max(1, L.R.nnz)), *tsrc = need(T, T.d, std::max(1, L.R.nnz));
     k_fill_int<<<blocks_for(nc), kBlock, 0, s>>>(fill, nc, 0);
     k_transpose_fill<<<nb, kBlock, 0, s>>>(n, L.P.rp.get(), L.P.ci.get(), L.R.rp.get(), fill, tci, tsrc);
     k_sort_rows<<<nbw, kBlock, 0, s>>>(nc, L.R.rp.get(), tci, tsrc, L.R.ci.get(), L.rsrc.get());
@@ -1772,7 +1776,7 @@ static void transfer_patterns(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     GLK_CHECK_LAUNCH();
     // the pairs of the upper triangle for the numeric Galerkin product
     const int nnzc = Nx.A.nnz;
-    int *pc = need(T.b, std::max(1, nnzc));
+    int *pc = need(T, T.b, std::max(1, nnzc));
     k_rap_pairs<<<nbw, kBlock, 0, s>>>(nc, L.R.rp.get(), L.R.ci.get(), L.AP.rp.get(), L.AP.ci.get(), Nx.A.rp.get(),
                                        Nx.A.ci.get(), pc, nullptr, nullptr);
     GLK_CHECK_LAUNCH();
@@ -1837,13 +1841,13 @@ static void permuted_copy(const Csr &M, const int *rowperm, const int *colmap, C
 {
     out.n = M.n;
     out.m = M.m;
-    int *cnt = need(T.a, std::max(1, M.n));
+    int *cnt = need(T, T.a, std::max(1, M.n));
     k_perm_count<<<blocks_for(M.n), kBlock, 0, s>>>(M.n, rowperm, M.rp.get(), cnt);
     GLK_CHECK_LAUNCH();
     alloc_rowptr(out, cnt, T, s);
     map.alloc(std::max(1, out.nnz));
-    int *fci = sorted ? need(T.b, std::max(1, out.nnz)) : out.ci.get();
-    int *fmap = sorted ? need(T.c, std::max(1, out.nnz)) : map.get();
+    int *fci = sorted ? need(T, T.b, std::max(1, out.nnz)) : out.ci.get();
+    int *fmap = sorted ? need(T, T.c, std::max(1, out.nnz)) : map.get();
     k_perm_fill<<<blocks_for(M.n), kBlock, 0, s>>>(M.n, rowperm, M.rp.get(), M.ci.get(), colmap, out.rp.get(), fci, fmap);
     if (sorted)
         k_sort_rows<<<(M.n + kRowWaves - 1) / kRowWaves, kBlock, 0, s>>>(M.n, out.rp.get(), fci, fmap, out.ci.get(),
@@ -1899,7 +1903,7 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
                 Csr &B = L.Rb;
                 B.n = L.Ra.n;
                 B.m = 2 * g.npair;
-                int *cnt = need(T.a, std::max(1, B.n));
+                int *cnt = need(T, T.a, std::max(1, B.n));
                 k_black_count<<<blocks_for(B.n), kBlock, 0, s>>>(B.n, g, L.Ra.rp.get(), L.Ra.ci.get(), cnt);
                 GLK_CHECK_LAUNCH();
                 alloc_rowptr(B, cnt, T, s);
@@ -1912,7 +1916,7 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
                 Csr &Q = L.Pb;
                 Q.n = g.npair;
                 Q.m = L.Pa.m;
-                int *qcnt = need(T.a, std::max(1, Q.n));
+                int *qcnt = need(T, T.a, std::max(1, Q.n));
                 k_pblack_count<<<blocks_for(Q.n), kBlock, 0, s>>>(g, L.Pa.rp.get(), qcnt);
                 GLK_CHECK_LAUNCH();
                 alloc_rowptr(Q, qcnt, T, s);
@@ -1926,7 +1930,7 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
         }
         if (generic) {
             // padded colour blocks for the Gauss-Seidel sweeps
-            int *row0 = need(T.a, (size_t)L.ncolors + 1), *wid = need(T.b, L.ncolors);
+            int *row0 = need(T, T.a, (size_t)L.ncolors + 1), *wid = need(T, T.b, L.ncolors);
             to_device(row0, L.coff, s);
             k_row_widths<<<L.ncolors, kBlock, 0, s>>>(L.Aa.rp.get(), row0, wid);
             GLK_CHECK_LAUNCH();
@@ -2007,8 +2011,8 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         t.k[0] = (int)std::max(1.0, std::min(tiles, std::round(std::sqrt(tiles * ext[0] / std::max(ext[1], 1e-300)))));
         t.k[1] = std::max(1, (int)std::round(tiles / t.k[0]));
         const int nt = t.k[0] * t.k[1];
-        int *tile = need(T.a, n), *cnt = need(T.b, nt), *trp = need(T.c, (size_t)nt + 1);
-        int *rows = need(T.d, n), *srt = need(T.e, 2 * (size_t)n), *err = need(T.err, 1);
+        int *tile = need(T, T.a, n), *cnt = need(T, T.b, nt), *trp = need(T, T.c, (size_t)nt + 1);
+        int *rows = need(T, T.d, n), *srt = need(T, T.e, 2 * (size_t)n), *err = need(T, T.err, 1);
         k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
         k_fill_int<<<blocks_for(nt), kBlock, 0, s>>>(cnt, nt, 0);
         k_tile_of<<<nb, kBlock, 0, s>>>(n, L.perm.get(), L.origin.get(), t, tile);
@@ -2038,7 +2042,7 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
             S.np = nt;
             S.v64.alloc((size_t)nt * S.W * NR);
             S.v32.alloc((size_t)nt * S.W * NR);
-            int *row0 = need(T.a, 2), *wid = need(T.b, 1);
+            int *row0 = need(T, T.a, 2), *wid = need(T, T.b, 1);
             to_device(row0, std::vector<int>{0, n}, s);
             k_row_widths<<<1, kBlock, 0, s>>>(L.Pa.rp.get(), row0, wid);
             GLK_CHECK_LAUNCH();
@@ -2065,8 +2069,9 @@ void precond_symbolic(gl_precond *pre, hipStream_t s)
     L0.n = n0;
     L0.A.n = L0.A.m = n0;
     SymTmp T;
+    T.arena.spare = m->spare;
     {
-        int *cnt = need(T.a, n0);
+        int *cnt = need(T, T.a, n0);
         if (m->g.simplicial) k_l0s_count<<<nb0, kBlock, 0, s>>>(n0, m->g.rp, cnt);
         else if (m->g.dim == 2) k_l0_count<2><<<nb0, kBlock, 0, s>>>(m->g, cnt);
         else k_l0_count<3><<<nb0, kBlock, 0, s>>>(m->g, cnt);
@@ -2250,7 +2255,11 @@ gl_status gl_precond_setup(const gl_mesh *mesh, const void *psi, const gl_amg_op
                 pre->uid = new_precond_uid();
                 pre->mesh = mesh;
                 pre->opts = *opts;
-                precond_symbolic(pre, s);
+                {
+                    pre->arena.spare = mesh->spare;
+                    const ArenaScope small(&pre->arena);
+                    precond_symbolic(pre, s);
+                }
                 precond_numeric(pre, (const double2 *)psi, s);
             } catch (...) {
                 delete pre;

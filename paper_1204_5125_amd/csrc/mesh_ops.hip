@@ -34,6 +34,19 @@ Allocator &allocator()
     return a;
 }
 
+static thread_local Arena *t_arena = nullptr;
+
+void *arena_take(size_t bytes)
+{
+    if (!t_arena) return nullptr;
+    Arena *a = t_arena;
+    const ArenaScope plain(nullptr);  // its chunks are buffers too
+    return a->take(bytes);
+}
+
+ArenaScope::ArenaScope(Arena *a) : before(t_arena) { t_arena = a; }
+ArenaScope::~ArenaScope() { t_arena = before; }
+
 RedSlot red_slot(const gl_mesh *m, int k)
 {
     const size_t per = m->partials.count / kMaxSlots;

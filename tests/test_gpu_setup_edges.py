@@ -84,3 +84,39 @@ def test_too_long_coarse_row_refused(glnk):
     psi = torch.ones(mesh.n, dtype=torch.complex128, device="cuda")
     with pytest.raises(glnk.GlnkError, match="GL_ERR_UNSUPPORTED"):
         glnk.Precond(mesh, psi, max_coarse=16)
+
+
+def test_memory_given_back_and_taken_again(glnk):
+    """Hierarchies built in the memory that others of the mesh gave back, with some
+    still alive beside them, and one that outlives its mesh: each applies as one
+    on a mesh of its own does, to the bit."""
+    shapes = [(33, 33), (70, 41), (129, 65)]
+    r = [torch.from_numpy(inputs.random_complex(s[0] * s[1], seed=7)).cuda() for s in shapes]
+    psi = [[torch.from_numpy(inputs.random_phase_state(s[0] * s[1], seed=q)).cuda() for q in (1, 2, 3)] for s in shapes]
+    mesh_of = lambda s: glnk.Mesh(2, s, tuple(0.25 * (n - 1) for n in s), mu=0.6)  # noqa: E731
+
+    def applied(pre, b):
+        z = torch.empty_like(b)
+        pre.apply(b, z)
+        return z
+
+    for k, s in enumerate(shapes):
+        want = []
+        for p in psi[k]:
+            m = mesh_of(s)
+            pre = glnk.Precond(m, p, max_coarse=16)
+            want.append(applied(pre, r[k]))
+            pre.close()
+            m.close()
+        m = mesh_of(s)
+        kept = glnk.Precond(m, psi[k][0], max_coarse=16)
+        for q in (1, 2, 1):
+            pre = glnk.Precond(m, psi[k][q], max_coarse=16)
+            assert torch.equal(applied(pre, r[k]), want[q])
+            pre.close()
+        assert torch.equal(applied(kept, r[k]), want[0])
+        last = glnk.Precond(m, psi[k][2], max_coarse=16)
+        kept.close()
+        assert torch.equal(applied(last, r[k]), want[2])
+        m.close()
+        last.close()
