@@ -769,31 +769,29 @@ struct Diag {
 // normalisation of each iterate is folded into the next step.
 constexpr int kRhoSteps = 20;
 
+__device__ __forceinline__ double2 pw_start(int i)
+{
+    const double a = (double)fmix32((uint32_t)i ^ 0x2545F491u) / 4294967296.0 - 0.5;
+    const double b = (double)fmix32((uint32_t)i ^ 0x6C8E9CF5u) / 4294967296.0 - 0.5;
+    return make_double2(a, b);
+}
+
 struct PwStart {
     int n;
     double2 *x;
-    RedSlot slot;
     __device__ void operator()(int, int) const
     {
-        __shared__ double sm[kBlock / 64];
         const int i = blockIdx.x * kBlock + threadIdx.x;
-        double part = 0.0;
-        if (i < n) {
-            const double a = (double)fmix32((uint32_t)i ^ 0x2545F491u) / 4294967296.0 - 0.5;
-            const double b = (double)fmix32((uint32_t)i ^ 0x6C8E9CF5u) / 4294967296.0 - 0.5;
-            x[i] = make_double2(a, b);
-            part = a * a + b * b;
-        }
-        block_reduce_store(part, slot, sm, blockIdx.x);
+        if (i < n) x[i] = pw_start(i);
     }
 };
 
-// y = D^-1 A x / ||x|| (||x||^2 in *xn2), partial sums of |y|^2; kPwLanes
-// lanes share a row (lane j takes entries j, j + kPwLanes, ... in order, then
-// a fixed butterfly), so long coarse rows are not one serial chain of gathers.
-// The grid is at most the partial-sum slot's size: a block strides over the
-// rows by the grid (the same iterations for all its threads) and stores one
-// partial.
+// y = D^-1 A x, divided by ||x|| where xn2 gives ||x||^2, and partial sums of
+// |y|^2 where the slot is set; kPwLanes lanes share a row (lane j takes entries j,
+// j + kPwLanes, ... in order, then a fixed butterfly), so long coarse rows are not
+// one serial chain of gathers.  The grid is at most the partial-sum slot's size: a
+// block strides over the rows by the grid (the same iterations for all its threads)
+// and stores one partial.
 constexpr int kPwLanes = 8;
 
 struct PwStep {
@@ -809,7 +807,7 @@ struct PwStep {
     {
         __shared__ double sm[kBlock / 64];
         const int64_t total = (int64_t)n * kPwLanes;
-        const double scale = 1.0 / sqrt(*xn2);
+        const double scale = xn2 ? 1.0 / sqrt(*xn2) : 1.0;
         double part = 0.0;
         for (int64_t base = (int64_t)blockIdx.x * kBlock; base < total; base += (int64_t)gridDim.x * kBlock) {
             const int64_t g = base + threadIdx.x;
@@ -829,7 +827,7 @@ struct PwStep {
                 part += cabs2(yi);
             }
         }
-        block_reduce_store(part, slot, sm, blockIdx.x);
+        if (slot.partials) block_reduce_store(part, slot, sm, blockIdx.x);
     }
 };
 
@@ -855,11 +853,11 @@ struct PwStepL0 {
             node_coords<DIM>(g.N, i, c);
             const double di = diag[i];
             const double2 acc = cadd(cscale(x[i], di), khat_offdiag<DIM, double>(g, i, c, x, U));
-            const double2 yi = cscale(acc, 1.0 / (di * sqrt(*xn2)));
+            const double2 yi = cscale(acc, 1.0 / (xn2 ? di * sqrt(*xn2) : di));
             y[i] = yi;
             part = cabs2(yi);
         }
-        block_reduce_store(part, slot, sm, blockIdx.x);
+        if (slot.partials) block_reduce_store(part, slot, sm, blockIdx.x);
     }
 };
 
@@ -872,6 +870,85 @@ struct PwRho {
     }
 };
 
+// The estimate is the growth of the last step, so only the vector before it has
+// to be normalised.  The one halfway is too, to keep the squares in range: rho is
+// at least 1 (the mean eigenvalue of D^-1 A), and 10 steps stay below 1e154 up to
+// rho = 2e15.  (A norm per step was a second dispatch per step: 513^2, four levels,
+// 1.35 ms per numeric setup, now 1.04; 97x81x65 2.70, now 2.47.)
+// |y|^2 of step k is wanted
+__host__ __device__ constexpr bool rho_normed(int k) { return k == kRhoSteps / 2 || k >= kRhoSteps - 1; }
+
+// The whole estimate of a small level by one work-group, from its CSR matrix: LPR
+// lanes per row, the matrix in registers (kPwSlots rows of kPwEntries entries per
+// thread), the vector in LDS.  A step is a few LDS reads and two barriers (0.8 us)
+// where a dispatch takes 4-5 with its gap: 33^2, two levels, 0.38 ms per numeric
+// setup with a dispatch per step, now 0.29.
+constexpr int kPwThreads = 1024, kPwSlots = 4, kPwEntries = 4;
+
+template <int LPR>
+struct PwSmall {
+    int n;
+    const int *rp, *ci;
+    const double2 *v;
+    const double *diag;
+    double *rho;
+    __device__ void operator()(int, int) const
+    {
+        __shared__ double2 x[kPwThreads * kPwSlots / LPR];
+        __shared__ double sm[kPwThreads / 64], norm;
+        double2 a[kPwSlots][kPwEntries], y[kPwSlots];
+        int j[kPwSlots][kPwEntries];
+        double w[kPwSlots];
+        const int lane = threadIdx.x % LPR;
+#pragma unroll
+        for (int s = 0; s < kPwSlots; ++s) {
+            const int i = (s * kPwThreads + threadIdx.x) / LPR;
+            const int b = i < n ? rp[i] : 0, e = i < n ? rp[i + 1] : 0;
+            w[s] = i < n ? 1.0 / diag[i] : 0.0;
+#pragma unroll
+            for (int k = 0; k < kPwEntries; ++k) {
+                const int p = b + lane + k * LPR;
+                j[s][k] = p < e ? ci[p] : 0;
+                a[s][k] = p < e ? v[p] : make_double2(0.0, 0.0);
+            }
+        }
+        for (int i = threadIdx.x; i < n; i += kPwThreads) x[i] = pw_start(i);
+        __syncthreads();
+        double scale = 1.0;
+        for (int step = 1; step <= kRhoSteps; ++step) {
+            double part = 0.0;
+#pragma unroll
+            for (int s = 0; s < kPwSlots; ++s) {
+                double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+                for (int k = 0; k < kPwEntries; ++k) acc = cadd(acc, cmul(a[s][k], x[j[s][k]]));
+#pragma unroll
+                for (int o = LPR / 2; o > 0; o >>= 1) {
+                    acc.x += __shfl_xor(acc.x, o, 64);
+                    acc.y += __shfl_xor(acc.y, o, 64);
+                }
+                y[s] = cscale(acc, scale * w[s]);
+                if (lane == 0) part += cabs2(y[s]);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < kPwSlots; ++s) {
+                const int i = (s * kPwThreads + threadIdx.x) / LPR;
+                if (i < n && lane == 0) x[i] = y[s];
+            }
+            scale = 1.0;
+            if (rho_normed(step)) {
+                const double s2 = block_sum(part, sm);
+                if (threadIdx.x == 0) norm = sqrt(s2);
+                __syncthreads();
+                scale = 1.0 / norm;
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *rho = norm;
+    }
+};
+
 static void rho_estimate(gl_precond *pre, Level &lev, const Launch &L)
 {
     const gl_mesh *m = pre->mesh;
@@ -879,8 +956,19 @@ static void rho_estimate(gl_precond *pre, Level &lev, const Launch &L)
     const RedSlot slot = red_slot(m, 0);
     double2 *x = pre->vin.get(), *y = pre->cyc_r.get();
     double *nrm = pre->pwn.get();
-    L.run(nb, PwStart{n, x, slot});
-    launch_finalize(slot.partials, nb, FIN_STORE, nullptr, nrm, nullptr, L);
+    const int width = lev.ewidth.empty() ? 2 * m->g.dim + 1 : *std::max_element(lev.ewidth.begin(), lev.ewidth.end());
+    const auto small = [&](auto lpr) {
+        constexpr int LPR = decltype(lpr)::value;
+        if (width > LPR * kPwEntries || (int64_t)n * LPR > kPwThreads * kPwSlots) return false;
+        L.run<PwSmall<LPR>, kPwThreads>(
+            1, PwSmall<LPR>{n, lev.A.rp.get(), lev.A.ci.get(), lev.A.v64.get(), lev.diag64.get(), lev.rho.get()});
+        return true;
+    };
+    if (small(std::integral_constant<int, 2>{}) || small(std::integral_constant<int, 4>{}) ||
+        small(std::integral_constant<int, 8>{}) || small(std::integral_constant<int, 16>{}) ||
+        small(std::integral_constant<int, 32>{}))
+        return;
+    L.run(nb, PwStart{n, x});
     // level 0 of a grid as the stencil, every other level (and level 0 of a
     // simplicial mesh) through its CSR matrix
     const bool l0 = &lev == &pre->L[0] && !m->g.simplicial;
@@ -888,14 +976,16 @@ static void rho_estimate(gl_precond *pre, Level &lev, const Launch &L)
     // CSR levels: kPwLanes threads per row, at most one partial per level-0 block
     const int nbl = std::min(blocks_for((int64_t)n * kPwLanes), blocks_for(m->g.n));
     for (int k = 1; k <= kRhoSteps; ++k) {
-        const double *xn2 = nrm + ((k - 1) & 1);
+        const double *xn2 = k > 1 && rho_normed(k - 1) ? nrm + ((k - 1) & 1) : nullptr;
+        const RedSlot sum = rho_normed(k) ? slot : RedSlot{nullptr};
         if (l0 && m->g.dim == 2)
-            L.run(nb, PwStepL0<2>{g, link_tab<double>(m), lev.diag64.get(), x, xn2, y, slot});
+            L.run(nb, PwStepL0<2>{g, link_tab<double>(m), lev.diag64.get(), x, xn2, y, sum});
         else if (l0)
-            L.run(nb, PwStepL0<3>{g, link_tab<double>(m), lev.diag64.get(), x, xn2, y, slot});
+            L.run(nb, PwStepL0<3>{g, link_tab<double>(m), lev.diag64.get(), x, xn2, y, sum});
         else
-            L.run(nbl, PwStep{n, lev.A.rp.get(), lev.A.ci.get(), lev.A.v64.get(), lev.diag64.get(), x, xn2, y, slot});
-        launch_finalize(slot.partials, l0 ? nb : nbl, FIN_STORE, nullptr, nrm + (k & 1), nullptr, L);
+            L.run(nbl, PwStep{n, lev.A.rp.get(), lev.A.ci.get(), lev.A.v64.get(), lev.diag64.get(), x, xn2, y, sum});
+        if (rho_normed(k))
+            launch_finalize(slot.partials, l0 ? nb : nbl, FIN_STORE, nullptr, nrm + (k & 1), nullptr, L);
         std::swap(x, y);
     }
     L.run<PwRho, 64>(1, PwRho{nrm + (kRhoSteps & 1), lev.rho.get()});
