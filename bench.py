@@ -37,7 +37,7 @@ RTOL = 1e-10
 L0_TILED_NAME = "L0 Gauss-Seidel in LDS tiles (L0PreTile, L0PostTile)"
 KERNEL_NAMES = {1: "MinresJapply", 2: "L0 Gauss-Seidel sweeps (L0PreBlack, L0Sweep, L0Last)",
                 3: "L0Residual", 4: "level-0 transfers (CsrSpmv restriction, L0ProlongBlack)", 5: "MinresVupdate", 6: "k_minres_wx",
-                7: "GlResidual", 8: "EllSgs (Gauss-Seidel colour sweep, levels >= 1)"}
+                7: "GlResidual", 8: "SgsPass (Gauss-Seidel colour pass, levels >= 1)"}
 
 
 def log(msg):

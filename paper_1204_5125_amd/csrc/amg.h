@@ -92,6 +92,7 @@ struct Level {
     // colour c has ewidth[c] entries at eoff[c] + (r - coff[c]) * ewidth[c];
     // padding entries point at the row itself with value 0
     std::vector<int> ewidth, eoff;
+    std::vector<int> elow, eup;     // entries before the diagonal at most, entries up to it at least
     DevBuf<int> eci, emap;          // emap: entry of Aa, or -1 for padding
     DevBuf<double2> ev64;
     DevBuf<float2> ev32;
@@ -101,6 +102,8 @@ struct Level {
     // node of colour c in red-black pair t at c * npair + t, 2 npair entries)
     DevBuf<double2> b64, x64, r64;
     DevBuf<float2> b32, x32, r32;
+    DevBuf<double2> t64;        // sweeps by colour passes
+    DevBuf<float2> t32;
 };
 
 // One level as seen by the bottom kernel (device-resident descriptor).

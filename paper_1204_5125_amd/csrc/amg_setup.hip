@@ -733,19 +733,31 @@ __global__ __launch_bounds__(kBlock) void k_colour_hist(int n, const int *__rest
         if (h[c]) atomicAdd(&hist[c], h[c]);
 }
 
-// longest row of rows row0[c] .. row0[c + 1] - 1 (block c)
-__global__ __launch_bounds__(kBlock) void k_row_widths(const int *__restrict__ rp, const int *__restrict__ row0,
-                                                       int *__restrict__ width)
+// of rows row0[c] .. row0[c + 1] - 1 (block c of C): the longest, and where the
+// places of their diagonal entries are given, at C + c the most entries before it and
+// at 2 C + c the least up to and with it
+__global__ __launch_bounds__(kBlock) void k_row_widths(const int *__restrict__ rp, const int *__restrict__ dpos,
+                                                       const int *__restrict__ row0, int *__restrict__ width)
 {
-    __shared__ int sm[kBlock / 64];
-    int m = 1;
-    for (int r = row0[blockIdx.x] + threadIdx.x; r < row0[blockIdx.x + 1]; r += kBlock) m = max(m, rp[r + 1] - rp[r]);
-    for (int d = 32; d > 0; d >>= 1) m = max(m, __shfl_xor(m, d, 64));
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
+    __shared__ int sm[3][kBlock / 64];
+    int m[3] = {1, 0, 0};  // (the third is INT_MAX - what is wanted, a minimum)
+    for (int r = row0[blockIdx.x] + threadIdx.x; r < row0[blockIdx.x + 1]; r += kBlock) {
+        m[0] = max(m[0], rp[r + 1] - rp[r]);
+        if (dpos) {
+            m[1] = max(m[1], dpos[r] - rp[r]);
+            m[2] = max(m[2], INT_MAX - (dpos[r] - rp[r] + 1));
+        }
+    }
+    for (int d = 32; d > 0; d >>= 1)
+        for (int q = 0; q < 3; ++q) m[q] = max(m[q], __shfl_xor(m[q], d, 64));
+    if ((threadIdx.x & 63) == 0)
+        for (int q = 0; q < 3; ++q) sm[q][threadIdx.x >> 6] = m[q];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < kBlock / 64; ++k) m = max(m, sm[k]);
-        width[blockIdx.x] = m;
+    if (threadIdx.x < (dpos ? 3 : 1)) {
+        int w = sm[threadIdx.x][0];
+        for (int k = 1; k < kBlock / 64; ++k) w = max(w, sm[threadIdx.x][k]);
+        if (threadIdx.x == 2) w = INT_MAX - w;
+        width[threadIdx.x * gridDim.x + blockIdx.x] = w;
     }
 }
 
@@ -1899,6 +1911,10 @@ static void alloc_values(gl_precond *pre)
         L.b32.alloc(nv);
         L.x32.alloc(nv);
         L.r32.alloc(nv);
+        if (l > 0 || simp) {
+            L.t64.alloc(nv);
+            L.t32.alloc(nv);
+        }
         if (l == 0 && !simp) {
             L.hs64.alloc(ns);
             L.hs32.alloc(ns);
@@ -2020,11 +2036,14 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
         }
         if (generic) {
             // padded colour blocks for the Gauss-Seidel sweeps
-            int *row0 = need(T, T.a, (size_t)L.ncolors + 1), *wid = need(T, T.b, L.ncolors);
+            int *row0 = need(T, T.a, (size_t)L.ncolors + 1), *wid = need(T, T.b, 3 * (size_t)L.ncolors);
             to_device(row0, L.coff, s);
-            k_row_widths<<<L.ncolors, kBlock, 0, s>>>(L.Aa.rp.get(), row0, wid);
+            k_row_widths<<<L.ncolors, kBlock, 0, s>>>(L.Aa.rp.get(), L.dpos.get(), row0, wid);
             GLK_CHECK_LAUNCH();
-            L.ewidth = to_host(wid, L.ncolors, s);
+            L.ewidth = to_host(wid, 3 * (size_t)L.ncolors, s);
+            L.elow.assign(L.ewidth.begin() + L.ncolors, L.ewidth.begin() + 2 * L.ncolors);
+            L.eup.assign(L.ewidth.begin() + 2 * L.ncolors, L.ewidth.end());
+            L.ewidth.resize(L.ncolors);
             L.eoff.assign(L.ncolors + 1, 0);
             for (int c = 0; c < L.ncolors; ++c) L.eoff[c + 1] = L.eoff[c] + L.ewidth[c] * (L.coff[c + 1] - L.coff[c]);
             const int ne = std::max(1, L.eoff[L.ncolors]);
@@ -2134,7 +2153,7 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
             S.v32.alloc((size_t)nt * S.W * NR);
             int *row0 = need(T, T.a, 2), *wid = need(T, T.b, 1);
             to_device(row0, std::vector<int>{0, n}, s);
-            k_row_widths<<<1, kBlock, 0, s>>>(L.Pa.rp.get(), row0, wid);
+            k_row_widths<<<1, kBlock, 0, s>>>(L.Pa.rp.get(), nullptr, row0, wid);
             GLK_CHECK_LAUNCH();
             S.PW = read_int(wid, s);
             const size_t np = (size_t)n * S.PW;

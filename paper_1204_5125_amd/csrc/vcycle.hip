@@ -640,105 +640,114 @@ __device__ __forceinline__ C<T> lanes_sum(C<T> s)
     return s;
 }
 
-// Gauss-Seidel update of one colour stored as a padded block (ELL, width W).
-// The gate flag is loaded alongside the data and checked only before the
-// store, so its latency overlaps the row loads.
-template <class T, int LPR>
-struct EllSgs {
+// Symmetric Gauss-Seidel sweeps on a level in colour order, A = L + D + U by that
+// order.  What a pass needs of a row is the part whose product is not known yet:
+//   down, from zero  forward   t = D^-1 (b - L t)
+//                    backward  e = D^-1 U x,  x = t - e
+//                    residual  t = b - A x = L e
+//   up               right-hand side of the forward half  r = b - U x
+//                    forward   t = D^-1 (r - L t), then r = b - L t
+//                    backward  x = D^-1 (r - U x)
+// (e is kept in r.)  That is three reads of the matrix a cycle instead of five, and a
+// pass writes a vector that it reads only at rows already final, so nothing is
+// updated in place.  The rows are padded blocks per colour (ELL), sorted by column:
+// the lower part of a row of colour c lies within its first elow[c] entries, the
+// upper part from entry eup[c] on.
+// A pass of a few thousand rows is bound by its launch and two dependent trips to
+// memory (5.5-6 us), one of a large level by the rows' traffic.  us per MINRES
+// iteration against whole rows updated in place and a residual of its own: 65^3 FP64
+// 332 -> 316, 97^3 FP32 1083 -> 910, 129^3 FP32 858 -> 836 and FP64 1097 -> 1022,
+// 161^3 FP32 1916 -> 1632.  (Two colours per dispatch, the second forming the values
+// it needs of the first itself: 97^3 1942, 129^3 FP32 1340.)
+enum { SGS_FWD0 = 0, SGS_FWD = 1, SGS_BWD0 = 2, SGS_BWD = 3 };
+
+// One colour: its rows and the entries [lo, hi) of them that hold the part.  LPR
+// lanes share a row, with kSgsBatch entries of each in flight; the gate is loaded
+// alongside the data and checked only before the store.
+constexpr int kSgsBatch = 4;
+
+template <class T, int LPR, int MODE>
+struct SgsPass {
     const int *eci;
     const C<T> *ev;
-    int W;
+    int W, lo, hi, row0, cnt;
     const T *diag;
-    int row0, count;
     const C<T> *b;
-    C<T> *x;
+    C<T> *x, *r, *t;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
+        constexpr bool fwd = MODE == SGS_FWD0 || MODE == SGS_FWD;
         const int go = gate ? *gate : 1;
-        const int t = bx * kBlock + threadIdx.x;
-        const int r = t / LPR, lane = t % LPR;
-        const bool act = r < count;
-        const int i = row0 + (act ? r : 0);
-        // the row's b and diagonal are loaded before the gathers (they do not
-        // depend on them), so the store waits for one memory round trip less
+        const int g = bx * kBlock + threadIdx.x;
+        const int row = g / LPR, lane = g % LPR;
+        const bool act = row < cnt;
+        const int i = row0 + (act ? row : 0);
+        // the row's own terms do not depend on the gathers
         const bool own = act && lane == 0;
-        const C<T> bi = own ? b[i] : mk<T>(0, 0);
-        const T di = own ? diag[i] : (T)1;
+        C<T> p = mk<T>(0, 0), q = p;
+        T d = (T)1;
+        if (own) {
+            d = diag[i];
+            p = MODE == SGS_FWD0 ? b[i] : MODE == SGS_BWD0 ? t[i] : r[i];
+            if (MODE == SGS_FWD) q = b[i];
+        }
+        const C<T> *from = fwd ? t : x;
         C<T> s = mk<T>(0, 0);
         if (act) {
-            const size_t base = (size_t)r * W;
-            for (int k = lane; k < W; k += LPR) {
-                const int j = eci[base + k];
-                if (j != i) s = cadd(s, cmul(ev[base + k], x[j]));
+            const size_t base = (size_t)row * W;
+            for (int k = lo + lane; k < hi; k += kSgsBatch * LPR) {
+                int c[kSgsBatch];
+                C<T> a[kSgsBatch], v[kSgsBatch];
+#pragma unroll
+                for (int u = 0; u < kSgsBatch; ++u) {
+                    const int e = min(k + u * LPR, hi - 1);
+                    c[u] = eci[base + e];
+                    a[u] = ev[base + e];
+                }
+#pragma unroll
+                for (int u = 0; u < kSgsBatch; ++u) v[u] = from[c[u]];
+#pragma unroll
+                for (int u = 0; u < kSgsBatch; ++u)
+                    if (k + u * LPR < hi && (fwd ? c[u] < row0 : c[u] >= row0 + cnt)) s = cadd(s, cmul(a[u], v[u]));
             }
         }
         s = lanes_sum<T, LPR>(s);
-        if (own && go) x[i] = cscale(csub(bi, s), (T)1 / di);
-    }
-};
-
-// The first two passes of a sweep from x = 0, and the zero start, in one
-// dispatch (rows are colour-ordered): colour 0 gets x = b / a_ii, colour 1
-// its Gauss-Seidel update from those values (evaluated on the fly from b and
-// the diagonal), every other row x = 0.  Same arithmetic as the three
-// separate steps.
-template <class T, int LPR>
-struct EllSgsStart {
-    const int *eci;  // colour-1 block
-    const C<T> *ev;
-    int W;
-    const T *diag;
-    int c1, c2, n;   // colour 0 = rows [0, c1), colour 1 = [c1, c2)
-    const C<T> *b;
-    C<T> *x;
-    const int *gate;
-    __device__ void operator()(int bx, int) const
-    {
-        const int go = gate ? *gate : 1;
-        const int t = bx * kBlock + threadIdx.x;
-        const int r = t / LPR, lane = t % LPR;
-        const bool valid = r < n, one = valid && r >= c1 && r < c2;
-        const bool own = valid && lane == 0 && r < c2;
-        const C<T> br = own ? b[r] : mk<T>(0, 0);
-        const T dr = own ? diag[r] : (T)1;
-        C<T> s = mk<T>(0, 0);
-        if (one) {
-            const size_t base = (size_t)(r - c1) * W;
-            for (int k = lane; k < W; k += LPR) {
-                const int j = eci[base + k];
-                if (j != r && j < c1) s = cadd(s, cmul(ev[base + k], cscale(b[j], (T)1 / diag[j])));
-            }
-        }
-        s = lanes_sum<T, LPR>(s);
-        if (valid && lane == 0 && go) {
-            if (r < c1) x[r] = cscale(br, (T)1 / dr);
-            else if (r < c2) x[r] = cscale(csub(br, s), (T)1 / dr);
-            else x[r] = mk<T>(0, 0);
+        if (!own || !go) return;
+        const T w = (T)1 / d;
+        if (MODE == SGS_BWD0) {
+            const C<T> e = cscale(s, w);
+            r[i] = e;
+            x[i] = csub(p, e);
+        } else {
+            (fwd ? t : x)[i] = cscale(csub(p, s), w);
+            if (MODE == SGS_FWD) r[i] = csub(q, s);
         }
     }
 };
 
-// r = b - A x
-template <class T, int LPR>
-struct CsrResidual {
+// y = L e (UP = 0) or y = b - U x (UP = 1) from the sorted rows
+template <class T, int LPR, int UP>
+struct SgsProduct {
     int n;
-    const int *rp, *ci;
+    const int *rp, *ci, *dpos;
     const C<T> *v, *b, *x;
-    C<T> *r;
+    C<T> *y;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
         GATE_LOAD();
-        const int t = bx * kBlock + threadIdx.x;
-        const int i = t / LPR, lane = t % LPR;
+        const int g = bx * kBlock + threadIdx.x;
+        const int i = g / LPR, lane = g % LPR;
         const bool act = i < n;
-        const C<T> bi = act && lane == 0 ? b[i] : mk<T>(0, 0);
+        const C<T> bi = UP && act && lane == 0 ? b[i] : mk<T>(0, 0);
         C<T> s = mk<T>(0, 0);
-        if (act)
-            for (int p = rp[i] + lane; p < rp[i + 1]; p += LPR) s = cadd(s, cmul(v[p], as_c<T>(x[ci[p]])));
+        if (act) {
+            const int p0 = UP ? dpos[i] + 1 : rp[i], p1 = UP ? rp[i + 1] : dpos[i];
+            for (int p = p0 + lane; p < p1; p += LPR) s = cadd(s, cmul(v[p], x[ci[p]]));
+        }
         s = lanes_sum<T, LPR>(s);
-        if (act && lane == 0 && gate_go) r[i] = csub(bi, s);
+        if (act && lane == 0 && gate_go) y[i] = UP ? csub(bi, s) : s;
     }
 };
 
@@ -1479,6 +1488,9 @@ template <> double2 *vec_r<double>(Level &L) { return L.r64.get(); }
 template <> float2 *vec_b<float>(Level &L) { return L.b32.get(); }
 template <> float2 *vec_x<float>(Level &L) { return L.x32.get(); }
 template <> float2 *vec_r<float>(Level &L) { return L.r32.get(); }
+template <class T> static C<T> *vec_t(Level &L);
+template <> double2 *vec_t<double>(Level &L) { return L.t64.get(); }
+template <> float2 *vec_t<float>(Level &L) { return L.t32.get(); }
 template <class T> static const C<T> *vals(const Csr &M);
 template <> const double2 *vals<double>(const Csr &M) { return M.v64.get(); }
 template <> const float2 *vals<float>(const Csr &M) { return M.v32.get(); }
@@ -1559,65 +1571,65 @@ template <class T> static const C<T> *evals(const Level &L);
 template <> const double2 *evals<double>(const Level &L) { return L.ev64.get(); }
 template <> const float2 *evals<float>(const Level &L) { return L.ev32.get(); }
 
-static int ell_lanes(int W, int shift) { return shifted(W <= 3 ? 2 : W <= 6 ? 4 : W <= 16 ? 8 : 16, shift); }
+// lanes per row of a pass whose rows have at most `part` entries in it
+// (half or twice as many: 97^3 FP32 953 and 909 us per iteration, 910 with these;
+// 161^3 1680 and 1675, 1632)
+static int sgs_lanes(int part, int shift) { return shifted(part <= 4 ? 2 : part <= 8 ? 4 : part <= 32 ? 8 : 16, shift); }
 
-// One symmetric sweep on a level >= 1: colours 0 .. C-1, then C-2 .. 0.
-// from_zero: the sweep starts from x = 0 (its first two passes and the zero
-// start are one dispatch).
-template <class T>
-static void csr_sgs(Level &Lv, int shift, bool from_zero, const int *gate, const Launch &L)
+// Half a symmetric sweep: the colours in order (forward) or in reverse
+template <class T, int MODE>
+static void sgs_half(Level &Lv, int shift, const int *gate, const Launch &L)
 {
-    const int nco = Lv.ncolors;
-    const int t0 = from_zero ? std::min(2, 2 * nco - 1) : 0;
-    // algorithmic bytes of a pass: the colour's padded rows (index + value),
-    // one x value per stored entry, b and the diagonal of each row, x written
-    double bytes = 0.0;
+    constexpr bool fwd = MODE == SGS_FWD0 || MODE == SGS_FWD;
+    // algorithmic bytes: the entries of the part (index, value, gathered value), and
+    // each row's own terms and results; the passes share one event bracket
+    const double own = (MODE == SGS_FWD ? 4.0 : MODE == SGS_BWD0 ? 3.0 : 2.0) * sizeof(C<T>) + sizeof(T);
+    const double bytes = 0.5 * (Lv.Aa.nnz - Lv.n) * (4.0 + 2.0 * sizeof(C<T>)) + Lv.n * own;
     int passes = 0;
-    for (int t = 0; t < 2 * nco - 1; ++t) {
-        const int c = t < nco ? t : 2 * nco - 2 - t;
-        const int cnt = Lv.coff[c + 1] - Lv.coff[c];
-        if (cnt == 0) continue;
-        bytes += (double)cnt * Lv.ewidth[c] * (4.0 + 2.0 * sizeof(C<T>)) + cnt * (2.0 * sizeof(C<T>) + sizeof(T));
-        ++passes;
-    }
-    if (from_zero) passes -= t0 - 1;
-    // the passes of one sweep share one event bracket
+    for (int c = 0; c < Lv.ncolors; ++c) passes += Lv.coff[c + 1] > Lv.coff[c];
     prof_launch(PROF_COARSE_SWEEP, bytes, L, [&] {
-        if (from_zero) {
-            const int c1 = Lv.coff[1], c2 = nco > 1 ? Lv.coff[2] : Lv.n;
-            const int W = nco > 1 ? Lv.ewidth[1] : 1;
-            const int lpr = ell_lanes(W, shift);
-            const int nb = blocks_for((int64_t)Lv.n * lpr);
-            GLK_LPR_SWITCH(lpr, {
-                L.run(nb, EllSgsStart<T, LPR>{Lv.eci.get() + (nco > 1 ? Lv.eoff[1] : 0), evals<T>(Lv) +
-                                              (nco > 1 ? Lv.eoff[1] : 0), W, dgn<T>(Lv), c1, c2, Lv.n,
-                                              vec_b<T>(Lv), vec_x<T>(Lv), gate});
-            });
-        }
-        for (int t = t0; t < 2 * nco - 1; ++t) {
-            const int c = t < nco ? t : 2 * nco - 2 - t;
-            const int cnt = Lv.coff[c + 1] - Lv.coff[c];
+        for (int k = 0; k < Lv.ncolors; ++k) {
+            const int c = fwd ? k : Lv.ncolors - 1 - k, W = Lv.ewidth[c], cnt = Lv.coff[c + 1] - Lv.coff[c];
             if (cnt == 0) continue;
-            const int W = Lv.ewidth[c];
-            const int lpr = ell_lanes(W, shift);
-            const int nb = blocks_for((int64_t)cnt * lpr);
+            const int lo = fwd ? 0 : std::min(W, Lv.eup[c]), hi = fwd ? Lv.elow[c] : W;
+            const int lpr = sgs_lanes(hi - lo, shift);
             GLK_LPR_SWITCH(lpr, {
-                L.run(nb, EllSgs<T, LPR>{Lv.eci.get() + Lv.eoff[c], evals<T>(Lv) + Lv.eoff[c], W, dgn<T>(Lv),
-                                         Lv.coff[c], cnt, vec_b<T>(Lv), vec_x<T>(Lv), gate});
+                L.run(blocks_for((int64_t)cnt * lpr),
+                      SgsPass<T, LPR, MODE>{Lv.eci.get() + Lv.eoff[c], evals<T>(Lv) + Lv.eoff[c], W, lo, hi, Lv.coff[c],
+                                            cnt, dgn<T>(Lv), vec_b<T>(Lv), vec_x<T>(Lv), vec_r<T>(Lv), vec_t<T>(Lv),
+                                            gate});
             });
         }
     }, passes);
 }
 
-template <class T>
-static void csr_residual(Level &Lv, int shift, const int *gate, const Launch &L)
+template <class T, int UP>
+static void sgs_product(Level &Lv, int shift, const int *gate, const Launch &L)
 {
-    const int lpr = lanes_for(Lv.Aa, shift);
-    const int nb = blocks_for((int64_t)Lv.n * lpr);
+    const int lpr = shifted(lanes_for(Lv.Aa, shift), -1);
     GLK_LPR_SWITCH(lpr, {
-        L.run(nb, CsrResidual<T, LPR>{Lv.n, Lv.Aa.rp.get(), Lv.Aa.ci.get(), vals<T>(Lv.Aa), vec_b<T>(Lv),
-                                      vec_x<T>(Lv), vec_r<T>(Lv), gate});
+        L.run(blocks_for((int64_t)Lv.n * lpr),
+              SgsProduct<T, LPR, UP>{Lv.n, Lv.Aa.rp.get(), Lv.Aa.ci.get(), Lv.dpos.get(), vals<T>(Lv.Aa), vec_b<T>(Lv),
+                                     UP ? vec_x<T>(Lv) : vec_r<T>(Lv), UP ? vec_r<T>(Lv) : vec_t<T>(Lv), gate});
     });
+}
+
+// x = sweep from zero; the residual in vec_t
+template <class T>
+static void csr_pre(Level &Lv, int shift, const int *gate, const Launch &L)
+{
+    sgs_half<T, SGS_FWD0>(Lv, shift, gate, L);
+    sgs_half<T, SGS_BWD0>(Lv, shift, gate, L);
+    sgs_product<T, 0>(Lv, shift, gate, L);
+}
+
+// a sweep of x
+template <class T>
+static void csr_post(Level &Lv, int shift, const int *gate, const Launch &L)
+{
+    sgs_product<T, 1>(Lv, shift, gate, L);
+    sgs_half<T, SGS_FWD>(Lv, shift, gate, L);
+    sgs_half<T, SGS_BWD>(Lv, shift, gate, L);
 }
 
 // ---- a level in patches
@@ -1729,10 +1741,9 @@ static void coarse_levels(gl_precond *pre, const int *gate, const Launch &L)
         if (Lv.patch.np) {
             patch_pre<TC>(Lv, gate, L);
         } else {
-            csr_sgs<TC>(Lv, sh, true, gate, L);
-            csr_residual<TC>(Lv, sh, gate, L);
+            csr_pre<TC>(Lv, sh, gate, L);
         }
-        csr_spmv<TC>(Lv.Ra, vec_r<TC>(Lv), vec_b<TC>(pre->L[l + 1]), false, sh, gate, L);
+        csr_spmv<TC>(Lv.Ra, Lv.patch.np ? vec_r<TC>(Lv) : vec_t<TC>(Lv), vec_b<TC>(pre->L[l + 1]), false, sh, gate, L);
     }
     if (pre->bottom < pre->tail) {
         L.run<Bottom<TC>, kBottomThreads>(1, Bottom<TC>{bdesc<TC>(pre), gate}, bottom_lds<TC>(pre));
@@ -1748,7 +1759,7 @@ static void coarse_levels(gl_precond *pre, const int *gate, const Launch &L)
             patch_post<TC>(Lv, xc, gate, L);
         } else {
             csr_spmv<TC>(Lv.Pa, xc, vec_x<TC>(Lv), true, sh, gate, L);
-            csr_sgs<TC>(Lv, sh, false, gate, L);
+            csr_post<TC>(Lv, sh, gate, L);
         }
     }
 }
@@ -1922,10 +1933,9 @@ static void vcycle_once_simplicial(const gl_precond *cpre, const double2 *v, con
     if (L0.patch.np) {
         patch_pre<T>(L0, gate, L);
     } else {
-        csr_sgs<T>(L0, sh, true, gate, L);
-        csr_residual<T>(L0, sh, gate, L);
+        csr_pre<T>(L0, sh, gate, L);
     }
-    csr_spmv<TC, T>(L0.Ra, vec_r<T>(L0), vec_b<TC>(L1), false, sh, gate, L);
+    csr_spmv<TC, T>(L0.Ra, L0.patch.np ? vec_r<T>(L0) : vec_t<T>(L0), vec_b<TC>(L1), false, sh, gate, L);
     coarse_levels<TC>(pre, gate, L);
     const C<TC> *x1 = cycle_result<TC>(pre, 1);
     if (L0.patch.np) {
@@ -1933,7 +1943,7 @@ static void vcycle_once_simplicial(const gl_precond *cpre, const double2 *v, con
         x0 = vec_r<T>(L0);
     } else {
         csr_spmv<T, TC>(L0.Pa, x1, x0, true, sh, gate, L);
-        csr_sgs<T>(L0, sh, false, gate, L);
+        csr_post<T>(L0, sh, gate, L);
     }
     if (add) L.run(nb0, OutputPerm<T, 1>{n0, x0, perm, vdot, z, slot, want, dd, gate});
     else L.run(nb0, OutputPerm<T, 0>{n0, x0, perm, vdot, z, slot, want, dd, gate});
