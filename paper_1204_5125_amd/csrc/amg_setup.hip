@@ -891,13 +891,13 @@ struct PwRho {
 __host__ __device__ constexpr bool rho_normed(int k) { return k == kRhoSteps / 2 || k >= kRhoSteps - 1; }
 
 // The whole estimate of a small level by one work-group, from its CSR matrix: LPR
-// lanes per row, the matrix in registers (kPwSlots rows of kPwEntries entries per
+// lanes per row, the matrix in registers (S rows of kPwEntries entries per
 // thread), the vector in LDS.  A step is a few LDS reads and two barriers (0.8 us)
 // where a dispatch takes 4-5 with its gap: 33^2, two levels, 0.38 ms per numeric
-// setup with a dispatch per step, now 0.29.
-constexpr int kPwThreads = 1024, kPwSlots = 4, kPwEntries = 4;
+// setup with a dispatch per step, 0.29 with S = 4 for every level, now 0.25.
+constexpr int kPwThreads = 1024, kPwEntries = 4;
 
-template <int LPR>
+template <int LPR, int S>
 struct PwSmall {
     int n;
     const int *rp, *ci;
@@ -906,14 +906,14 @@ struct PwSmall {
     double *rho;
     __device__ void operator()(int, int) const
     {
-        __shared__ double2 x[kPwThreads * kPwSlots / LPR];
+        __shared__ double2 x[kPwThreads * S / LPR];
         __shared__ double sm[kPwThreads / 64], norm;
-        double2 a[kPwSlots][kPwEntries], y[kPwSlots];
-        int j[kPwSlots][kPwEntries];
-        double w[kPwSlots];
+        double2 a[S][kPwEntries], y[S];
+        int j[S][kPwEntries];
+        double w[S];
         const int lane = threadIdx.x % LPR;
 #pragma unroll
-        for (int s = 0; s < kPwSlots; ++s) {
+        for (int s = 0; s < S; ++s) {
             const int i = (s * kPwThreads + threadIdx.x) / LPR;
             const int b = i < n ? rp[i] : 0, e = i < n ? rp[i + 1] : 0;
             w[s] = i < n ? 1.0 / diag[i] : 0.0;
@@ -930,7 +930,7 @@ struct PwSmall {
         for (int step = 1; step <= kRhoSteps; ++step) {
             double part = 0.0;
 #pragma unroll
-            for (int s = 0; s < kPwSlots; ++s) {
+            for (int s = 0; s < S; ++s) {
                 double2 acc = make_double2(0.0, 0.0);
 #pragma unroll
                 for (int k = 0; k < kPwEntries; ++k) acc = cadd(acc, cmul(a[s][k], x[j[s][k]]));
@@ -944,7 +944,7 @@ struct PwSmall {
             }
             __syncthreads();
 #pragma unroll
-            for (int s = 0; s < kPwSlots; ++s) {
+            for (int s = 0; s < S; ++s) {
                 const int i = (s * kPwThreads + threadIdx.x) / LPR;
                 if (i < n && lane == 0) x[i] = y[s];
             }
@@ -969,16 +969,20 @@ static void rho_estimate(gl_precond *pre, Level &lev, const Launch &L)
     double2 *x = pre->vin.get(), *y = pre->cyc_r.get();
     double *nrm = pre->pwn.get();
     const int width = lev.ewidth.empty() ? 2 * m->g.dim + 1 : *std::max_element(lev.ewidth.begin(), lev.ewidth.end());
-    const auto small = [&](auto lpr) {
-        constexpr int LPR = decltype(lpr)::value;
-        if (width > LPR * kPwEntries || (int64_t)n * LPR > kPwThreads * kPwSlots) return false;
-        L.run<PwSmall<LPR>, kPwThreads>(
-            1, PwSmall<LPR>{n, lev.A.rp.get(), lev.A.ci.get(), lev.A.v64.get(), lev.diag64.get(), lev.rho.get()});
+    const auto small = [&](auto lpr, auto slots) {
+        constexpr int LPR = decltype(lpr)::value, S = decltype(slots)::value;
+        if (width > LPR * kPwEntries || (int64_t)n * LPR > kPwThreads * S) return false;
+        L.run<PwSmall<LPR, S>, kPwThreads>(
+            1, PwSmall<LPR, S>{n, lev.A.rp.get(), lev.A.ci.get(), lev.A.v64.get(), lev.diag64.get(), lev.rho.get()});
         return true;
     };
-    if (small(std::integral_constant<int, 2>{}) || small(std::integral_constant<int, 4>{}) ||
-        small(std::integral_constant<int, 8>{}) || small(std::integral_constant<int, 16>{}) ||
-        small(std::integral_constant<int, 32>{}))
+    const auto small_rows = [&](auto lpr) {
+        return small(lpr, std::integral_constant<int, 1>{}) || small(lpr, std::integral_constant<int, 2>{}) ||
+               small(lpr, std::integral_constant<int, 4>{});
+    };
+    if (small_rows(std::integral_constant<int, 2>{}) || small_rows(std::integral_constant<int, 4>{}) ||
+        small_rows(std::integral_constant<int, 8>{}) || small_rows(std::integral_constant<int, 16>{}) ||
+        small_rows(std::integral_constant<int, 32>{}))
         return;
     L.run(nb, PwStart{n, x});
     // level 0 of a grid as the stencil, every other level (and level 0 of a
@@ -1003,31 +1007,52 @@ static void rho_estimate(gl_precond *pre, Level &lev, const Launch &L)
     L.run<PwRho, 64>(1, PwRho{nrm + (kRhoSteps & 1), lev.rho.get()});
 }
 
+// whether any lane of the wave is left (lanes of a wave that share shuffles stay together)
+__device__ __forceinline__ bool wave_any(bool p) { return __any(p); }
+
+// P = T - omega D^-1 A T.  LPR lanes share a row, a lane per entry of P's row: each
+// loads one entry of A's row with the aggregate of its column, and every lane adds
+// those of its own aggregate, in the order of the row, as they are passed round.
+// (A thread per row that walked A's row once per entry of P's: 97x81x65, three
+// levels, 550 us per numeric setup, now 84.)
+constexpr int kPLanes = 8;
+
 struct PValues {
+    static constexpr int LPR = kPLanes;
     int n;
-    const int *arp, *aci;
-    const double2 *av;
+    const int *__restrict__ arp, *__restrict__ aci;
+    const double2 *__restrict__ av;
     const double *diag;
-    const int *agg, *aggsize;
+    const int *__restrict__ agg, *aggsize;
     const double *rho;
-    const int *prp, *pci;
-    double2 *pv;
+    const int *__restrict__ prp, *__restrict__ pci;
+    double2 *__restrict__ pv;
     __device__ void operator()(int, int) const
     {
-        const int i = blockIdx.x * kBlock + threadIdx.x;
-        if (i >= n) return;
-        const double omega = (4.0 / 3.0) / *rho;
-        const double dii = diag[i];
-        const int ai = agg[i];
-        for (int p = prp[i]; p < prp[i + 1]; ++p) {
-            const int a = pci[p];
-            const double ta = 1.0 / sqrt((double)aggsize[a]);
+        const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+        const int i = (int)(g / LPR), lane = (int)(g % LPR);
+        const bool act = i < n;
+        const int b = act ? arp[i] : 0, e = act ? arp[i + 1] : 0;
+        const int pb = act ? prp[i] : 0, pe = act ? prp[i + 1] : 0;
+        const double f = act ? (4.0 / 3.0) / *rho / diag[i] : 0.0;
+        const int ai = act ? agg[i] : -1;
+        for (int p0 = pb; wave_any(p0 < pe); p0 += LPR) {
+            const int p = p0 + lane;
+            const int a = p < pe ? pci[p] : -1;
+            const double ta = a >= 0 ? 1.0 / sqrt((double)aggsize[a]) : 0.0;
             double2 at = make_double2(0.0, 0.0);
-            for (int q = arp[i]; q < arp[i + 1]; ++q)
-                if (agg[aci[q]] == a) at = cadd(at, cscale(av[q], ta));
-            const double t0 = (ai == a) ? ta : 0.0;
-            const double f = omega / dii;
-            pv[p] = make_double2(t0 - f * at.x, -f * at.y);
+            for (int q0 = p0 < pe ? b : e; wave_any(q0 < e); q0 += LPR) {
+                const int q = q0 + lane;
+                const int mine = q < e ? agg[aci[q]] : -2;
+                const double2 v = q < e ? av[q] : make_double2(0.0, 0.0);
+#pragma unroll
+                for (int t = 0; t < LPR; ++t) {
+                    const int c = __shfl(mine, t, LPR);
+                    const double2 u = make_double2(__shfl(v.x, t, LPR), __shfl(v.y, t, LPR));
+                    if (c == a) at = cadd(at, cscale(u, ta));
+                }
+            }
+            if (p < pe) pv[p] = make_double2((ai == a ? ta : 0.0) - f * at.x, -f * at.y);
         }
     }
 };
@@ -1049,7 +1074,12 @@ struct RValues {
 // third of the terms that R A P has term by term, and lists two indices per
 // term instead of three.
 // (A P)_ik = sum of A_ij P_jk over the row's j, LPR lanes per row, a lane per
-// entry; the lanes of a row read the same A and P entries.
+// entry of A P.  The row's products are formed LPR at a time, a lane each (the
+// lanes load an entry of A each, count the entries of P's rows below them and find
+// their own) and put into LDS: every lane adds those of its column, in the order of
+// the row.  (Each lane searching every P row for its column: chains of dependent
+// loads, 97x81x65 807 us per numeric setup, now 290; 129^3 2.7 ms, now 1.0.  The
+// products passed round by shuffles, five words each: 750 us and 2.65 ms.)
 template <int LPR>
 struct ApValues {
     int n;
@@ -1061,20 +1091,56 @@ struct ApValues {
     double2 *__restrict__ apv;
     __device__ void operator()(int, int) const
     {
+        __shared__ double2 s_a[kBlock], s_v[kBlock];
+        __shared__ int s_at[kBlock];
+        __shared__ int4 s_c[kBlock / 4];
         const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-        const int i = (int)(g / LPR), lane = (int)(g % LPR);
-        if (i >= n) return;
-        const int b = rp[i], e = rp[i + 1], ke = aprp[i + 1];
-        for (int k = aprp[i] + lane; k < ke; k += LPR) {
-            const int c = apci[k];
+        const int i = (int)(g / LPR), lane = (int)(g % LPR), own = threadIdx.x - lane;  // own: the row's first place
+        const bool act = i < n;
+        const int b = act ? rp[i] : 0, e = act ? rp[i + 1] : 0;
+        const int kb = act ? aprp[i] : 0, ke = act ? aprp[i + 1] : 0;
+        for (int k0 = kb; wave_any(k0 < ke); k0 += LPR) {
+            const int k = k0 + lane;
+            const int mine = k < ke ? apci[k] : -1;
             double2 acc = make_double2(0.0, 0.0);
-            for (int q = b; q < e; ++q) {
-                const int j = ci[q], s1 = prp[j + 1];
-                int s = prp[j];
-                while (s < s1 && pci[s] < c) ++s;
-                if (s < s1 && pci[s] == c) acc = cadd(acc, cmul(av[q], pv[s]));
+            for (int q0 = k0 < ke ? b : e; wave_any(q0 < e); q0 += LPR) {
+                const int q = q0 + lane;
+                const int j = q < e ? ci[q] : 0;
+                const double2 a = q < e ? av[q] : make_double2(0.0, 0.0);
+                const int s0 = q < e ? prp[j] : 0, len = q < e ? prp[j + 1] - s0 : 0;
+                int upto = len;  // products of this lane's entry and those before it
+#pragma unroll
+                for (int o = 1; o < LPR; o *= 2) {
+                    const int x = __shfl_up(upto, o, LPR);
+                    if (lane >= o) upto += x;
+                }
+                const int total = __shfl(upto, LPR - 1, LPR);
+                s_a[threadIdx.x] = a;
+                s_at[threadIdx.x] = s0 - (upto - len);  // product m is entry s_at + m of P
+                wave_sync();
+                for (int m0 = 0; wave_any(m0 < total); m0 += LPR) {
+                    const int m = m0 + lane;
+                    int src = 0;  // the first lane with upto > m
+#pragma unroll
+                    for (int o = LPR / 2; o > 0; o /= 2)
+                        if (__shfl(upto, src + o - 1, LPR) <= m) src += o;
+                    const bool in = m < total;
+                    const int at = s_at[own + src] + m;
+                    reinterpret_cast<int *>(s_c)[threadIdx.x] = in ? pci[at] : -2;
+                    s_v[threadIdx.x] = in ? cmul(s_a[own + src], pv[at]) : make_double2(0.0, 0.0);
+                    wave_sync();
+                    unsigned hit = 0;
+#pragma unroll
+                    for (int t = 0; t < LPR; t += 4) {
+                        const int4 c = s_c[(own + t) / 4];
+                        hit |= ((c.x == mine) | (c.y == mine) << 1 | (c.z == mine) << 2 | (c.w == mine) << 3) << t;
+                    }
+                    for (; hit; hit &= hit - 1) acc = cadd(acc, s_v[own + __ffs(hit) - 1]);
+                    wave_sync();
+                }
+                wave_sync();
             }
-            apv[k] = acc;
+            if (k < ke) apv[k] = acc;
         }
     }
 };
@@ -2252,8 +2318,9 @@ void precond_numeric_enqueue(gl_precond *pre, const double2 *psi, const Launch &
         const int n = lv.n, nb = blocks_for(n);
         if (l > 0) L.run(nb, Diag{n, lv.A.rp.get(), lv.A.ci.get(), lv.A.v64.get(), lv.diag64.get()});
         rho_estimate(pre, lv, L);
-        L.run(nb, PValues{n, lv.A.rp.get(), lv.A.ci.get(), lv.A.v64.get(), lv.diag64.get(), lv.agg.get(),
-                          lv.aggsize.get(), lv.rho.get(), lv.P.rp.get(), lv.P.ci.get(), lv.P.v64.get()});
+        L.run(blocks_for((int64_t)n * kPLanes),
+              PValues{n, lv.A.rp.get(), lv.A.ci.get(), lv.A.v64.get(), lv.diag64.get(), lv.agg.get(), lv.aggsize.get(),
+                      lv.rho.get(), lv.P.rp.get(), lv.P.ci.get(), lv.P.v64.get()});
         L.run(blocks_for(lv.R.nnz), RValues{lv.R.nnz, lv.rsrc.get(), lv.P.v64.get(), lv.R.v64.get()});
         // A P: about a lane per entry of a row
         auto ap = [&](auto lanes) {
