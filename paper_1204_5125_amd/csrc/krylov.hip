@@ -1307,8 +1307,7 @@ gl_status gl_newton_solve(const gl_mesh *mesh, void *psi_inout, const gl_newton_
         gl_newton_info ni;
         std::memset(&ni, 0, sizeof(ni));
         auto residual = [&]() {
-            gl_residual_enqueue(mesh, psi, r, mesh->dscal.get(), s);
-            GLK_HIP(hipMemcpyAsync(mesh->hscal, mesh->dscal.get(), sizeof(double), hipMemcpyDeviceToHost, s));
+            gl_residual_enqueue(mesh, psi, r, mesh->hscal, s);  // pinned: the device writes it
             GLK_HIP(hipStreamSynchronize(s));
             return std::sqrt(mesh->hscal[0]);
         };

@@ -1087,9 +1087,9 @@ gl_status gl_residual(const gl_mesh *mesh, const void *psi, void *out, double *n
         if (!mesh || !psi) fail(GL_ERR_INVALID_ARGUMENT, "gl_residual: NULL mesh or psi");
         if (out == psi) fail(GL_ERR_INVALID_ARGUMENT, "gl_residual: out aliases psi");
         hipStream_t s = as_stream(stream);
-        gl_residual_enqueue(mesh, (const double2 *)psi, (double2 *)out, mesh->dscal.get(), s);
+        // the total goes straight to pinned host memory (33^2: 21.6 us a call, 23.5 with a copy)
+        gl_residual_enqueue(mesh, (const double2 *)psi, (double2 *)out, norm_D ? mesh->hscal : mesh->dscal.get(), s);
         if (norm_D) {
-            GLK_HIP(hipMemcpyAsync(mesh->hscal, mesh->dscal.get(), sizeof(double), hipMemcpyDeviceToHost, s));
             GLK_HIP(hipStreamSynchronize(s));
             *norm_D = std::sqrt(mesh->hscal[0]);
         }
