@@ -31,7 +31,9 @@ def split(info, tiles):
     """(lane_shift, first level of the bottom kernel, level applied as a dense
     operator) that a preconditioner with these level sizes and colour counts
     (`Precond.info()`) derives from `tiles`, by the rule of
-    gl_precond_set_tiles."""
+    gl_precond_set_tiles.  (Levels whose sweeps run on patches stay out of the
+    bottom kernel whatever its bound; `info` does not tell them, so candidates
+    that differ in such levels alone are timed each.)"""
     ls, br, dr = tiles
     sizes, colours = info["sizes"], info["ncolors"]
     last = len(sizes) - 1
