@@ -297,7 +297,7 @@ __device__ __forceinline__ void store_relaxed(int *p, int v)
 // front and waits; the others are listed in LDS and get kMisLanes lanes each,
 // which take the neighbours in turn with a batch of loads in flight (a thread
 // walking the 25 words of its neighbourhood one by one took 23 us a round).
-// flag (nullable): set when a node was undecided before this round.
+// flag (nullable): set when a node was undecided before it.
 constexpr int kMisLanes = 8;
 
 __global__ __launch_bounds__(kBlock) void k_mis_round(int n, const int *__restrict__ rp, const int *__restrict__ ci,

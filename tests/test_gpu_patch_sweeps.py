@@ -130,3 +130,20 @@ def test_large_levels(glnk, shape):
         pre = glnk.Precond(mg, torch.from_numpy(psi).cuda(), precision=prec, cycles=1, max_coarse=64)
         z = vcycle(pre, r, mo.n)
         assert np.abs(z - want).max() <= tol * np.abs(want).max(), prec
+
+
+@pytest.mark.parametrize("shift", [-1, 0, 1])
+@pytest.mark.parametrize("shape", [(9, 8, 7), (23, 5, 17), (30, 31, 29)])
+def test_colour_passes(glnk, shape, shift):
+    """3D levels, a dispatch per colour on the halves of the rows, with fewer and
+    more lanes per row; bounds as above."""
+    side = tuple(0.4 * (n - 1) for n in shape)
+    mg, mo = glnk.Mesh(3, shape, side, mu=0.6), oracle.Mesh(3, shape, side, mu=0.6)
+    psi = inputs.random_phase_state(mo.n, seed=4)
+    r = inputs.random_complex(mo.n, seed=5)
+    want = oracle.Amg.for_state(mo, psi, max_coarse=8).precond(mo, r, cycles=1)
+    for prec, tol in ((glnk.GL_FP64, 1e-11), (glnk.GL_FP32, 1e-5), (glnk.GL_MIXED, 1e-5)):
+        pre = glnk.Precond(mg, torch.from_numpy(psi).cuda(), precision=prec, cycles=1, max_coarse=8)
+        glnk.gl_precond_set_tiles(pre, shift, 1, 0, 0)
+        z = vcycle(pre, r, mo.n)
+        assert np.abs(z - want).max() <= tol * np.abs(want).max(), prec

@@ -120,3 +120,12 @@ def test_memory_given_back_and_taken_again(glnk):
         assert torch.equal(applied(last, r[k]), want[2])
         m.close()
         last.close()
+
+
+@pytest.mark.parametrize("shape", [(64, 32), (683, 3), (32, 32), (25, 41), (8, 8, 8), (11, 31, 6)])
+def test_power_iteration_of_small_levels(glnk, shape):
+    """Levels at and past the sizes whose spectral-radius estimate one work-group
+    runs (2048 and 1024 rows of up to 8 entries, 512 and 1024 of seven in 3D): the
+    prolongator and the coarse operators against the oracle, as above."""
+    side = tuple(0.3 * (n - 1) for n in shape)
+    compare(glnk, glnk.Mesh(len(shape), shape, side, mu=0.7), oracle.Mesh(len(shape), shape, side, mu=0.7), 8)
