@@ -262,7 +262,14 @@ gl_status gl_precond_inner_steps(const gl_precond *pre, int *steps);
 void gl_precond_destroy(gl_precond *pre);
 
 /* Launch-shape choices of the V-cycle (no effect on what is computed beyond
- * the order of rounding in row sums):
+ * the order of rounding in row sums).  All four fields 0, the state of a new
+ * handle: automatic, chosen by the level sizes (2D grids: l0_tiled form 2; in
+ * solves, where it pays, the sub-cycle of a level of at most 2048 rows as an
+ * explicit matrix).  With any field nonzero every field is taken as it stands;
+ * {0, 512, 0, 0} is each field's fixed default (one dispatch per pass, no
+ * explicit sub-cycle).  What a handle does depends on the last call alone, and
+ * gl_precond_get_tiles gives values that restore it (bottom_rows 0 only for
+ * automatic):
  *   lane_shift: lanes that share one row in the sparse kernels of levels >= 1
  *     = the built-in rule (about one lane per 2.5 stored entries of the row)
  *     times 2^lane_shift, clamped to 1 .. 32; -2 .. 2, default 0;
@@ -276,7 +283,7 @@ void gl_precond_destroy(gl_precond *pre);
  *     explicit matrix at every setup, in FP64 by the cycle's steps applied
  *     to the unit vectors, and applied as one dense
  *     product; the same operator up to rounding, one dispatch in place of a
- *     few dozen latency-bound ones.  0 = off (default), else 1 .. 8192; the
+ *     few dozen latency-bound ones.  0 = off, else 1 .. 8192; the
  *     matrix takes 24 n^2 bytes (FP64 and FP32 copies) and its formation a
  *     workspace of at most 1.5 GB (per-column vectors of every level from
  *     that one down), all held by the handle.
@@ -291,10 +298,9 @@ typedef struct {
                            sweep passes and the residual; up: the coarse
                            correction, the three passes and the output) on
                            tiles of 32 x 32 (768 threads), 32 x 16 (448) or
-                           16 x 16 nodes (320); 0 (default) one dispatch per
-                           pass; the same operator up to rounding.  A handle
-                           whose tiles were never changed takes form 2.  3D
-                           grids always use one dispatch per pass */
+                           16 x 16 nodes (320); 0 one dispatch per pass; the
+                           same operator up to rounding.  3D grids always use
+                           one dispatch per pass */
 } gl_tiles;
 
 gl_status gl_precond_set_tiles(gl_precond *pre, const gl_tiles *tiles);

@@ -277,16 +277,16 @@ struct gl_precond {
     int nlev = 0;
     int bottom = 0;                // first level handled by the bottom kernel
     int tail = 0;                  // level whose sub-cycle is one dense product (the coarsest if none)
-    // Solves on a handle whose tiles were never changed apply the sub-cycle of
-    // level stail (0: none) as an explicit matrix, formed by the first solve
-    // after a numeric setup (solver_tail_enqueue)
+    // With automatic tiles solves apply the sub-cycle of level stail (0: none)
+    // as an explicit matrix, formed by the first solve after a numeric setup
+    // (solver_tail_enqueue)
     int stail = 0;
     bool stail_current = false;
     int bottom_rows = glk::kBottomRows;  // tile choices (gl_precond_set_tiles)
     int lane_shift = 0;
     int dense_rows = 0;
     int l0_tiled = 0;              // 1: 2D level-0 passes in two LDS-tiled kernels
-    bool auto_tiles = true;        // gl_precond_set_tiles has not changed them: chosen by size
+    bool auto_tiles = true;        // all four tile choices 0: chosen by size
     bool has_values = false;       // a numeric setup has run
     glk::Level L[glk::kMaxLevels];
     glk::DevBuf<double2> cfac;     // Cholesky factor of the coarsest operator

@@ -1707,8 +1707,8 @@ static C<T> *cycle_result(gl_precond *pre, int l)
     return l < pre->bottom && Lv.patch.np ? vec_r<T>(Lv) : vec_x<T>(Lv);
 }
 
-// The form of level 0 of a 2D grid: as gl_precond_set_tiles asked; on a handle
-// whose tiles were never changed, tiles of 32 x 16.  Microseconds per MINRES
+// The form of level 0 of a 2D grid: as gl_precond_set_tiles asked; with
+// automatic tiles, tiles of 32 x 16.  Microseconds per MINRES
 // iteration, a dispatch per pass / tiles, FP64: 513^2 147 / 136, 769^2 190 /
 // 175, 1025^2 291 / 278, 1537^2 578 / 559, 2049^2 1058 / 1048 (smaller grids and
 // FP32 gain more).
@@ -2226,8 +2226,8 @@ void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const i
     vcycle_enqueue(pre, v, z, gate, ks, mode, L, pre->opts.precision, DeflDot{}, false);
 }
 
-// The level whose sub-cycle a solve applies as an explicit matrix when the
-// tiles were never changed (0: none): the one that saves most over
+// The level whose sub-cycle a solve applies as an explicit matrix with
+// automatic tiles (0: none): the one that saves most over
 // kSolverCycles V-cycles, its formation counted.  Microseconds, from
 // measurements: a level in patches 30, else 3.2 per dispatch of its 4 C, or 1.4
 // per step inside the bottom kernel; a dense product 4 and its bytes at 4 TB/s;
