@@ -930,8 +930,9 @@ def main():
     # sweeps take the most GPU time (latency-bound small launches); the
     # level-0 sweeps move the most bytes.
     # level 0 of the FP32 V-cycle: one dispatch per pass, or LDS tiles of
-    # shape l0_tiled (the same profile id; the counters are per form)
-    l0_form = tiles["fp32"][3] if len(tiles["fp32"]) > 3 else 0
+    # shape l0_tiled (the same profile id; the counters are per form); the
+    # automatic choice takes shape 2
+    l0_form = 2 if tiles["fp32"] == autotune.AUTO else tiles["fp32"][3] if len(tiles["fp32"]) > 3 else 0
     names = dict(KERNEL_NAMES)
     if l0_form:
         names[2] = L0_TILED_NAME
