@@ -654,11 +654,18 @@ __device__ __forceinline__ C<T> lanes_sum(C<T> s)
 // the lower part of a row of colour c lies within its first elow[c] entries, the
 // upper part from entry eup[c] on.
 // A pass of a few thousand rows is bound by its launch and two dependent trips to
-// memory (5.5-6 us), one of a large level by the rows' traffic.  us per MINRES
-// iteration against whole rows updated in place and a residual of its own: 65^3 FP64
-// 332 -> 316, 97^3 FP32 1083 -> 910, 129^3 FP32 858 -> 836 and FP64 1097 -> 1022,
-// 161^3 FP32 1916 -> 1632.  (Two colours per dispatch, the second forming the values
-// it needs of the first itself: 97^3 1942, 129^3 FP32 1340.)
+// memory (5.5-6 us), one of a large level by the rows' traffic, so passes with
+// nothing to gather are not dispatches of their own: the first colour from zero
+// (t = D^-1 b) is formed by the kernel that writes b, in the sweep of x by that of r =
+// b - U x, and the last colour's backward value is its forward one (its rows have no
+// U).  C colours take 2 C - 1 dispatches each way, as many as whole rows updated in
+// place with a residual of their own.  us per MINRES iteration, automatic tiles, whole
+// rows / halves with 2 C + 1 dispatches / now: tetrahedron of 3 101 nodes 186 / 81 /
+// 73 FP64, 97^3 1151 / 920 / 900, 129^3 1596 / 1310 / 1291 and FP32 1364 / 1149 /
+// 1132; one application (gl_precond_apply) to 5x5x3001 204 / 214 / 206, to 129^3 1488
+// / 1199 / 1182.  (Two colours per dispatch, the second forming the values it needs of
+// the first itself: 97^3 1942, 129^3 FP32 1340 against 910 and 836; the first colour
+// alone that way: 129^3 2 % slower, its FP64 divisions.)
 enum { SGS_FWD0 = 0, SGS_FWD = 1, SGS_BWD0 = 2, SGS_BWD = 3 };
 
 // One colour: its rows and the entries [lo, hi) of them that hold the part.  LPR
@@ -666,11 +673,13 @@ enum { SGS_FWD0 = 0, SGS_FWD = 1, SGS_BWD0 = 2, SGS_BWD = 3 };
 // alongside the data and checked only before the store.
 constexpr int kSgsBatch = 4;
 
+// last: no later colour, so x is the forward value.
 template <class T, int LPR, int MODE>
 struct SgsPass {
     const int *eci;
     const C<T> *ev;
     int W, lo, hi, row0, cnt;
+    bool last;
     const T *diag;
     const C<T> *b;
     C<T> *x, *r, *t;
@@ -720,19 +729,23 @@ struct SgsPass {
             r[i] = e;
             x[i] = csub(p, e);
         } else {
-            (fwd ? t : x)[i] = cscale(csub(p, s), w);
+            const C<T> n = cscale(csub(p, s), w);
+            (fwd ? t : x)[i] = n;
+            if (fwd && last) x[i] = n;
             if (MODE == SGS_FWD) r[i] = csub(q, s);
         }
     }
 };
 
-// y = L e (UP = 0) or y = b - U x (UP = 1) from the sorted rows
+// y = L e (UP = 0) or y = b - U x (UP = 1) from the sorted rows; UP: the rows of
+// colour 0, the first `first`, also take their forward value t = D^-1 (b - U x), and y = b
 template <class T, int LPR, int UP>
 struct SgsProduct {
-    int n;
+    int n, first;
     const int *rp, *ci, *dpos;
     const C<T> *v, *b, *x;
-    C<T> *y;
+    const T *diag;
+    C<T> *y, *t;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
@@ -747,8 +760,24 @@ struct SgsProduct {
             for (int p = p0 + lane; p < p1; p += LPR) s = cadd(s, cmul(v[p], x[ci[p]]));
         }
         s = lanes_sum<T, LPR>(s);
-        if (act && lane == 0 && gate_go) y[i] = UP ? csub(bi, s) : s;
+        if (!act || lane != 0 || !gate_go) return;
+        const C<T> yi = UP ? csub(bi, s) : s;
+        if (UP && i < first) {  // (the diagonal loaded ahead of the sum: 80 us for 255 871 rows, 35 here)
+            t[i] = cscale(yi, (T)1 / diag[i]);
+            y[i] = bi;
+        } else {
+            y[i] = yi;
+        }
     }
+};
+
+// The rows of colour 0 of a level that runs its sweeps by colour passes, for the
+// kernel that writes its right-hand side b: t = D^-1 b there (n = 0: none)
+template <class T>
+struct FirstColour {
+    int n = 0;
+    const T *diag = nullptr;
+    C<T> *t = nullptr;
 };
 
 // y = A x (ADD = 0) or y += A x (ADD = 1); x may be held in the other precision
@@ -759,6 +788,7 @@ struct CsrSpmv {
     const C<T> *v;
     const C<TX> *x;
     C<T> *y;
+    FirstColour<T> fc;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
@@ -767,11 +797,14 @@ struct CsrSpmv {
         const int i = t / LPR, lane = t % LPR;
         const bool act = i < n;
         const C<T> yi = ADD && act && lane == 0 ? y[i] : mk<T>(0, 0);
+        const T d = !ADD && lane == 0 && i < fc.n ? fc.diag[i] : (T)1;
         C<T> s = mk<T>(0, 0);
         if (act)
             for (int p = rp[i] + lane; p < rp[i + 1]; p += LPR) s = cadd(s, cmul(v[p], as_c<T>(x[ci[p]])));
         s = lanes_sum<T, LPR>(s);
-        if (act && lane == 0 && gate_go) y[i] = ADD ? cadd(yi, s) : s;
+        if (!act || lane != 0 || !gate_go) return;
+        y[i] = ADD ? cadd(yi, s) : s;
+        if (!ADD && i < fc.n) fc.t[i] = cscale(s, (T)1 / d);
     }
 };
 
@@ -1027,12 +1060,16 @@ struct NarrowPerm {
     const double2 *v;
     const int *perm;
     C<T> *b;
+    FirstColour<T> fc;
     const int *gate;
     __device__ void operator()(int bx, int) const
     {
         GATE();
         const int r = bx * kBlock + threadIdx.x;
-        if (r < n) b[r] = narrow<T>(v[perm[r]]);
+        if (r >= n) return;
+        const C<T> br = narrow<T>(v[perm[r]]);
+        b[r] = br;
+        if (r < fc.n) fc.t[r] = cscale(br, (T)1 / fc.diag[r]);
     }
 };
 
@@ -1557,13 +1594,13 @@ static int lanes_for(const Csr &M, int shift)
 
 template <class T, class TX = T>
 static void csr_spmv(const Csr &M, const C<TX> *x, C<T> *y, bool add, int shift, const int *gate,
-                     const Launch &L)
+                     const Launch &L, const FirstColour<T> &fc = {})
 {
     const int lpr = lanes_for(M, shift);
     const int nb = blocks_for((int64_t)M.n * lpr);
     GLK_LPR_SWITCH(lpr, {
-        if (add) L.run(nb, CsrSpmv<T, LPR, 1, TX>{M.n, M.rp.get(), M.ci.get(), vals<T>(M), x, y, gate});
-        else L.run(nb, CsrSpmv<T, LPR, 0, TX>{M.n, M.rp.get(), M.ci.get(), vals<T>(M), x, y, gate});
+        if (add) L.run(nb, CsrSpmv<T, LPR, 1, TX>{M.n, M.rp.get(), M.ci.get(), vals<T>(M), x, y, fc, gate});
+        else L.run(nb, CsrSpmv<T, LPR, 0, TX>{M.n, M.rp.get(), M.ci.get(), vals<T>(M), x, y, fc, gate});
     });
 }
 
@@ -1576,28 +1613,44 @@ template <> const float2 *evals<float>(const Level &L) { return L.ev32.get(); }
 // 161^3 1680 and 1675, 1632)
 static int sgs_lanes(int part, int shift) { return shifted(part <= 4 ? 2 : part <= 8 ? 4 : part <= 32 ? 8 : 16, shift); }
 
-// Half a symmetric sweep: the colours in order (forward) or in reverse
+// the first colour of level l, when its sweep from zero is csr_pre's
+template <class T>
+static FirstColour<T> first_colour(gl_precond *pre, int l)
+{
+    Level &Lv = pre->L[l];
+    if (l >= pre->bottom || Lv.patch.np || Lv.ncolors < 2) return {};
+    return {Lv.coff[1], dgn<T>(Lv), vec_t<T>(Lv)};
+}
+
+// Half a symmetric sweep: the colours in order (forward) or in reverse, those that
+// other dispatches form left out (see SgsPass): of the first colour the forward value
+// (the writer of b's, sgs_product's), of the last one the backward value
 template <class T, int MODE>
 static void sgs_half(Level &Lv, int shift, const int *gate, const Launch &L)
 {
     constexpr bool fwd = MODE == SGS_FWD0 || MODE == SGS_FWD;
+    const int nc = Lv.ncolors;
+    const auto rows = [&](int c) { return Lv.coff[c + 1] - Lv.coff[c]; };
+    const int k0 = fwd && nc == 1 ? 0 : 1;
     // algorithmic bytes: the entries of the part (index, value, gathered value), and
     // each row's own terms and results; the passes share one event bracket
     const double own = (MODE == SGS_FWD ? 4.0 : MODE == SGS_BWD0 ? 3.0 : 2.0) * sizeof(C<T>) + sizeof(T);
-    const double bytes = 0.5 * (Lv.Aa.nnz - Lv.n) * (4.0 + 2.0 * sizeof(C<T>)) + Lv.n * own;
+    const int left_out = k0 ? rows(fwd ? 0 : nc - 1) : 0;
+    const double bytes = 0.5 * (Lv.Aa.nnz - Lv.n) * (4.0 + 2.0 * sizeof(C<T>)) + (Lv.n - left_out) * own;
     int passes = 0;
-    for (int c = 0; c < Lv.ncolors; ++c) passes += Lv.coff[c + 1] > Lv.coff[c];
+    for (int k = k0; k < nc; ++k) passes += rows(fwd ? k : nc - 1 - k) > 0;
+    if (passes == 0) return;
     prof_launch(PROF_COARSE_SWEEP, bytes, L, [&] {
-        for (int k = 0; k < Lv.ncolors; ++k) {
-            const int c = fwd ? k : Lv.ncolors - 1 - k, W = Lv.ewidth[c], cnt = Lv.coff[c + 1] - Lv.coff[c];
+        for (int k = k0; k < nc; ++k) {
+            const int c = fwd ? k : nc - 1 - k, W = Lv.ewidth[c], cnt = rows(c);
             if (cnt == 0) continue;
             const int lo = fwd ? 0 : std::min(W, Lv.eup[c]), hi = fwd ? Lv.elow[c] : W;
             const int lpr = sgs_lanes(hi - lo, shift);
             GLK_LPR_SWITCH(lpr, {
                 L.run(blocks_for((int64_t)cnt * lpr),
                       SgsPass<T, LPR, MODE>{Lv.eci.get() + Lv.eoff[c], evals<T>(Lv) + Lv.eoff[c], W, lo, hi, Lv.coff[c],
-                                            cnt, dgn<T>(Lv), vec_b<T>(Lv), vec_x<T>(Lv), vec_r<T>(Lv), vec_t<T>(Lv),
-                                            gate});
+                                            cnt, c == nc - 1, dgn<T>(Lv), vec_b<T>(Lv), vec_x<T>(Lv),
+                                            vec_r<T>(Lv), vec_t<T>(Lv), gate});
             });
         }
     }, passes);
@@ -1606,11 +1659,12 @@ static void sgs_half(Level &Lv, int shift, const int *gate, const Launch &L)
 template <class T, int UP>
 static void sgs_product(Level &Lv, int shift, const int *gate, const Launch &L)
 {
-    const int lpr = shifted(lanes_for(Lv.Aa, shift), -1);
+    const int lpr = shifted(lanes_for(Lv.Aa, shift), -1), first = UP && Lv.ncolors > 1 ? Lv.coff[1] : 0;
     GLK_LPR_SWITCH(lpr, {
         L.run(blocks_for((int64_t)Lv.n * lpr),
-              SgsProduct<T, LPR, UP>{Lv.n, Lv.Aa.rp.get(), Lv.Aa.ci.get(), Lv.dpos.get(), vals<T>(Lv.Aa), vec_b<T>(Lv),
-                                     UP ? vec_x<T>(Lv) : vec_r<T>(Lv), UP ? vec_r<T>(Lv) : vec_t<T>(Lv), gate});
+              SgsProduct<T, LPR, UP>{Lv.n, first, Lv.Aa.rp.get(), Lv.Aa.ci.get(), Lv.dpos.get(), vals<T>(Lv.Aa),
+                                     vec_b<T>(Lv), UP ? vec_x<T>(Lv) : vec_r<T>(Lv), dgn<T>(Lv),
+                                     UP ? vec_r<T>(Lv) : vec_t<T>(Lv), vec_t<T>(Lv), gate});
     });
 }
 
@@ -1743,7 +1797,8 @@ static void coarse_levels(gl_precond *pre, const int *gate, const Launch &L)
         } else {
             csr_pre<TC>(Lv, sh, gate, L);
         }
-        csr_spmv<TC>(Lv.Ra, Lv.patch.np ? vec_r<TC>(Lv) : vec_t<TC>(Lv), vec_b<TC>(pre->L[l + 1]), false, sh, gate, L);
+        csr_spmv<TC>(Lv.Ra, Lv.patch.np ? vec_r<TC>(Lv) : vec_t<TC>(Lv), vec_b<TC>(pre->L[l + 1]), false, sh, gate, L,
+                     first_colour<TC>(pre, l + 1));
     }
     if (pre->bottom < pre->tail) {
         L.run<Bottom<TC>, kBottomThreads>(1, Bottom<TC>{bdesc<TC>(pre), gate}, bottom_lds<TC>(pre));
@@ -1853,7 +1908,7 @@ static void vcycle_once_grid(const gl_precond *cpre, const double2 *v, const dou
         });
     }
     prof_launch(PROF_L0_TRANSFER, b_restr, L, [&] {
-        csr_spmv<TC, T>(L0.Rb, vec_r<T>(L0), vec_b<TC>(L1), false, 0, gate, L);
+        csr_spmv<TC, T>(L0.Rb, vec_r<T>(L0), vec_b<TC>(L1), false, 0, gate, L, first_colour<TC>(pre, 1));
     });
     // levels >= 1: b of level 1 in, x of level 1 out
     coarse_levels<TC>(pre, gate, L);
@@ -1929,13 +1984,14 @@ static void vcycle_once_simplicial(const gl_precond *cpre, const double2 *v, con
     const int sh = pre->lane_shift;
     const int *perm = L0.perm.get();
     C<T> *x0 = vec_x<T>(L0);
-    L.run(nb0, NarrowPerm<T>{n0, v, perm, vec_b<T>(L0), gate});
+    L.run(nb0, NarrowPerm<T>{n0, v, perm, vec_b<T>(L0), first_colour<T>(pre, 0), gate});
     if (L0.patch.np) {
         patch_pre<T>(L0, gate, L);
     } else {
         csr_pre<T>(L0, sh, gate, L);
     }
-    csr_spmv<TC, T>(L0.Ra, L0.patch.np ? vec_r<T>(L0) : vec_t<T>(L0), vec_b<TC>(L1), false, sh, gate, L);
+    csr_spmv<TC, T>(L0.Ra, L0.patch.np ? vec_r<T>(L0) : vec_t<T>(L0), vec_b<TC>(L1), false, sh, gate, L,
+                    first_colour<TC>(pre, 1));
     coarse_levels<TC>(pre, gate, L);
     const C<TC> *x1 = cycle_result<TC>(pre, 1);
     if (L0.patch.np) {
