@@ -1650,6 +1650,7 @@ __global__ __launch_bounds__(NR) void k_patch_build(const int *__restrict__ tile
     if (tid == 0) cnt = nrows = bad = 0;
     __syncthreads();
     auto insert = [&](int g, int e) {
+        if (load_relaxed(&bad)) return;  // (a full table would be walked round by every further row)
         unsigned h = ((unsigned)g * 2654435761u) % H;
         for (int tries = 0; tries < H; ++tries, h = (h + 1) % H) {
             const int old = atomicCAS(&key[h], -1, g);
@@ -1657,7 +1658,7 @@ __global__ __launch_bounds__(NR) void k_patch_build(const int *__restrict__ tile
             if (old != -1) continue;
             const int slot = atomicAdd(&cnt, 1);
             if (slot >= NS) {
-                bad = 1;
+                store_relaxed(&bad, 1);
                 return;
             }
             val[h] = slot;
@@ -1666,7 +1667,7 @@ __global__ __launch_bounds__(NR) void k_patch_build(const int *__restrict__ tile
             col[slot] = (unsigned char)color[perm[g]];
             return;
         }
-        bad = 1;
+        store_relaxed(&bad, 1);
     };
     const int T = 2 * ncol - 1;
     for (int q = beg + tid; q < end; q += NR) insert(tile_rows[q], T);
@@ -2188,12 +2189,21 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
         const int nt = t.k[0] * t.k[1];
         int *tile = need(T, T.a, n), *cnt = need(T, T.b, nt), *trp = need(T, T.c, (size_t)nt + 1);
         int *rows = need(T, T.d, n), *srt = need(T, T.e, 2 * (size_t)n), *err = need(T, T.err, 1);
+        int *range = need(T, T.f, 3);
         k_fill_int<<<1, 64, 0, s>>>(err, 1, 0);
         k_fill_int<<<blocks_for(nt), kBlock, 0, s>>>(cnt, nt, 0);
         k_tile_of<<<nb, kBlock, 0, s>>>(n, L.perm.get(), L.origin.get(), t, tile);
         k_col_count<<<nb, kBlock, 0, s>>>(n, tile, cnt);
         GLK_CHECK_LAUNCH();
-        scan_excl(cnt, trp, nt, T, s);
+        scan_tiles(cnt, trp, nt, need(T, T.scan, 4 * ((size_t)nt / kScanTile + 4) + 64), s);
+        // tiles are equal parts of the plane: on a graded mesh one may hold most of
+        // the level, which no patch can (and whose rows would be sorted by one wave,
+        // at a cost that grows with their square)
+        k_fill_int<<<1, 64, 0, s>>>(range, 1, 0);
+        k_fill_int<<<1, 64, 0, s>>>(range + 1, 1, nt);
+        k_row_widths<<<1, kBlock, 0, s>>>(trp, nullptr, range, range + 2);
+        GLK_CHECK_LAUNCH();
+        if (read_int(range + 2, s) > NR) continue;
         k_fill_int<<<blocks_for(nt), kBlock, 0, s>>>(cnt, nt, 0);
         k_tile_fill<<<nb, kBlock, 0, s>>>(n, tile, trp, cnt, rows);
         k_sort_rows<<<(nt + kRowWaves - 1) / kRowWaves, kBlock, 0, s>>>(nt, trp, rows, rows, srt, srt + n);
