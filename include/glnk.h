@@ -22,7 +22,9 @@
  *     8-byte aligned and must not alias unless a call says so.
  *   - Handles (gl_mesh, gl_precond) are owned by the library and freed by the
  *     matching *_destroy call.  Only *_create / *_setup calls allocate device
- *     memory; apply and solve calls allocate nothing.
+ *     memory; apply and solve calls allocate nothing, but for what the first
+ *     solve of its kind keeps for the next: a stored basis (gl_krylov_opts) and
+ *     the explicit sub-cycle of automatic tiles (gl_tiles).
  *   - stream is a hipStream_t (NULL = the default stream).  Calls enqueue work
  *     on it; calls that return host scalars (norms, solve info) synchronise it.
  *   - Every call returns a gl_status; arguments are validated before any work
@@ -267,7 +269,10 @@ void gl_precond_destroy(gl_precond *pre);
  * solves, where it pays, the sub-cycle of a level of at most 2048 rows as an
  * explicit matrix).  With any field nonzero every field is taken as it stands;
  * {0, 512, 0, 0} is each field's fixed default (one dispatch per pass, no
- * explicit sub-cycle).  What a handle does depends on the last call alone, and
+ * explicit sub-cycle).  The automatic sub-cycle of n rows takes 24 n^2 bytes and
+ * a workspace (about 55 n^2 bytes), allocated by the first solve and
+ * held by the handle; a batch holds one workspace for all its handles, of at
+ * most 1.5 GB.  Where there is no memory for it solves do without.  What a handle does depends on the last call alone, and
  * gl_precond_get_tiles gives values that restore it (bottom_rows 0 only for
  * automatic):
  *   lane_shift: lanes that share one row in the sparse kernels of levels >= 1

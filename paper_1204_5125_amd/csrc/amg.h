@@ -279,7 +279,7 @@ struct gl_precond {
     int tail = 0;                  // level whose sub-cycle is one dense product (the coarsest if none)
     // With automatic tiles solves apply the sub-cycle of level stail (0: none)
     // as an explicit matrix, formed by the first solve after a numeric setup
-    // (solver_tail_enqueue)
+    // (solver_tail_enqueue); its memory comes with the first of them
     int stail = 0;
     bool stail_current = false;
     int bottom_rows = glk::kBottomRows;  // tile choices (gl_precond_set_tiles)
@@ -309,10 +309,9 @@ struct gl_precond {
     // work-group
     glk::DevBuf<double2> tinv64;
     glk::DevBuf<float2> tinv32;
-    glk::DevBuf<double2> tws;      // per-block vectors of that formation
+    glk::DevBuf<double2> tws;      // per-block vectors of that formation (a batch has one for all its handles)
     glk::DevBuf<char> tdesc64;
     size_t tws_col = 0;            // elements per block of columns in tws
-    int tws_cols = 0;              // blocks of columns per launch
     int lds64 = 0, lds32 = 0;      // dynamic LDS bytes of the bottom kernel
 };
 
@@ -381,6 +380,16 @@ constexpr int kPcgMaxSteps = 64;
 void scale_by_volume(const gl_mesh *m, const double2 *x, double2 *y, hipStream_t s);
 void bottom_descriptors(gl_precond *pre, hipStream_t s);
 void form_tail(gl_precond *pre, hipStream_t s);  // after a numeric setup
-void solver_tail_enqueue(const gl_precond *pre, const Launch &L);  // at the start of a solve
+// At the start of a solve: the explicit sub-cycle of the current values, with vectors
+// in the handle's own workspace or a shared one of `blocks` blocks of columns
+struct TailSpace {
+    double2 *p = nullptr;
+    int blocks = 0;
+};
+void solver_tail_enqueue(const gl_precond *pre, const Launch &L, const TailSpace &shared = {});
+// elements of a shared workspace that forming it takes (at most `most`, more than that
+// only for a single block), 0 when there is nothing to form
+size_t solver_tail_space(const gl_precond *pre, size_t most, int *blocks);
+void solver_tail_drop(const gl_precond *pre);  // no memory for it: solves do without
 uint64_t new_precond_uid();
 }  // namespace glk

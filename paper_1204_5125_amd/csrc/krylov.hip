@@ -1462,6 +1462,7 @@ struct gl_batch {
     glk::BatchScalars *host_sc = nullptr;
     int *host_status = nullptr;  // per instance: the coarsest factor's failure flag of the last setup
     glk::DevBuf<unsigned char> init_args;
+    glk::DevBuf<double2> tail_ws;  // workspace of the explicit sub-cycles' formation
     unsigned char *staging = nullptr;
     size_t staging_cap = 0;
     int64_t graph_launches = 0;
@@ -1711,11 +1712,57 @@ static void batch_flush(gl_batch *B, double2 *const *psi, int i, bool refine, bo
     GLK_CHECK_LAUNCH();
 }
 
+// Places in the batch's workspace for the sub-cycles that these instances' solves
+// form.  As many as fit at a time (kTailWorkspace): all but the last such set are
+// formed here, the last one's with the start of the solves.
+static std::vector<TailSpace> batch_tails(gl_batch *B, const std::vector<int> &members)
+{
+    std::vector<TailSpace> space(B->meshes.size());
+    const size_t most = kTailWorkspace / sizeof(double2);
+    std::vector<std::vector<int>> sets(1);
+    std::vector<size_t> at(B->meshes.size(), 0);
+    size_t used = 0, largest = 0;
+    for (int i : members) {
+        const size_t need = solver_tail_space(B->pre[i], most, &space[i].blocks);
+        if (need == 0) continue;
+        if (used + need > most && used > 0) {
+            sets.emplace_back();
+            used = 0;
+        }
+        at[i] = used;
+        used += need;
+        largest = std::max(largest, used);
+        sets.back().push_back(i);
+    }
+    if (largest > B->tail_ws.count) {
+        try {
+            B->tail_ws.alloc(largest);
+        } catch (const Error &e) {
+            if (e.status != GL_ERR_OUT_OF_MEMORY) throw;
+            for (const auto &set : sets)
+                for (int i : set) solver_tail_drop(B->pre[i]);
+            return std::vector<TailSpace>(B->meshes.size());
+        }
+    }
+    for (const auto &set : sets)
+        for (int i : set) space[i].p = B->tail_ws.get() + at[i];
+    for (size_t k = 0; k + 1 < sets.size(); ++k) {
+        batch_run_direct(B, sets[k], [&](int i, std::vector<Step> &r) {
+            solver_tail_enqueue(B->pre[i], Launch{nullptr, &r}, space[i]);
+        });
+        GLK_HIP(hipStreamSynchronize(B->s));  // the staging buffer is filled again
+    }
+    return space;
+}
+
 static void batch_init(gl_batch *B, double2 *const *psi, const std::vector<int> &members, bool refine,
                        bool use_pre, double rtol, int max_iter)
 {
+    std::vector<TailSpace> space;
+    if (use_pre) space = batch_tails(B, members);
     batch_run_direct(B, members, [&](int i, std::vector<Step> &r) {
         Launch L{nullptr, &r};
+        if (use_pre) solver_tail_enqueue(B->pre[i], L, space[i]);
         Ksolve k = batch_ksolve(B, psi, i, refine, use_pre);
         with_dim(B->meshes[i]->g, [&](auto D) { ksolve_init<decltype(D)::value>(k, rtol, max_iter, L); });
     });

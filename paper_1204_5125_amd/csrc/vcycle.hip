@@ -2365,6 +2365,31 @@ static void fill_bottom(gl_precond *pre, BottomDesc<T> &D)
     }
 }
 
+// memory of the explicit sub-cycle of level ex
+static void tail_matrix(gl_precond *pre, int ex)
+{
+    const size_t nt = (size_t)pre->L[ex].n;
+    if (pre->tinv64.count < nt * nt) pre->tinv64.alloc(nt * nt);
+    if (pre->tinv32.count < nt * nt) pre->tinv32.alloc(nt * nt);
+}
+
+static int tail_blocks(const gl_precond *pre, int ex) { return (pre->L[ex].n + kTailBlock - 1) / kTailBlock; }
+
+// blocks of columns that one launch forms at most: as many as the workspace bound allows
+static int tail_fit(const gl_precond *pre, int ex)
+{
+    const size_t fit = kTailWorkspace / (pre->tws_col * sizeof(double2));
+    return (int)std::max<size_t>(1, std::min<size_t>(tail_blocks(pre, ex), fit));
+}
+
+// the handle's own workspace for forming it
+static TailSpace tail_workspace(gl_precond *pre, int ex)
+{
+    const int blocks = tail_fit(pre, ex);
+    if (pre->tws.count < pre->tws_col * blocks) pre->tws.alloc(pre->tws_col * blocks);
+    return TailSpace{pre->tws.get(), blocks};
+}
+
 void bottom_descriptors(gl_precond *pre, hipStream_t s)
 {
     const int last = pre->nlev - 1;
@@ -2401,17 +2426,19 @@ void bottom_descriptors(gl_precond *pre, hipStream_t s)
     pre->bottom = first;
     pre->stail = solver_tail(pre);
     pre->stail_current = false;
+    pre->tinv64.release();
+    pre->tinv32.release();
+    pre->tws.release();
+    pre->tws_col = 0;
     if (const int ex = tail < last ? tail : pre->stail) {  // the level with an explicit sub-cycle
-        const int nt = pre->L[ex].n;
-        pre->tinv64.alloc((size_t)nt * nt);
-        pre->tinv32.alloc((size_t)nt * nt);
         size_t col = 0;
         for (int l = ex; l <= last; ++l) col += tail_vectors(l == ex, l == last) * (size_t)pre->L[l].n;
         pre->tws_col = col * kTailBlock;  // elements per block of columns
-        const int nblk = (nt + kTailBlock - 1) / kTailBlock;
-        const size_t fit = kTailWorkspace / (pre->tws_col * sizeof(double2));
-        pre->tws_cols = (int)std::max<size_t>(1, std::min<size_t>(nblk, fit));  // blocks per launch
-        pre->tws.alloc(pre->tws_col * pre->tws_cols);
+        if (ex == tail) {
+            // (a solve's is allocated by the first solve: a handle may serve applications only)
+            tail_matrix(pre, ex);
+            tail_workspace(pre, ex);
+        }
         // formation: levels ex .. coarsest with the coarsest inverse
         BottomDesc<double> dt;
         const int keep = pre->tail;
@@ -2425,12 +2452,7 @@ void bottom_descriptors(gl_precond *pre, hipStream_t s)
         pre->tdesc64.alloc(sizeof(dt));
         GLK_HIP(hipMemcpyAsync(pre->tdesc64.get(), &dt, sizeof(dt), hipMemcpyHostToDevice, s));
     } else {
-        pre->tinv64.release();
-        pre->tinv32.release();
-        pre->tws.release();
         pre->tdesc64.release();
-        pre->tws_col = 0;
-        pre->tws_cols = 0;
     }
     BottomDesc<double> d64;
     BottomDesc<float> d32;
@@ -2448,15 +2470,15 @@ void bottom_descriptors(gl_precond *pre, hipStream_t s)
 // The explicit sub-cycle of level `tail` from the current values: FP64
 // columns, kTailBlock per work-group and as many work-groups per launch as
 // the workspace holds, then the FP32 copy.
-static void tail_columns(gl_precond *pre, int ex, const Launch &L)
+static void tail_columns(gl_precond *pre, int ex, const TailSpace &ws, const Launch &L)
 {
     const int nt = pre->L[ex].n;
     const auto *D = reinterpret_cast<const BottomDesc<double> *>(pre->tdesc64.get());
-    const int nblk = (nt + kTailBlock - 1) / kTailBlock;
-    for (int b0 = 0; b0 < nblk; b0 += pre->tws_cols) {
-        const int nb = std::min(pre->tws_cols, nblk - b0);
+    const int nblk = tail_blocks(pre, ex);
+    for (int b0 = 0; b0 < nblk; b0 += ws.blocks) {
+        const int nb = std::min(ws.blocks, nblk - b0);
         L.run<TailColumns<double>, kTailThreads>(
-            nb, TailColumns<double>{D, pre->tws.get(), pre->tws_col, b0 * kTailBlock, nb, pre->tinv64.get()});
+            nb, TailColumns<double>{D, ws.p, pre->tws_col, b0 * kTailBlock, nb, pre->tinv64.get()});
     }
     const int64_t nn = (int64_t)nt * nt;
     L.run(blocks_for(nn), Narrow<float>{(int)nn, pre->tinv64.get(), pre->tinv32.get(), nullptr});
@@ -2464,15 +2486,57 @@ static void tail_columns(gl_precond *pre, int ex, const Launch &L)
 
 void form_tail(gl_precond *pre, hipStream_t s)
 {
-    if (pre->has_values && pre->tail < pre->nlev - 1) tail_columns(pre, pre->tail, Launch{s});
+    if (pre->has_values && pre->tail < pre->nlev - 1)
+        tail_columns(pre, pre->tail, tail_workspace(pre, pre->tail), Launch{s});
 }
 
-void solver_tail_enqueue(const gl_precond *cpre, const Launch &L)
+// f, which allocates for the explicit sub-cycle of solves on pre: where there is no
+// memory for it, solves on the handle do without
+template <class F>
+static bool tail_allocates(gl_precond *pre, F &&f)
+{
+    try {
+        f();
+        return true;
+    } catch (const Error &e) {
+        if (e.status != GL_ERR_OUT_OF_MEMORY) throw;
+    }
+    (void)hipGetLastError();
+    pre->tinv64.release();
+    pre->tinv32.release();
+    pre->tws.release();
+    pre->stail = 0;
+    pre->uid = new_precond_uid();
+    return false;
+}
+
+size_t solver_tail_space(const gl_precond *cpre, size_t most, int *blocks)
+{
+    gl_precond *pre = const_cast<gl_precond *>(cpre);
+    if (!pre->stail || pre->stail_current) return 0;
+    if (!tail_allocates(pre, [&] { tail_matrix(pre, pre->stail); })) return 0;
+    *blocks = (int)std::max<size_t>(1, std::min<size_t>(tail_fit(pre, pre->stail), most / pre->tws_col));
+    return pre->tws_col * *blocks;
+}
+
+void solver_tail_enqueue(const gl_precond *cpre, const Launch &L, const TailSpace &shared)
 {
     gl_precond *pre = const_cast<gl_precond *>(cpre);
     if (!pre->stail || pre->stail_current) return;
-    tail_columns(pre, pre->stail, L);
+    TailSpace ws = shared;
+    if (!ws.p && !tail_allocates(pre, [&] {
+            tail_matrix(pre, pre->stail);
+            ws = tail_workspace(pre, pre->stail);
+        }))
+        return;
+    tail_columns(pre, pre->stail, ws, L);
     pre->stail_current = true;
+}
+
+void solver_tail_drop(const gl_precond *cpre)
+{
+    gl_precond *pre = const_cast<gl_precond *>(cpre);
+    tail_allocates(pre, [] { fail(GL_ERR_OUT_OF_MEMORY, ""); });
 }
 
 }  // namespace glk
