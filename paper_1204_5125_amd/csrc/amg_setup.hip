@@ -2179,6 +2179,11 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
     // the line, 147 either way; 513^2, 44 075 rows, 143 and 141)
     const int tries[8][2] = {{1024, 380}, {1024, 340}, {1024, 300}, {1024, 256},
                              {512, 96}, {512, 64}, {1024, 112}, {1024, 64}};
+    const Arena::Mark before = pre->arena.mark();
+    const auto drop = [&] {  // (a try's kernels are done when its outcome has been read)
+        S = PatchSet();
+        pre->arena.rewind(before);
+    };
     for (int k = n >= kPatchLarge ? 0 : 4; k < 8; ++k) {
         const int NR = tries[k][0], own = tries[k][1];
         S.rows = NR;
@@ -2241,9 +2246,9 @@ static void build_patches(gl_precond *pre, int l, SymTmp &T, hipStream_t s)
             GLK_CHECK_LAUNCH();
             return;
         }
+        drop();
         if (fits) break;
     }
-    S = PatchSet();
 }
 
 void precond_symbolic(gl_precond *pre, hipStream_t s)

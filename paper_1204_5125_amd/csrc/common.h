@@ -225,6 +225,24 @@ struct Arena {
         left -= bytes;
         return q;
     }
+    // rewind gives back what was taken since the mark: by buffers that are released by
+    // now and that nothing on the device uses any more
+    struct Mark {
+        size_t chunks;
+        char *at;
+        size_t left, next;
+    };
+    Mark mark() const { return Mark{chunks.size(), at, left, next}; }
+    void rewind(const Mark &m)
+    {
+        while (chunks.size() > m.chunks) {
+            if (spare) spare->give(std::move(chunks.back()));
+            chunks.pop_back();
+        }
+        at = m.at;
+        left = m.left;
+        next = m.next;
+    }
 };
 
 // buffers that the thread allocates inside the scope come from the arena (none: nullptr)

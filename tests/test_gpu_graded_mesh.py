@@ -53,3 +53,43 @@ def test_crowded_tile(glnk, k, side, far):
         z = torch.empty(mo.n, dtype=torch.complex128, device="cuda")
         pre.apply(torch.from_numpy(r).cuda(), z)
         assert np.abs(z.cpu().numpy() - want).max() <= tol * np.abs(want).max(), prec
+
+
+def disc_handle_bytes(glnk, k, power):
+    """Device memory of a handle on a disc of k rings with radii r^power."""
+    from paper_1204_5125_amd import meshes
+    x, t = meshes.disc(k)
+    rel = np.linalg.norm(x, axis=1, keepdims=True) / meshes.RADIUS
+    held, sizes = [0], {}
+
+    def alloc(n):
+        p = torch.cuda.caching_allocator_alloc(n)
+        sizes[p] = n
+        held[0] += n
+        return p
+
+    def release(p):
+        held[0] -= sizes.pop(p)
+        torch.cuda.caching_allocator_delete(p)
+
+    glnk.gl_set_allocator(alloc, release)
+    try:
+        m = glnk.Mesh.simplicial(x * rel ** (power - 1), t, mu=0.3)
+        before = held[0]
+        pre = glnk.Precond(m, torch.from_numpy(inputs.random_phase_state(m.n, seed=1)).cuda(), max_coarse=64)
+        used = held[0] - before
+        pre.close()
+        m.close()
+        assert held[0] == 0
+    finally:
+        glnk.gl_set_allocator(None, None)
+    return used
+
+
+@pytest.mark.parametrize("k,power", [(64, 2.5), (128, 1.8), (128, 2.0)])
+def test_tries_that_do_not_fit_hold_nothing(glnk, k, power):
+    """Rings moved towards the centre leave the connectivity, and with it the
+    hierarchy, as they were.  With radii r^5 no level's fullest tile fits a patch
+    and nothing is built; with these, patches are built and found not to fit:
+    the handle holds as much."""
+    assert disc_handle_bytes(glnk, k, power) == disc_handle_bytes(glnk, k, 5)
