@@ -992,18 +992,6 @@ struct PatchPost {
         if (R.own && gate_go) xo[R.g] = xs[threadIdx.x];
     }
 };
-template <class T>
-struct FillZero {
-    int n;
-    C<T> *x;
-    const int *gate;
-    __device__ void operator()(int bx, int) const
-    {
-        GATE();
-        const int i = bx * kBlock + threadIdx.x;
-        if (i < n) x[i] = mk<T>(0, 0);
-    }
-};
 
 template <class T>
 struct Narrow {
