@@ -2337,15 +2337,18 @@ void precond_numeric_enqueue(gl_precond *pre, const double2 *psi, const Launch &
               PValues{n, lv.A.rp.get(), lv.A.ci.get(), lv.A.v64.get(), lv.diag64.get(), lv.agg.get(), lv.aggsize.get(),
                       lv.rho.get(), lv.P.rp.get(), lv.P.ci.get(), lv.P.v64.get()});
         L.run(blocks_for(lv.R.nnz), RValues{lv.R.nnz, lv.rsrc.get(), lv.P.v64.get(), lv.R.v64.get()});
-        // A P: about a lane per entry of a row
+        // A P: eight lanes a row on the finest levels in 2D (five-point and triangle
+        // rows, at most 5 entries of A P), 16 on denser ones.  us by 4 / 8 / 16 lanes:
+        // level 0 of 1025^2 122 / 90 / 134, of a disc of 49 537 nodes 11.5 / 7.5 / 11;
+        // level 0 of 129^3 657 / 448 / 378, of a tetrahedron of 12 001 nodes 54 / 21 /
+        // 10; levels 1 of 1025^2 54 / 38 / 32, of 129^3 1006 / 425 / 305.
         auto ap = [&](auto lanes) {
             constexpr int LPR = decltype(lanes)::value;
             L.run(blocks_for((int64_t)n * LPR),
                   ApValues<LPR>{n, lv.A.rp.get(), lv.A.ci.get(), lv.A.v64.get(), lv.P.rp.get(), lv.P.ci.get(),
                                 lv.P.v64.get(), lv.AP.rp.get(), lv.AP.ci.get(), lv.AP.v64.get()});
         };
-        if (lv.AP.nnz <= 5 * (int64_t)n) ap(std::integral_constant<int, 4>{});
-        else if (lv.AP.nnz <= 12 * (int64_t)n) ap(std::integral_constant<int, 8>{});
+        if (lv.AP.nnz <= 5 * (int64_t)n) ap(std::integral_constant<int, 8>{});
         else ap(std::integral_constant<int, 16>{});
         L.run(blocks_for((int64_t)Nx.A.nnz * kRapLanes),
               RapValues{Nx.A.nnz, lv.rap_tp.get(), lv.rap_pair.get(), lv.rap_mir.get(), lv.R.v64.get(), lv.AP.v64.get(),
