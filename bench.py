@@ -37,7 +37,7 @@ RTOL = 1e-10
 L0_TILED_NAME = "L0 Gauss-Seidel in LDS tiles (L0PreTile, L0PostTile)"
 KERNEL_NAMES = {1: "MinresJapply", 2: "L0 Gauss-Seidel sweeps (L0PreBlack, L0Sweep, L0Last)",
                 3: "L0Residual", 4: "level-0 transfers (CsrSpmv restriction, L0ProlongBlack)", 5: "MinresVupdate", 6: "k_minres_wx",
-                7: "GlResidual", 8: "SgsPass (Gauss-Seidel colour pass, levels >= 1)"}
+                7: "GlResidual", 8: "Gauss-Seidel sweeps of levels >= 1 (PatchPre, PatchPost; SgsPass where patches do not fit)"}
 
 
 def log(msg):
@@ -47,11 +47,11 @@ def log(msg):
 MAX_COARSE = 512
 BATCH_HALVINGS = 3   # batched continuation: halvings of a step whose Newton fails
 # tiles of the single counter pass (--one-pass): the autotuner's choice for
-# this grid on MI355X, FP32 and FP64 alike (lane_shift, bottom_rows, dense_rows)
+# this grid on MI355X with the FP32 V-cycle (lane_shift, bottom_rows, dense_rows)
 ONE_PASS_TILES = (0, 64, 4096)
 # the autotuner's full choice without the profiler (--fixed-tiles): level 0 in
-# 16 x 16-node LDS tiles with the FP32 V-cycle, one dispatch per pass in FP64
-FIXED_TILES = {"fp32": ONE_PASS_TILES + (3,), "fp64": ONE_PASS_TILES + (0,)}
+# 32 x 16-node LDS tiles (32 x 32 ones time within 1 %); in FP64 the automatic tiles
+FIXED_TILES = {"fp32": ONE_PASS_TILES + (2,), "fp64": (0, 0, 0, 0)}
 COPY_BYTES = 256 << 20   # counter calibration copy: reads and writes this many bytes
 # HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE counter passes
 # (calibrated on the copy), valid for the kernel sources with this fingerprint;
@@ -160,21 +160,20 @@ def cpu_baseline():
 def iteration_bytes(glnk, pre, precision):
     """Algorithmic bytes of the V-cycle kernels the profiler does not count,
     per MINRES iteration, from the handle's hierarchy: per multi-kernel
-    level >= 1 the residual (operator, b, x, r) and the transfers
-    (P / R entries, both vectors), and the dense product of the explicit
-    sub-cycle or coarsest inverse."""
+    level >= 1 the transfers (P / R entries, the residual written and read, both
+    coarse vectors), and the dense product of the explicit sub-cycle or coarsest
+    inverse.  (The residual is formed by the sweep's kernel from entries it holds:
+    no bytes of its own.  With automatic tiles the handle does not tell its
+    sub-cycle's level: the coarsest inverse is counted, a little less.)"""
     info = pre.info()
     tiles = glnk.gl_precond_get_tiles(pre)
     sz = 16.0 if precision == glnk.GL_FP64 else 8.0
-    sizes, nnz = info["sizes"], info["nnz"]
-    nlev = info["nlev"]
+    sizes, nlev = info["sizes"], info["nlev"]
     dense = next((l for l in range(1, nlev) if sizes[l] <= tiles["dense_rows"]), nlev - 1)
     total = 0.0
     for l in range(1, dense):
-        total += nnz[l] * (4 + sz) + (sizes[l] + 1) * 4 + 3 * sizes[l] * sz          # residual
-    for l in range(1, dense):
         pn = int(pre.export(l, "P_rp")[-1])
-        total += 2 * (pn * (4 + sz) + (sizes[l] + sizes[l + 1] + 2) * 4) + 3 * (sizes[l] + sizes[l + 1]) * sz
+        total += 2 * (pn * (4 + sz) + (sizes[l] + sizes[l + 1] + 2) * 4) + 2 * (sizes[l] + sizes[l + 1]) * sz
     total += sizes[dense] ** 2 * sz + 2 * sizes[dense] * sz                          # dense product
     return total
 
@@ -829,9 +828,9 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--fixed-tiles", action="store_true",
                     help="jacobian: skip the autotuner and use the tiles it picks on MI355X for this grid "
-                         "(lane_shift 0, bottom_rows 64, dense_rows 4096; level 0 in 16 x 16 LDS tiles with "
-                         "the FP32 V-cycle, one dispatch per pass with FP64), so that a profiled run times "
-                         "the configuration of an unprofiled one")
+                         "(FP32 V-cycle: lane_shift 0, bottom_rows 64, dense_rows 4096, level 0 in 32 x 16 "
+                         "LDS tiles; FP64: automatic), so that a profiled run times the configuration of "
+                         "an unprofiled one")
     ap.add_argument("--profile-kernel", type=int, default=8,
                     help="internal kernel id for the roofline (see gl_profile_start)")
     ap.add_argument("--one-pass", action="store_true",
@@ -927,8 +926,8 @@ def main():
 
     # roofline: an identical pass per kernel class with its launches timed by
     # HIP events on the stream they run on.  The coarse-level Gauss-Seidel
-    # sweeps take the most GPU time (latency-bound small launches); the
-    # level-0 sweeps move the most bytes.
+    # sweeps (a dispatch each, bound by their passes) and the level-0 sweeps,
+    # which move the most bytes, take about the same time.
     # level 0 of the FP32 V-cycle: one dispatch per pass, or LDS tiles of
     # shape l0_tiled (the same profile id; the counters are per form); the
     # automatic choice takes shape 2
@@ -954,8 +953,8 @@ def main():
     roof = profile(args.profile_kernel)
     roof_l0 = profile(2) if args.profile_kernel != 2 else roof
     # whole iteration: the algorithmic bytes of every profiled kernel class in
-    # one pass of the workload, plus the coarse residuals, transfers and the
-    # dense product from the hierarchy, per MINRES iteration, over the timed
+    # one pass of the workload, plus the coarse transfers and the dense product
+    # from the hierarchy, per MINRES iteration, over the timed
     # run's time per iteration
     by_class = {}
     for kid in sorted(KERNEL_NAMES):
@@ -970,7 +969,7 @@ def main():
                  "achieved": bytes_iter / t_iter32 / 1e9,
                  "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": bytes_iter / t_iter32 / 1e9 / HBM_PEAK_GBS,
                  "bytes_per_iteration": bytes_iter, "us_per_iteration": t_iter32 * 1e6,
-                 "bytes_by_kernel_class": by_class, "bytes_coarse_residual_transfer_dense": rest,
+                 "bytes_by_kernel_class": by_class, "bytes_coarse_transfer_dense": rest,
                  "traffic": None}
     # the headline leg: the same kernels per iteration plus the basis traffic
     # of the reorthogonalisation, per node 4 (j + 1) bytes read by the dots
