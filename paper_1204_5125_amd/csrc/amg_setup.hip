@@ -892,9 +892,11 @@ __host__ __device__ constexpr bool rho_normed(int k) { return k == kRhoSteps / 2
 
 // The whole estimate of a small level by one work-group, from its CSR matrix: LPR
 // lanes per row, the matrix in registers (S rows of kPwEntries entries per
-// thread), the vector in LDS.  A step is a few LDS reads and two barriers (0.8 us)
-// where a dispatch takes 4-5 with its gap: 33^2, two levels, 0.38 ms per numeric
-// setup with a dispatch per step, 0.29 with S = 4 for every level, now 0.25.
+// thread), the vector in LDS.  A step is a few LDS reads and two barriers where a
+// dispatch takes 4-5 us with its gap.  us per step by <LPR, S>: <2, 1> and <4, 1> 0.8,
+// <8, 1> 1.1, <2, 2> 1.3, <8, 2> 2.0, <2, 4> 2.2, <16, 2> 2.3, <4, 4> 2.8, <8, 4> 3.4,
+// <16, 4> 4.1.  33^2, two levels, 0.38 ms per numeric setup with a dispatch per step,
+// 0.29 with S = 4 for every level, now 0.22.
 constexpr int kPwThreads = 1024, kPwEntries = 4;
 
 template <int LPR, int S>
@@ -1078,7 +1080,7 @@ struct RValues {
 // lanes load an entry of A each, count the entries of P's rows below them and find
 // their own) and put into LDS: every lane adds those of its column, in the order of
 // the row.  (Each lane searching every P row for its column: chains of dependent
-// loads, 97x81x65 807 us per numeric setup, now 290; 129^3 2.7 ms, now 1.0.  The
+// loads, 97x81x65 807 us per numeric setup, now 218; 129^3 2.7 ms, now 0.76.  The
 // products passed round by shuffles, five words each: 750 us and 2.65 ms.)
 template <int LPR>
 struct ApValues {
@@ -2137,8 +2139,14 @@ static void build_apply_copies(gl_precond *pre, SymTmp &T, hipStream_t s)
 // colour pass where patches do not pay or do not fit: rows of more than
 // kPatchWidth neighbours (the 3D hierarchies: 30 entries and 15-30 colours reach
 // over the whole level), a patch of more than 1024 rows, or more than kPatchMost
-// updated rows per row of the level.  (Measured on the 2D levels:
-// 3-5 with 96 rows of a patch's own, 2.3-2.7 with 256-380.)
+// updated rows per row of the level.  On every level measured that fits there are
+// fewer (3-5 with 96 rows of a patch's own, 2.6-2.7 with 256-380; a disc whose rings
+// crowd, 5 419 rows, 4.8), and up to there patches win (us per iteration with levels
+// of more than 3 in passes / in patches: disc of 49 537 nodes 121 / 79, 1025^2 341 /
+// 258), so the bound keeps only unmeasured levels out.  kPatchLevel is where they stop
+// winning (us per iteration, passes / patches: level 1 of 394 113 rows FP64 547 / 509,
+// FP32 418 / 386, of 700 587 rows 976 / 957 and 766 / 748, of 1 094 000 rows 1188 /
+// 1212 and 897 / 888).
 constexpr double kPatchMost = 8.0;
 constexpr int kPatchLevel = 1 << 20;  // rows of a level in patches at most
 constexpr int kPatchLarge = 65536;    // rows from which a level takes the largest patches that fit

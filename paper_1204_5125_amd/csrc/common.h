@@ -184,7 +184,8 @@ struct SpareChunks {
 // a few chunks that live as long as the handle does (declare the arena before
 // the buffers).  A hierarchy has some 280 buffers; one by one they cost 8 us each
 // to get and 17 to give back: setting up and destroying the one of a 257^2 grid
-// took 19.2 ms, and takes 14.1 (18.1 with chunks that are not kept, 100-150 us each).
+// took 19.2 ms, and takes 13.7, the first one of a mesh, which finds no spare chunks,
+// 14.0.
 struct Arena {
     static constexpr size_t kFirst = size_t(1) << 20, kChunk = size_t(32) << 20, kMost = size_t(8) << 20;
     std::shared_ptr<SpareChunks> spare;

@@ -13,11 +13,13 @@
 //     made it so), and only black residuals are formed;
 //   - after the coarse correction only the black values x_b + (P x_c)_b are
 //     read (by the first red update), so only black nodes are prolonged.
-// On the coarser levels the zero start and the first two colour passes of the
-// pre-smoothing sweep are one dispatch for the same reason.  Below the first
-// level with at most dense_rows rows (a tile choice) the cycle is a fixed
-// linear map of that level's right-hand side; it is formed as a dense matrix
-// at setup and applied as one product, like the coarsest inverse.
+// In 2D these passes run on tiles in LDS, two kernels a cycle (L0PreTile,
+// L0PostTile).  The coarser levels run a whole symmetric sweep per dispatch on
+// patches of rows (PatchPre, PatchPost) where the patches fit, and a dispatch per
+// colour and half a sweep (SgsPass) where they do not.  Below the first level with at most dense_rows rows (a tile choice), or that
+// solver_tail picks for solves, the cycle is a fixed linear map of that level's
+// right-hand side; it is formed as a dense matrix and applied as one product, like
+// the coarsest inverse.
 #include <cstring>
 #include <type_traits>
 
@@ -2278,6 +2280,12 @@ void vcycle_enqueue(const gl_precond *pre, const double2 *v, double2 *z, const i
 // the formation 3 per step of the cycle, and its gathers, about 46 bytes per
 // column and stored entry, at 7 TB/s (545 rows: 0.17 ms for 29 us a cycle; 195
 // rows: 0.04 for 16; 5 592 rows of 31 colours: 12 ms for 270 us, not taken).
+// The choice hardly depends on the cycles assumed: 12 to 200 give the same levels on
+// all of 15 grids and domains measured (65^2-1025^2, 17x4001, 49^3-129^3, discs,
+// tetrahedra), 6 gives up the sub-cycles of 1247, 1540 and 1387 rows (257^2, 8 / 24 /
+// 152 iterations 1.47 / 2.41 / 10.22 ms with 24, 1.44 / 2.54 / 11.89 with 6).  2048
+// rows keep matrix and workspace under 0.35 GB a handle; the sub-cycle of 2561 rows
+// (97^3) would take 0.55 GB and 18.7 ms for 24 iterations, 26.0 without.
 constexpr int kSolverCycles = 24, kSolverTail = 2048;
 
 static int solver_tail(const gl_precond *pre)
