@@ -55,9 +55,9 @@ FIXED_TILES = {"fp32": ONE_PASS_TILES + (2,), "fp64": (0, 0, 0, 0)}
 COPY_BYTES = 256 << 20   # counter calibration copy: reads and writes this many bytes
 # HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE counter passes
 # (calibrated on the copy), valid for the kernel sources with this fingerprint;
-# "2t2", "2t3": the level-0 class in 32 x 16 and 16 x 16 LDS tiles
-TRAFFIC = {"csrc_sha256": "001a72ced063a46ec0329231d3fb9f116a665765e5dd16b1156c50e0eaf5befd",
-           8: 4971861.0, 2: 21189661.2, "2t2": 48767097.9, "2t3": 48785225.5}
+# "2t1", "2t2", "2t3": the level-0 class in 32 x 32, 32 x 16 and 16 x 16 LDS tiles
+TRAFFIC = {"csrc_sha256": "54f63a72dd577e3779360c00b61ae429ce101f4bd118bca32be6527b592ffb88",
+           8: 45594942.0, 2: 20793426.7, "2t1": 49063150.5, "2t2": 49700725.2, "2t3": 48820557.6}
 
 
 def csrc_fingerprint():
