@@ -56,7 +56,7 @@ COPY_BYTES = 256 << 20   # counter calibration copy: reads and writes this many 
 # HBM bytes per launch from the FETCH_SIZE / WRITE_SIZE counter passes
 # (calibrated on the copy), valid for the kernel sources with this fingerprint;
 # "2t1", "2t2", "2t3": the level-0 class in 32 x 32, 32 x 16 and 16 x 16 LDS tiles
-TRAFFIC = {"csrc_sha256": "6ff56120b86cf339b4587e731e94eb2fb7b1fef0816a80a94cc82947dd2889ee",
+TRAFFIC = {"csrc_sha256": "03270abcfbc403daa7a546c4bc57f9c12c9340720d610bb9fa7c62b4950dd797",
            8: 45594942.0, 2: 20793426.7, "2t1": 49063150.5, "2t2": 49700725.2, "2t3": 48820557.6}
 
 

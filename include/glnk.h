@@ -230,11 +230,12 @@ typedef struct {
  * they depend only on the grid) and its values.  *inout != NULL (a handle from
  * an earlier call on the same mesh): recompute only the values for the new psi
  * (opts may then be NULL; a different precision or cycle count is applied).
- * Memory of a handle: about 1.4 KB per node of a 2D grid, 1.9 KB in 3D, 2 to 7 KB
+ * Memory of a handle: 1.4 to 2 KB per node of a 2D grid, 1.9 KB in 3D, 2 to 8 KB
  * on 2D simplicial meshes (padded copies of the levels whose sweeps run on
- * patches).  Blocks of up to 32 MB that a destroyed hierarchy used stay with the
- * mesh for its next one, at most 128 MB, until the mesh and its handles are
- * destroyed; not with the caller's allocator (gl_set_allocator).
+ * patches).  Blocks of up to 32 MB that building it took, and that a destroyed one
+ * held, stay with the mesh (a batch's with the batch) for the next one, at most 128
+ * MB, until the mesh and its handles are destroyed; not with the caller's allocator
+ * (gl_set_allocator).
  * Errors: SINGULAR (coarsest operator not positive definite, e.g. psi = 0 and
  * A = 0), UNSUPPORTED (a coarse row longer than the setup kernels handle),
  * OUT_OF_MEMORY, HIP. */

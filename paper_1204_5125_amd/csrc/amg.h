@@ -375,6 +375,10 @@ void patch_values_enqueue(gl_precond *pre, const Launch &L);  // of the levels t
 void precond_numeric_enqueue(gl_precond *pre, const double2 *psi, const Launch &L);
 void precond_numeric_finish(gl_precond *pre, bool singular, hipStream_t s);
 void check_amg_opts(const gl_amg_opts *opts, const char *who);
+// a new handle (opts checked), built from the spare chunks given, which get its own
+// when it is destroyed
+gl_precond *precond_new(const gl_mesh *mesh, const double2 *psi, const gl_amg_opts &opts,
+                        const std::shared_ptr<SpareChunks> &spare, hipStream_t s);
 void pcg_calibrate(gl_precond *pre, hipStream_t s);  // R_inf: the CG step count of this setup
 constexpr int kPcgMaxSteps = 64;
 void scale_by_volume(const gl_mesh *m, const double2 *x, double2 *y, hipStream_t s);

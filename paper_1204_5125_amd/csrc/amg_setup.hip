@@ -2267,7 +2267,7 @@ void precond_symbolic(gl_precond *pre, hipStream_t s)
     L0.n = n0;
     L0.A.n = L0.A.m = n0;
     SymTmp T;
-    T.arena.spare = m->spare;
+    T.arena.spare = pre->arena.spare;
     {
         int *cnt = need(T, T.a, n0);
         if (m->g.simplicial) k_l0s_count<<<nb0, kBlock, 0, s>>>(n0, m->g.rp, cnt);
@@ -2431,6 +2431,22 @@ void check_amg_opts(const gl_amg_opts *opts, const char *who)
         fail(GL_ERR_INVALID_ARGUMENT, w + ": max_levels must be in 1..16");
 }
 
+gl_precond *precond_new(const gl_mesh *mesh, const double2 *psi, const gl_amg_opts &opts,
+                        const std::shared_ptr<SpareChunks> &spare, hipStream_t s)
+{
+    std::unique_ptr<gl_precond> pre(new gl_precond());
+    pre->uid = new_precond_uid();
+    pre->mesh = mesh;
+    pre->opts = opts;
+    pre->arena.spare = spare;
+    {
+        const ArenaScope small(&pre->arena);
+        precond_symbolic(pre.get(), s);
+    }
+    precond_numeric(pre.get(), psi, s);
+    return pre.release();
+}
+
 uint64_t new_precond_uid()
 {
     static std::atomic<uint64_t> next{1};
@@ -2452,22 +2468,7 @@ gl_status gl_precond_setup(const gl_mesh *mesh, const void *psi, const gl_amg_op
         if (!pre && !opts) fail(GL_ERR_INVALID_ARGUMENT, "gl_precond_setup: opts required for a new handle");
         if (opts) check_amg_opts(opts, "gl_precond_setup");
         if (!pre) {
-            pre = new gl_precond();
-            try {
-                pre->uid = new_precond_uid();
-                pre->mesh = mesh;
-                pre->opts = *opts;
-                {
-                    pre->arena.spare = mesh->spare;
-                    const ArenaScope small(&pre->arena);
-                    precond_symbolic(pre, s);
-                }
-                precond_numeric(pre, (const double2 *)psi, s);
-            } catch (...) {
-                delete pre;
-                throw;
-            }
-            *inout = pre;
+            *inout = precond_new(mesh, (const double2 *)psi, *opts, mesh->spare, s);
         } else {
             if (opts) {
                 if (opts->max_coarse != pre->opts.max_coarse || opts->max_levels != pre->opts.max_levels)

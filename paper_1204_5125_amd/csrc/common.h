@@ -149,9 +149,9 @@ struct DevBuf {
     T *get() const { return p; }
 };
 
-// Chunks that the hierarchies of a mesh have given back, for the next one: at
-// most kKeep bytes, freed with the last of the mesh and its hierarchies.  A chunk
-// comes here only when nothing on the device uses it any more.
+// Chunks that the hierarchies of a mesh, or of a batch, have given back, for the
+// next one: at most kKeep bytes, freed with the last of the mesh (the batch) and its
+// hierarchies.  A chunk comes here only when nothing on the device uses it any more.
 struct SpareChunks {
     static constexpr size_t kKeep = size_t(128) << 20;
     std::mutex lock;

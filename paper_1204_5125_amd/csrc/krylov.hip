@@ -1450,6 +1450,9 @@ struct BatchGroup {
 struct gl_batch {
     std::vector<gl_mesh *> meshes;
     std::vector<gl_precond *> pre;
+    // one pool for all its handles: their symbolic scratch is the same memory, and
+    // the meshes keep nothing of it (a pool each had kept up to 128 MB a mesh)
+    std::shared_ptr<glk::SpareChunks> spare = std::make_shared<glk::SpareChunks>();
     std::vector<gl_tiles> tiles;
     hipStream_t s = nullptr;
     std::vector<glk::BatchGroup> groups;
@@ -1998,7 +2001,9 @@ static gl_status batch_newton(gl_batch *B, double2 *const *psi, const gl_newton_
                     built.push_back(i);
                     continue;
                 }
-                gl_status ps = gl_precond_setup(B->meshes[i], psi[i], &o.amg, &B->pre[i], B->s);
+                gl_status ps = guarded([&] {  // (the options are checked)
+                    B->pre[i] = precond_new(B->meshes[i], psi[i], o.amg, B->spare, B->s);
+                });
                 if (ps == GL_OK) ps = gl_precond_set_tiles(B->pre[i], &B->tiles[i]);
                 if (ps != GL_OK) {
                     st[i] = ps;

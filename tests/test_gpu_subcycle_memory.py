@@ -144,3 +144,24 @@ def test_workspace_in_turns(glnk, allocator, N, count):
         m, psi = mesh(glnk, N), state(mesh(glnk, N).n, 10 + i)
         glnk.gl_newton_solve(m, psi, fixed_steps=1, krylov_rtol=1e-3, krylov_max_iter=200, max_coarse=16)
         assert np.array_equal(psi.cpu().numpy(), got[i])
+
+
+def test_batch_leaves_nothing_with_its_meshes(glnk):
+    """The memory that a batch's handles took is gone with the batch, also while
+    its meshes live (hipMalloc; the first batch is for what the runtime keeps)."""
+    def used():
+        torch.cuda.synchronize()
+        free, total = torch.cuda.mem_get_info()
+        return total - free
+
+    ms = [mesh(glnk, 129) for _ in range(8)]
+    psis = [state(m.n, 10 + i) for i, m in enumerate(ms)]
+    for _ in range(2):
+        before = used()
+        batch = glnk.Batch(ms)
+        batch.newton_solve(psis, fixed_steps=1, krylov_rtol=1e-2, krylov_max_iter=50, raise_on_fail=False)
+        held = used() - before
+        batch.close()
+        left = used() - before
+    assert held > 8 * 20e6
+    assert left <= 8e6
